@@ -213,10 +213,16 @@ EBC_API ebc_status ebc_marginal_gains(ebc_dataset* ds, const double* m, const in
  * submodular_function_optimization_cardinality_constraint; Sec. 4.1: every
  * step scores all not-yet-selected points). Starts from S = {} (resets the
  * dataset state), runs all k steps on the device with no host round trip.
- * Each step: gains of all n points -> masked argmax -> every candidate
+ * Each step: gains of the candidates -> masked argmax -> every candidate
  * within a window of the best is re-scored in float64 with direct
  * differences -> the best float64 gain wins, ties to the lowest index ->
  * m_v <- min(m_v, d(v, c*)) in float64 -> f(S_t) = L({e0}) - |V|^-1 sum m_v.
+ * The first step computes the gains of all n points. Where that takes longer
+ * than a few launches (rows up to 128 values; the library decides by n and
+ * d), a later step computes only those of the points whose earlier gain, an
+ * upper bound of the present one because gains never grow, still reaches the
+ * window: the same window, hence the same picks. While profiling is on every
+ * step computes all n gains.
  *   k         0 <= k <= n (k = 0 is a no-op).
  *   sel_out   [device] int32 [k]: selected indices in pick order.
  *   f_out     [device] float64 [k]: f(S_1) .. f(S_k).
@@ -441,8 +447,9 @@ EBC_API int32_t ebc_tune_cache_size(void);
 /* Per-kernel timing of ebc_greedy with HIP events recorded on the call's
  * stream around each step's marginal-gains launch and around the whole step.
  * Off by default; when on, ebc_greedy records 3 events per step (host-side
- * event objects, no device memory). ebc_profile_read waits for the last
- * recorded event and returns the totals since the last reset. */
+ * event objects, no device memory), and every step scores all n points, so
+ * that the gains time is that of whole launches. ebc_profile_read waits for
+ * the last recorded event and returns the totals since the last reset. */
 typedef struct {
     double gains_ms;        /* summed duration of the marginal-gains kernel */
     double select_ms;       /* summed duration of the rest of each step */

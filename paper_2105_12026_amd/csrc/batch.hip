@@ -176,6 +176,7 @@ ebc_status ebc_greedy_batched(ebc_batch* bt, const int32_t* k, int32_t* const* s
     InstDesc* hd = reinterpret_cast<InstDesc*>(h + bt->tl.desc);
     for (int32_t i = 0; i < bt->count; ++i) {
         fill_desc(bt->ds[i], k[i], sel_out[i], f_out[i], gain_out ? gain_out[i] : nullptr, &hd[i]);
+        hd[i].lazy = 0;
         bt->ds[i]->stats.steps = k[i];
     }
     memcpy(h + bt->tl.row_pre, bt->h_row_pre.data(), bt->h_row_pre.size() * sizeof(int64_t));

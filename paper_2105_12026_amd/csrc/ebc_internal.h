@@ -43,6 +43,8 @@ struct DevState {
     int32_t gexp;        // 2^gexp >= m_v / 2 for every point and every m loaded since the dataset's
                          // creation (raised, never lowered): the reduced-precision gains scale
                          // their clamped terms by 2^-gexp into [0, 1]
+    int32_t list_heads;  // heads and list of the current step (see lazy.h)
+    int32_t list_len;
     int32_t pad1;
 };
 
@@ -106,7 +108,7 @@ struct InstDesc {
     int32_t t0;                      // steps already done: a batched tick t runs step t0 + t
     int32_t dt, variant;
     int32_t metric;                  // dissimilarity: 0 squared Euclidean, 1 L1
-    int32_t pad_m;
+    int32_t lazy;                    // steps after the first re-evaluate only candidates that can win (lazy.h)
     int64_t chunk;                   // ground-set chunk of the gains kernel
     int32_t* sel;
     double* f;
@@ -258,6 +260,7 @@ struct PinnedTables {
 // Host helpers shared by the solo and batched paths.
 int64_t gains_chunk(const ebc_dataset* ds);
 int64_t gains_cand_tile(const ebc_dataset* ds);
+bool greedy_lazy(const ebc_dataset* ds);      // greedy steps of this dataset re-evaluate a list (lazy.h)
 int32_t gains_bucket(const ebc_dataset* ds);  // datasets with equal keys share a batched gains launch
 void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double* gain, InstDesc* out);
 
@@ -321,6 +324,12 @@ hipError_t launch_gains_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n
 hipError_t launch_gains_wide(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 hipError_t launch_gains_l1(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 hipError_t launch_gains(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
+// gains of the instance's heads (part 0) or list (part 1), see lazy.h
+hipError_t launch_gains_f32_list(const InstDesc& c, int32_t part, hipStream_t s);
+hipError_t launch_gains_lp_list(const InstDesc& c, int32_t part, hipStream_t s);
+hipError_t launch_gains_l1_list(const InstDesc& c, int32_t part, hipStream_t s);
+hipError_t launch_gains_list(const InstDesc& c, int32_t part, hipStream_t s);
+hipError_t launch_list_step(const InstDesc& c, hipStream_t s);
 int elem_bytes(ebc_dtype dt);
 
 // Byte offset of byte `byte` of row r in a tiled reduced-precision array whose

@@ -26,6 +26,7 @@
 // two more steps whose half-1 values are all zeros: KH - 2 matrix
 // instructions per column block instead of KH (50 instead of 52 at d = 100).
 #include "ebc_internal.h"
+#include "lazy.h"
 
 namespace ebc {
 
@@ -269,6 +270,14 @@ kb_gains_f32(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slo
     gains_f32_body<KP, TRIM>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
 }
 
+// Heads or list (lazy.h): the workgroups walk its (tile, chunk) pairs.
+template <int KP, bool TRIM>
+__global__ void __launch_bounds__(256) k_gains_f32_list(InstDesc c, int32_t part) {
+    int64_t items;
+    const GainsArgs ga = list_args(c, part, kGainsCandTile, &items);
+    for (int64_t i = blockIdx.x; i < items; i += gridDim.x) gains_f32_body<KP, TRIM>(ga, i);
+}
+
 template <int KP>
 static void launch_kp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
     const int64_t tiles = (n_cand + kGainsCandTile - 1) / kGainsCandTile;
@@ -289,6 +298,22 @@ hipError_t launch_gains_f32(const ebc_dataset* ds, const int32_t* cand, int64_t 
     switch (ds->k_pad) {
 #define EBC_KP(K) \
     case K: launch_kp<K>(ds, cand, n_cand, s); break;
+        EBC_F32_KPS(EBC_KP)
+#undef EBC_KP
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_gains_f32_list(const InstDesc& c, int32_t part, hipStream_t s) {
+    switch (c.k_pad) {
+#define EBC_KP(K)                                                                                              \
+    case K:                                                                                                    \
+        if (c.d <= K - 4)                                                                                      \
+            hipLaunchKernelGGL((k_gains_f32_list<K, true>), dim3(kListGrid), dim3(256), 0, s, c, part);        \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_gains_f32_list<K, false>), dim3(kListGrid), dim3(256), 0, s, c, part);       \
+        break;
         EBC_F32_KPS(EBC_KP)
 #undef EBC_KP
         default: return hipErrorInvalidValue;

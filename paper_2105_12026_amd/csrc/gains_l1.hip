@@ -20,6 +20,7 @@
 // are added in float64 per thread, and the 16 threads of each candidate are
 // added in a fixed order. Reads the caller's float32 rows directly.
 #include "ebc_internal.h"
+#include "lazy.h"
 
 namespace ebc {
 
@@ -53,7 +54,7 @@ struct L1Args {
     int* err;
 };
 
-__global__ void __launch_bounds__(256) k_gains_l1(L1Args a) {
+__device__ __forceinline__ void gains_l1_body(const L1Args& a, int64_t bid) {
     __shared__ float4 lc4[kL1Cand * kL1S / 4];
     __shared__ float4 lp4[kL1VTile * kL1S / 4];
     __shared__ float lm[kL1VTile];
@@ -63,8 +64,8 @@ __global__ void __launch_bounds__(256) k_gains_l1(L1Args a) {
 
     const int tid = threadIdx.x;
     const int tc = tid & 15, tv = tid >> 4;
-    const int split = int(blockIdx.x % unsigned(a.v_splits));
-    const int64_t ctile = int64_t(blockIdx.x / unsigned(a.v_splits));
+    const int split = int(bid % a.v_splits);
+    const int64_t ctile = bid / a.v_splits;
     const int d = a.d;
     const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(a.x) & 15) == 0;
 
@@ -170,22 +171,46 @@ __global__ void __launch_bounds__(256) k_gains_l1(L1Args a) {
     }
 }
 
+__host__ __device__ inline L1Args l1_args(const InstDesc& c, const GainsArgs& ga) {
+    L1Args a;
+    a.x = c.x;
+    a.hm = ga.hm;
+    a.cand = ga.cand;
+    a.n = c.n;
+    a.n_cand = ga.n_cand;
+    a.n_pad = ga.n_pad;
+    a.chunk = ga.chunk;
+    a.part_stride = ga.part_stride;
+    a.d = c.d;
+    a.v_splits = ga.v_splits;
+    a.part = ga.part;
+    a.err = ga.err;
+    return a;
+}
+
+__global__ void __launch_bounds__(256) k_gains_l1(L1Args a) { gains_l1_body(a, blockIdx.x); }
+
+// Heads or list (lazy.h): the workgroups walk its (tile, chunk) pairs.
+__global__ void __launch_bounds__(256) k_gains_l1_list(InstDesc c, int32_t part) {
+    int64_t items;
+    const L1Args a = l1_args(c, list_args(c, part, kL1Cand, &items));
+    for (int64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        gains_l1_body(a, i);
+        __syncthreads();  // the sums in LDS are read before the next pair overwrites them
+    }
+}
+
 }  // namespace
 
+hipError_t launch_gains_l1_list(const InstDesc& c, int32_t part, hipStream_t s) {
+    hipLaunchKernelGGL(k_gains_l1_list, dim3(kListGrid), dim3(256), 0, s, c, part);
+    return hipGetLastError();
+}
+
 hipError_t launch_gains_l1(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
-    L1Args a;
-    a.x = ds->x;
-    a.hm = ds->b.hm;
-    a.cand = cand;
-    a.n = ds->n;
-    a.n_cand = n_cand;
-    a.n_pad = ds->n_pad;
-    a.chunk = gains_chunk(ds);
-    a.part_stride = ds->n_pad;
-    a.d = ds->d;
-    a.v_splits = ds->v_splits;
-    a.part = ds->b.part;
-    a.err = &ds->b.state->error;
+    InstDesc c;
+    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
+    const L1Args a = l1_args(c, gains_args(c, cand, n_cand));
     const int64_t tiles = (n_cand + kL1Cand - 1) / kL1Cand;
     hipLaunchKernelGGL(k_gains_l1, dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s, a);
     return hipGetLastError();

@@ -40,6 +40,7 @@
 // points; each lane reads contiguous K from its half of a row (the order of
 // K inside a dot product is free as long as both operands use the same one).
 #include "ebc_internal.h"
+#include "lazy.h"
 #include "lp_mfma.h"
 
 namespace ebc {
@@ -768,6 +769,18 @@ constexpr int wide_stage(int DT, int KC) {
                                                             : 64;
 }
 
+// Heads or list (lazy.h): the workgroups walk its (tile, chunk)
+// pairs. The interleaved body serves every variant (their sums are the same).
+template <int DT, int KC, int CB, int VTS>
+__global__ void __launch_bounds__(256) k_gains_lp_list(InstDesc c, int32_t part) {
+    int64_t items;
+    const GainsArgs ga = list_args(c, part, LpGeom<DT, KC, CB, VTS>::CAND_TILE, &items);
+    for (int64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        gains_lp_sp_body<DT, KC, CB, VTS>(ga, i);
+        __syncthreads();  // every wave is done with the ring before the next pair fills it
+    }
+}
+
 template <int DT, int KC, int CB>
 __global__ void __launch_bounds__(512) k_gains_lp_pp(GainsArgs ga) {
     gains_lp_pp_body<DT, KC, CB>(ga, blockIdx.x);
@@ -883,6 +896,40 @@ hipError_t launch_gains_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n
             break;
         default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_gains_lp_list(const InstDesc& c, int32_t part, hipStream_t s) {
+    const int kc = c.k_pad / (c.dt == EBC_DT_FP8_E4M3 ? 64 : 16);
+#define EBC_LPL(DTV, K)                                                                                             \
+    case K:                                                                                                         \
+        hipLaunchKernelGGL((k_gains_lp_list<DTV, K, 2, wide_stage(DTV, K)>), dim3(kListGrid), dim3(256), 0, s, c,   \
+                           part);                                                                                   \
+        break;
+    switch (c.dt) {
+        case EBC_DT_BF16:
+            switch (kc) {
+                EBC_LPL(EBC_DT_BF16, 1) EBC_LPL(EBC_DT_BF16, 2) EBC_LPL(EBC_DT_BF16, 3) EBC_LPL(EBC_DT_BF16, 4)
+                EBC_LPL(EBC_DT_BF16, 5) EBC_LPL(EBC_DT_BF16, 6) EBC_LPL(EBC_DT_BF16, 7) EBC_LPL(EBC_DT_BF16, 8)
+                default: return hipErrorInvalidValue;
+            }
+            break;
+        case EBC_DT_F16:
+            switch (kc) {
+                EBC_LPL(EBC_DT_F16, 1) EBC_LPL(EBC_DT_F16, 2) EBC_LPL(EBC_DT_F16, 3) EBC_LPL(EBC_DT_F16, 4)
+                EBC_LPL(EBC_DT_F16, 5) EBC_LPL(EBC_DT_F16, 6) EBC_LPL(EBC_DT_F16, 7) EBC_LPL(EBC_DT_F16, 8)
+                default: return hipErrorInvalidValue;
+            }
+            break;
+        case EBC_DT_FP8_E4M3:
+            switch (kc) {
+                EBC_LPL(EBC_DT_FP8_E4M3, 1) EBC_LPL(EBC_DT_FP8_E4M3, 2)
+                default: return hipErrorInvalidValue;
+            }
+            break;
+        default: return hipErrorInvalidValue;
+    }
+#undef EBC_LPL
     return hipGetLastError();
 }
 

@@ -42,6 +42,26 @@ int64_t gains_cand_tile(const ebc_dataset* ds) {
     return ds->variant == 1 ? 512 : 256;
 }
 
+// A list step launches four kernels more than one that scores everything, and
+// its two short gains launches take 20 to 40 us; it pays once the launch over
+// all candidates takes longer than about that. Measured crossovers (us per
+// greedy step, all candidates / lists): float32 d = 16: 8192 points 63 / 64,
+// 12000 93 / 76; d = 100: 3000 82 / 109, 4096 97 / 86; BF16 d = 64: 16384
+// 89 / 90, 24000 131 / 95; L1 d = 20: 4096 68 / 67. The line is drawn on the
+// launch's time, n_pad^2 pairs of k_pad products plus the clamp and sum.
+bool greedy_lazy(const ebc_dataset* ds) {
+    if (ds->prof || wide_rows(ds->k_pad) || ds->v_splits < 4) return false;
+    const double pairs = double(ds->n_pad) * double(ds->n_pad);
+    double us;  // measured rates: 77 T products/s (float32), 20 (L1), 1250 (16 bit), 2500 (8 bit)
+    if (ds->metric == 1)
+        us = pairs * ds->d / 20e6;
+    else if (ds->dt == EBC_DT_F32)
+        us = pairs * (ds->k_pad + 2) / 77e6;
+    else
+        us = pairs * (ds->k_pad / (ds->dt == EBC_DT_FP8_E4M3 ? 2.0 : 1.0) + 27) / 1250e6;
+    return us > 20.0;
+}
+
 int32_t gains_bucket(const ebc_dataset* ds) {
     // last digit: the tile variant (reduced precision), for long rows the K
     // split, for float32 whether the rows' last 4 padded slots are empty (the
@@ -66,7 +86,7 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
     c.dt = int32_t(ds->dt);
     c.variant = ds->variant;
     c.metric = ds->metric;
-    c.pad_m = 0;
+    c.lazy = greedy_lazy(ds) ? 1 : 0;
     c.chunk = gains_chunk(ds);
     c.sel = sel;
     c.f = f;
@@ -769,6 +789,8 @@ __global__ void k_state_init(DevState* st) {
         st->tau_abs = 0.0;
         st->nmax = 0.0;
         st->gexp = 0;
+        st->list_heads = 0;
+        st->list_len = 0;
         st->pad1 = 0;
     }
 }

@@ -9,10 +9,17 @@
 //   k_pick     best float64 gain, ties to the lowest index; record the pick
 //   k_update   m_v <- min(m_v, d(v, c*)) in float64, per-block sums of m_v
 //   k_fsum     f(S_t) = L({e0}) - |V|^-1 sum_v m_v  (Alg. 1: sum, then / |V|)
+// Steps that score a list instead of every candidate (lazy.h) replace the
+// first three stages by
+//   k_list_sum    per-chunk sums of the heads or the list -> gsum
+//   k_list_build  candidates whose old gain reaches the window of the best head
+//   k_list_window the window out of the list
+// and k_update / k_fsum also choose the heads of the next step's list.
 // No step reads anything back to the host; all sums run in a fixed order.
 #include <math.h>
 
 #include "ebc_internal.h"
+#include "lazy.h"
 #include "quant.h"
 
 namespace ebc {
@@ -367,11 +374,45 @@ __device__ void pick_body(const InstDesc& c, int32_t t) {
     }
 }
 
+// Estimate of candidate v's present gain, and the block's best one: the gain
+// it had when it was last scored, times what is left of its own minimum since
+// (old: m_v before this step, which is what step 0 scored every candidate
+// with). The best of each block goes to bmax / barg.
+__device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, double old, double mv,
+                                    double* __restrict__ red, int* __restrict__ ri) {
+    const Buffers& b = c.b;
+    const int64_t v = blk * kBlock + threadIdx.x;
+    float* __restrict__ lm = list_m(c);
+    float m_scored = float(old);
+    if (t == 0)
+        lm[v] = m_scored;
+    else
+        m_scored = lm[v];
+    double est = -INFINITY;
+    if (!b.selected[v]) est = b.gsum[v] * (m_scored > 0.0f ? mv / double(m_scored) : 1.0);
+    __syncthreads();
+    red[threadIdx.x] = est;
+    ri[threadIdx.x] = int(v);
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if (threadIdx.x < w && better(red[threadIdx.x + w], ri[threadIdx.x + w], red[threadIdx.x], ri[threadIdx.x])) {
+            red[threadIdx.x] = red[threadIdx.x + w];
+            ri[threadIdx.x] = ri[threadIdx.x + w];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        b.bmax[blk] = red[0];
+        b.barg[blk] = ri[0];
+    }
+}
+
 // ---- update: m_v <- min(m_v, d(v, c*)) in float64, per-block sums of m_v ----
-__device__ void update_body(const InstDesc& c, int64_t blk) {
+__device__ void update_body(const InstDesc& c, int64_t blk, int32_t t) {
     static_assert(kNarrowMaxK <= kRescoreChunk, "short rows fit one staged piece");
     __shared__ double cx[kRescoreChunk];
     __shared__ double red[kBlock];
+    __shared__ int ri[kBlock];
     const Buffers& b = c.b;
     const float* __restrict__ x = c.x;
     const int d = c.d;
@@ -380,14 +421,14 @@ __device__ void update_body(const InstDesc& c, int64_t blk) {
         for (int k = threadIdx.x; k < d; k += kBlock) cx[k] = double(x[int64_t(cs) * d + k]);
     __syncthreads();
     const int64_t v = blk * kBlock + threadIdx.x;
-    double mv = 0.0;
+    double mv = 0.0, old = 0.0;
     if (v < c.n && cs < 0) {
-        mv = b.m64[v];
+        mv = old = b.m64[v];
     } else if (v < c.n) {
         const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
         double acc[1] = {0.0};
         row_terms<0, 1>(x + v * d, vec, d, cx, acc);
-        mv = b.m64[v];
+        mv = old = b.m64[v];
         if (acc[0] < mv) {
             mv = acc[0];
             b.m64[v] = mv;
@@ -401,14 +442,16 @@ __device__ void update_body(const InstDesc& c, int64_t blk) {
         __syncthreads();
     }
     if (threadIdx.x == 0) b.fpart[blk] = red[0];
+    if (c.lazy) block_best_estimate(c, blk, t, old, mv, red, ri);
 }
 
 // ---- L1 update (any row length): m_v <- min(m_v, sum_k |x_vk - x_c*k|) in
 // float64, the new member's values staged in LDS 128 at a time; per-block
 // sums of m_v as in update_body ----
-__device__ void update_l1_body(const InstDesc& c, int64_t blk) {
+__device__ void update_l1_body(const InstDesc& c, int64_t blk, int32_t t) {
     __shared__ float cx[kRescoreChunk];
     __shared__ double red[kBlock];
+    __shared__ int ri[kBlock];
     const Buffers& b = c.b;
     const float* __restrict__ x = c.x;
     const int d = c.d;
@@ -425,9 +468,9 @@ __device__ void update_l1_body(const InstDesc& c, int64_t blk) {
         if (live)
             for (int k = 0; k < kn; ++k) acc += fabs(double(xv[k0 + k]) - double(cx[k]));
     }
-    double mv = 0.0;
+    double mv = 0.0, old = 0.0;
     if (live) {
-        mv = b.m64[v];
+        mv = old = b.m64[v];
         if (cs >= 0 && acc < mv) {
             mv = acc;
             b.m64[v] = mv;
@@ -441,6 +484,7 @@ __device__ void update_l1_body(const InstDesc& c, int64_t blk) {
         __syncthreads();
     }
     if (threadIdx.x == 0) b.fpart[blk] = red[0];
+    if (c.lazy) block_best_estimate(c, blk, t, old, mv, red, ri);
 }
 
 // ---- long rows (padded length above 128): re-score and update ----
@@ -806,6 +850,210 @@ __device__ void fsum_body(const InstDesc& c, int32_t t) {
         __syncthreads();
     }
     if (threadIdx.x == 0) c.f[t] = c.b.state->l0 - red[0] / double(c.n);
+    if (!c.lazy) return;
+    // heads of the next step's list: the best estimate of each stretch
+    const int bps = list_stretch(c);
+    const int heads = (c.nb + bps - 1) / bps;
+    for (int h = threadIdx.x; h < heads; h += kBlock) {
+        double e = -INFINITY;
+        int row = c.b.barg[h * bps];
+        for (int i = h * bps; i < (h + 1) * bps && i < c.nb; ++i)
+            if (c.b.bmax[i] > e) {
+                e = c.b.bmax[i];
+                row = c.b.barg[i];
+            }
+        list_part(c, 0)[h] = row;
+    }
+    if (threadIdx.x == 0) {
+        c.b.state->list_heads = heads;
+        c.b.state->list_len = 0;
+    }
+}
+
+// ---- lists (lazy.h) ----
+// Per-chunk sums of the heads or the list -> gsum of their rows, and the m each
+// was scored with. A workgroup of 1024 threads takes 32 list positions at a
+// time; thread (p, q) adds chunks q, q + 32, ... of position p and the 32
+// sums are added in q order.
+constexpr int kListSumThreads = 1024;
+constexpr int kListSumPos = 32;
+__device__ void list_sum_body(const InstDesc& c, int32_t part, int64_t first, int64_t step) {
+    __shared__ double red[kListSumThreads / kListSumPos][kListSumPos];
+    const Buffers& b = c.b;
+    const int64_t cnt = list_count(c, part);
+    const ListGeom g = list_geom(c, cnt, list_tile(c.dt, c.metric));
+    const int32_t* __restrict__ rows = list_part(c, part);
+    const int p = threadIdx.x % kListSumPos, q = threadIdx.x / kListSumPos;
+    constexpr int Q = kListSumThreads / kListSumPos;
+    for (int64_t p0 = first * kListSumPos; p0 < cnt; p0 += step * kListSumPos) {
+        double s = 0.0;
+        if (p0 + p < cnt)
+            for (int i = q; i < g.splits; i += Q) s += b.part[int64_t(i) * g.stride + p0 + p];
+        red[q][p] = s;
+        __syncthreads();
+        if (q == 0 && p0 + p < cnt) {
+            for (int i = 1; i < Q; ++i) s += red[i][p];
+            const int64_t row = rows[p0 + p];
+            b.gsum[row] = b.selected[row] ? -INFINITY : s;
+            list_m(c)[row] = float(b.m64[row]);
+        }
+        __syncthreads();
+    }
+}
+
+// Append every unselected candidate whose last gain reaches the window of the
+// best head, less the rounding of a gain (lazy.h).
+// Rows are taken in the grouped order where there is one, so that neighbours
+// in the list are neighbours in space (their tiles clamp together).
+__device__ void list_build_body(const InstDesc& c, int64_t blk) {
+    __shared__ double red[kBlock];
+    __shared__ int wave_n[kBlock / 64];
+    __shared__ int base;
+    const Buffers& b = c.b;
+    const int heads = b.state->list_heads;
+    const int32_t* __restrict__ head = list_part(c, 0);
+    double best = -INFINITY;
+    for (int i = threadIdx.x; i < heads; i += kBlock) best = fmax(best, b.gsum[head[i]]);
+    red[threadIdx.x] = best;
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
+        __syncthreads();
+    }
+    best = red[0];
+    const double slack = 2.0 * (double(c.chunk) / 32.0 + 64.0) * 0x1p-24 * fabs(best);
+    const double thr = window_threshold(best, b.state) - slack;
+    const int64_t i = blk * kBlock + threadIdx.x;
+    const int64_t row = b.perm ? int64_t(b.perm[i]) : i;
+    const bool take = !b.selected[row] && b.gsum[row] >= thr;
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(take);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) wave_n[wave] = __popcll(hit);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int n = 0;
+        for (int w = 0; w < kBlock / 64; ++w) n += wave_n[w];
+        base = n ? atomicAdd(&b.state->list_len, n) : 0;
+    }
+    __syncthreads();
+    if (!take) return;
+    int at = base + __popcll(hit & ((uint64_t(1) << lane) - 1));
+    for (int w = 0; w < wave; ++w) at += wave_n[w];
+    list_rows(c)[at] = int32_t(row);
+}
+
+// The window out of the list (one block): the same candidates, and the same
+// rules above kWindowMax and kWindowCap of them, as wcount and wselect.
+// Entries land in index or rank order, so nothing depends on the list's order.
+__device__ void list_window_body(const InstDesc& c) {
+    __shared__ WindowEntry list[kWindowCap];
+    __shared__ double red[kSelThreads];
+    __shared__ int ri[kSelThreads];
+    __shared__ int found;
+    const Buffers& b = c.b;
+    const int tid = threadIdx.x;
+    const int len = b.state->list_len;
+    const int32_t* __restrict__ rows = list_rows(c);
+    double gb = -INFINITY;
+    int ib = 0x7fffffff;
+    for (int i = tid; i < len; i += kSelThreads) {
+        const int r = rows[i];
+        const double g = b.gsum[r];
+        if (better(g, r, gb, ib)) {
+            gb = g;
+            ib = r;
+        }
+    }
+    red[tid] = gb;
+    ri[tid] = ib;
+    if (tid == 0) found = 0;
+    __syncthreads();
+    for (int w = kSelThreads / 2; w > 0; w >>= 1) {
+        if (tid < w && better(red[tid + w], ri[tid + w], red[tid], ri[tid])) {
+            red[tid] = red[tid + w];
+            ri[tid] = ri[tid + w];
+        }
+        __syncthreads();
+    }
+    const double gmax = red[0];
+    const int first = ri[0];
+    const double thr = window_threshold(gmax, b.state);
+    for (int i = tid; i < len; i += kSelThreads) {
+        const int r = rows[i];
+        const double g = b.gsum[r];
+        if (!(g >= thr && g > -INFINITY)) continue;
+        const int at = atomicAdd(&found, 1);
+        if (at >= kWindowCap) continue;
+        list[at].g = g;
+        list[at].idx = r;
+        list[at].pad = 0;
+    }
+    __syncthreads();
+    const int total = found;
+    __syncthreads();  // every wave has read it: found is reused below
+    if (total <= kWindowCap) {
+        for (int i = tid; i < total; i += kSelThreads) {
+            int rank = 0;
+            if (total <= kWindowMax)
+                for (int j = 0; j < total; ++j) rank += list[j].idx < list[i].idx ? 1 : 0;
+            else
+                for (int j = 0; j < total; ++j) rank += better(list[j].g, list[j].idx, list[i].g, list[i].idx) ? 1 : 0;
+            if (rank < kWindowMax) b.wfinal[rank] = list[i];
+        }
+    } else {
+        // overflow: the best one, then the lowest indices among the others.
+        // The largest index taken is found by bisection (indices are distinct).
+        int lo = -1, hi = int(c.n);  // count(index <= lo) < kWindowMax - 1 <= count(index <= hi)
+        while (hi - lo > 1) {
+            const int mid = lo + (hi - lo) / 2;
+            if (tid == 0) found = 0;
+            __syncthreads();
+            int k = 0;
+            for (int i = tid; i < len; i += kSelThreads) {
+                const int r = rows[i];
+                const double g = b.gsum[r];
+                k += (g >= thr && g > -INFINITY && r <= mid && r != first) ? 1 : 0;
+            }
+            if (k) atomicAdd(&found, k);
+            __syncthreads();
+            if (found >= kWindowMax - 1)
+                hi = mid;
+            else
+                lo = mid;
+            __syncthreads();
+        }
+        if (tid == 0) found = 0;
+        __syncthreads();
+        for (int i = tid; i < len; i += kSelThreads) {
+            const int r = rows[i];
+            const double g = b.gsum[r];
+            if (!(g >= thr && g > -INFINITY && r <= hi && r != first)) continue;
+            const int at = atomicAdd(&found, 1);
+            if (at >= kWindowMax - 1) continue;
+            list[at].g = g;
+            list[at].idx = r;
+            list[at].pad = 0;
+        }
+        __syncthreads();
+        for (int i = tid; i < kWindowMax - 1; i += kSelThreads) {
+            int rank = 0;
+            for (int j = 0; j < kWindowMax - 1; ++j) rank += list[j].idx < list[i].idx ? 1 : 0;
+            b.wfinal[1 + rank] = list[i];
+        }
+        if (tid == 0) {
+            WindowEntry e;
+            e.g = gmax;
+            e.idx = first;
+            e.pad = 0;
+            b.wfinal[0] = e;
+        }
+    }
+    if (tid == 0) {
+        const int W = total < kWindowMax ? total : kWindowMax;
+        b.state->window_count = W;
+        if (total > b.state->window_max) b.state->window_max = total;
+        if (total > kWindowCap) b.state->window_overflow += 1;
+    }
 }
 
 // ---- solo kernels ----
@@ -814,8 +1062,8 @@ __global__ void __launch_bounds__(kBlock) k_wcount(InstDesc c) { wcount_body(c, 
 __global__ void __launch_bounds__(kSelThreads) k_wselect(InstDesc c) { wselect_body(c); }
 __global__ void __launch_bounds__(kBlock) k_rescore(InstDesc c) { rescore_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_pick(InstDesc c, int32_t t) { pick_body(c, t); }
-__global__ void __launch_bounds__(kBlock) k_update(InstDesc c) { update_body(c, blockIdx.x); }
-__global__ void __launch_bounds__(kBlock) k_update_l1(InstDesc c) { update_l1_body(c, blockIdx.x); }
+__global__ void __launch_bounds__(kBlock) k_update(InstDesc c, int32_t t) { update_body(c, blockIdx.x, t); }
+__global__ void __launch_bounds__(kBlock) k_update_l1(InstDesc c, int32_t t) { update_l1_body(c, blockIdx.x, t); }
 __global__ void __launch_bounds__(kBlock) k_rescore_long(InstDesc c) { rescore_long_body(c, blockIdx.x, blockIdx.y); }
 __global__ void __launch_bounds__(kBlock) k_update_long(InstDesc c) { update_long_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_dist_slices(InstDesc c) {
@@ -825,6 +1073,11 @@ __global__ void __launch_bounds__(kBlock) k_update_split(InstDesc c) { update_sp
 __global__ void __launch_bounds__(kBlock) k_dist_window(InstDesc c) { dist_window_body(c, blockIdx.x, blockIdx.y); }
 __global__ void __launch_bounds__(kBlock) k_rescore_split(InstDesc c) { rescore_split_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_fsum(InstDesc c, int32_t t) { fsum_body(c, t); }
+__global__ void __launch_bounds__(kListSumThreads) k_list_sum(InstDesc c, int32_t part) {
+    list_sum_body(c, part, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(kBlock) k_list_build(InstDesc c) { list_build_body(c, blockIdx.x); }
+__global__ void __launch_bounds__(kSelThreads) k_list_window(InstDesc c) { list_window_body(c); }
 
 // ---- batched kernels: blocks of row_pre[i] .. row_pre[i+1] belong to instance i;
 // tick t runs step t0 + t of each instance; instances whose k is reached skip ----
@@ -844,7 +1097,7 @@ __device__ __forceinline__ void rescore_short(const InstDesc& c, int64_t blk) {
     if (!wide_rows(c.k_pad)) rescore_body(c, blk);
 }
 __device__ __forceinline__ void update_short(const InstDesc& c, int64_t blk) {
-    if (!wide_rows(c.k_pad)) update_body(c, blk);
+    if (!wide_rows(c.k_pad)) update_body(c, blk, 1);
 }
 __device__ __forceinline__ void rescore_long(const InstDesc& c, int64_t blk) {
     if (wide_rows(c.k_pad)) rescore_long_body(c, blk, blockIdx.y);
@@ -885,19 +1138,23 @@ __global__ void __launch_bounds__(kBlock) kb_fsum(const InstDesc* __restrict__ d
 
 hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out, double* f_out,
                               double* gain_out, hipStream_t s, hipEvent_t ev_gains_done) {
-    hipError_t e = launch_gains(ds, nullptr, ds->n_pad, s);
-    if (e != hipSuccess) return e;
-    if (ev_gains_done && (e = hipEventRecord(ev_gains_done, s)) != hipSuccess) return e;
     InstDesc c;
     fill_desc(ds, t + 1, sel_out, f_out, gain_out, &c);
     const int nb = c.nb;
-    hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(kBlock), 0, s, c);
-    hipLaunchKernelGGL(k_wcount, dim3(nb), dim3(kBlock), 0, s, c);
-    hipLaunchKernelGGL(k_wselect, dim3(1), dim3(kSelThreads), 0, s, c);
+    hipError_t e = hipSuccess;
+    if (c.lazy && t > 0) {
+        if ((e = launch_list_step(c, s)) != hipSuccess) return e;
+    } else {
+        if ((e = launch_gains(ds, nullptr, ds->n_pad, s)) != hipSuccess) return e;
+        if (ev_gains_done && (e = hipEventRecord(ev_gains_done, s)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_wcount, dim3(nb), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_wselect, dim3(1), dim3(kSelThreads), 0, s, c);
+    }
     if (c.metric == 1) {
         hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_pick, dim3(1), dim3(kBlock), 0, s, c, t);
-        hipLaunchKernelGGL(k_update_l1, dim3(nb), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_update_l1, dim3(nb), dim3(kBlock), 0, s, c, t);
     } else if (wide_rows(c.k_pad)) {
         // small windows: pass 1 over slices of the dimension here, pass 2 inside k_rescore_long
         if (long_split(c)) hipLaunchKernelGGL(k_dist_window, dim3(nb, 16), dim3(kBlock), 0, s, c);
@@ -912,9 +1169,23 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
     } else {
         hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_pick, dim3(1), dim3(kBlock), 0, s, c, t);
-        hipLaunchKernelGGL(k_update, dim3(nb), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_update, dim3(nb), dim3(kBlock), 0, s, c, t);
     }
     hipLaunchKernelGGL(k_fsum, dim3(1), dim3(kBlock), 0, s, c, t);
+    return hipGetLastError();
+}
+
+// Gains, sums, list and window of a step that scores a list.
+hipError_t launch_list_step(const InstDesc& c, hipStream_t s) {
+    const unsigned sums = 256;  // workgroups; each walks its share of the list
+    for (int32_t part = 0; part < 2; ++part) {
+        const hipError_t e = launch_gains_list(c, part, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_list_sum, dim3(part ? sums : kListHeads / kListSumPos), dim3(kListSumThreads), 0, s, c,
+                           part);
+        if (part == 0) hipLaunchKernelGGL(k_list_build, dim3(c.nb), dim3(kBlock), 0, s, c);
+    }
+    hipLaunchKernelGGL(k_list_window, dim3(1), dim3(kSelThreads), 0, s, c);
     return hipGetLastError();
 }
 
@@ -946,6 +1217,11 @@ hipError_t launch_gains(const ebc_dataset* ds, const int32_t* cand, int64_t n_ca
     if (ds->metric == 1) return launch_gains_l1(ds, cand, n_cand, s);
     if (wide_rows(ds->k_pad)) return launch_gains_wide(ds, cand, n_cand, s);
     return ds->dt == EBC_DT_F32 ? launch_gains_f32(ds, cand, n_cand, s) : launch_gains_lp(ds, cand, n_cand, s);
+}
+
+hipError_t launch_gains_list(const InstDesc& c, int32_t part, hipStream_t s) {
+    if (c.metric == 1) return launch_gains_l1_list(c, part, s);
+    return c.dt == EBC_DT_F32 ? launch_gains_f32_list(c, part, s) : launch_gains_lp_list(c, part, s);
 }
 
 // Marginal-gains output: sum the per-chunk sums, divide by |V|.

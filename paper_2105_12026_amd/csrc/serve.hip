@@ -361,6 +361,7 @@ ebc_status ebc_server_step(ebc_server* sv, int32_t* completed) {
     for (int32_t i = 0; i < count; ++i) {
         Request* r = sv->active[i];
         fill_desc(r->ds, r->k, r->sel_d, r->f_d, r->gain_d, &hd[i]);
+        hd[i].lazy = 0;
         hd[i].t0 = r->t;
     }
     memcpy(h + sv->tl.row_pre, sv->h_row_pre.data(), sv->h_row_pre.size() * sizeof(int64_t));

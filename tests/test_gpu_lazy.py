@@ -1,0 +1,92 @@
+"""Greedy steps that score a list of candidates (csrc/lazy.h) against steps that
+score every candidate (what a profiled run does): the same picks, f and gains,
+bit for bit, since both re-score the same window in float64, and against the
+float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2105_12026_amd import ebc, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def points(data, n, d, seed):
+    rng = np.random.default_rng([91, seed])
+    if data == "curves":
+        return workloads.process_curves(rng, n, d).astype(np.float32)
+    if data == "normal":
+        return rng.standard_normal((n, d)).astype(np.float32)
+    x = workloads.gaussian_mixture(rng, n, d, 12)
+    if data == "outliers":
+        x[: n // 50] = rng.uniform(-20.0, 20.0, (n // 50, d))
+        x = x[rng.permutation(n)]
+    if data == "few":  # 7 distinct points: after 7 picks every gain is 0
+        x = x[rng.integers(0, 7, n)]
+    if data == "sorted":  # whole stretches of one cluster
+        x = x[np.argsort(x[:, 0])]
+    return x.astype(np.float32)
+
+
+def both(x, k, dtype, dist="sqeuclidean", graph=False):
+    """(sel, f, gain, window_max) of a full-scoring run and of a default run."""
+    t = torch.from_numpy(x).cuda()
+    out = []
+    for full in (True, False):
+        ds = ebc.Dataset(t, dtype=dtype, dist=dist)
+        if full:
+            ds.profile(True)
+        else:
+            ds.set_graph(graph)
+        for _ in range(2 if graph else 1):
+            sel, f, gain = ds.greedy(k)
+        st = ds.sync()
+        out.append((sel.cpu().numpy(), f.cpu().numpy(), gain.cpu().numpy(), st["window_max"]))
+    return out
+
+
+# sizes: smallest that keeps lists (2048 rows), one past a block, a padded tail, many stretches; d at both ends
+CASES = [
+    ("mixture", 2048, 16, 30, "f32", "sqeuclidean"),
+    ("mixture", 2049, 3, 30, "f32", "sqeuclidean"),
+    ("outliers", 9001, 100, 40, "f32", "sqeuclidean"),
+    ("sorted", 33000, 33, 25, "f32", "sqeuclidean"),
+    ("normal", 5000, 128, 12, "f32", "sqeuclidean"),
+    ("few", 3000, 20, 12, "f32", "sqeuclidean"),
+    ("curves", 7003, 64, 30, "bf16", "sqeuclidean"),
+    ("outliers", 20011, 100, 60, "bf16", "sqeuclidean"),
+    ("mixture", 2305, 8, 20, "f16", "sqeuclidean"),
+    ("sorted", 70001, 17, 20, "f16", "sqeuclidean"),
+    ("curves", 12345, 33, 20, "fp8", "sqeuclidean"),
+    ("few", 4097, 128, 12, "fp8", "sqeuclidean"),
+    ("mixture", 4100, 50, 12, "f32", "l1"),
+    ("outliers", 9217, 7, 20, "f32", "l1"),
+]
+
+
+@pytest.mark.parametrize("data,n,d,k,dtype,dist", CASES)
+def test_lists_pick_what_full_scoring_picks(data, n, d, k, dtype, dist):
+    x = points(data, n, d, n)
+    full, lists = both(x, k, dtype, dist)
+    assert lists[0].tolist() == full[0].tolist()
+    assert np.array_equal(lists[1], full[1]) and np.array_equal(lists[2], full[2])
+    assert lists[3] == full[3]  # the same window
+
+
+def test_lists_under_graph_replay():
+    x = points("mixture", 6001, 40, 5)
+    full, lists = both(x, 20, "f32", graph=True)
+    assert lists[0].tolist() == full[0].tolist() and np.array_equal(lists[1], full[1])
+
+
+@pytest.mark.parametrize("dtype,dist", [("f32", "sqeuclidean"), ("bf16", "sqeuclidean"), ("f32", "l1")])
+def test_lists_after_other_calls(dtype, dist):
+    """Gains asked for between runs use the buffers that hold the lists."""
+    x = torch.from_numpy(points("mixture", 4003, 24, 7)).cuda()
+    ds = ebc.Dataset(x, dtype=dtype, dist=dist)
+    a = [t.cpu().numpy() for t in ds.greedy(15)]
+    g0 = ds.marginal_gains().cpu().numpy()
+    b = [t.cpu().numpy() for t in ds.greedy(15)]
+    g1 = ds.marginal_gains().cpu().numpy()
+    ds.sync()
+    assert all(np.array_equal(p, q) for p, q in zip(a, b)) and np.array_equal(g0, g1)

@@ -303,14 +303,15 @@ EBC_API ebc_status ebc_sieve_streaming(ebc_dataset* ds, int32_t k, double eps, d
  * recorded once into a HIP graph (on a private stream; recording runs
  * nothing) and the graph is replayed on `stream` by every later call with
  * the same k, output pointers and gains variant; other calls re-record.
- * One graph launch replaces 8k+1 kernel launches, which is what bounds small
+ * One graph launch replaces 8 to 11 kernel launches a step, which is what bounds small
  * problems. Results are identical to eager mode. Ignored while profiling. */
 EBC_API ebc_status ebc_set_greedy_graph(ebc_dataset* ds, int32_t on);
 
 /* Batched greedy over many independent datasets (different n, d, k and
  * distance dtype). Per step tick the library issues one marginal-gains
- * launch per kernel bucket (same dtype, row padding and tile variant) and
- * seven step launches, each covering every instance; instances whose k is
+ * launch per kernel bucket (same dtype, row padding and tile variant; two
+ * short ones where instances score lists, see ebc_greedy) and the step
+ * launches, each covering every instance; instances whose k is
  * reached skip the remaining ticks. Every instance computes exactly what its
  * solo ebc_greedy computes (bitwise-identical selections, f and gains),
  * independent of the batch composition.
@@ -355,7 +356,7 @@ EBC_API ebc_status ebc_batch_info(ebc_batch* batch, int32_t* buckets, int64_t* g
  * ebc_server_step: one scheduler tick: admits queued requests in arrival
  * order while a slot is free and the head request fits the arena (the head
  * waits otherwise); advances every active request by one greedy step in one
- * batched launch set (one gains launch per kernel bucket, seven step
+ * batched launch set (one or two gains launches per kernel bucket, the step
  * launches); copies out and releases the requests that reached k, waiting
  * for `stream` only when one did. Each request computes exactly what a solo
  * ebc_greedy computes, alone or in any mix.

@@ -1,7 +1,8 @@
 // Many independent greedy instances (different n, d, k and distance dtype)
 // advanced together: per step tick one marginal-gains launch per kernel
-// bucket (same dtype, row padding and tile variant) plus the seven step
-// launches, each covering every instance through a block -> instance map.
+// bucket (same dtype, row padding and tile variant; two for lists, lazy.h)
+// plus the step launches, each covering every instance through a block ->
+// instance map.
 // Each instance runs exactly the arithmetic of its solo ebc_greedy (same
 // kernels bodies, same per-instance geometry), so results are bitwise equal
 // to solo runs and do not depend on the batch composition.
@@ -15,17 +16,6 @@
 
 using namespace ebc;
 
-namespace {
-
-struct Bucket {
-    int32_t key;
-    int32_t slot_begin, slots;  // slots [slot_begin, slot_begin + slots) of slot_inst
-    int32_t pre_off;            // its prefix array starts at wg_pre[pre_off] (slots + 1 entries)
-    int64_t total_wgs;
-};
-
-}  // namespace
-
 struct ebc_batch {
     int32_t count;
     std::vector<ebc_dataset*> ds;
@@ -37,7 +27,7 @@ struct ebc_batch {
     int64_t* d_wg_pre;
     int64_t total_rows;
     bool long_rows;  // some instance has rows longer than kNarrowMaxK
-    std::vector<Bucket> buckets;
+    std::vector<GainsBucket> buckets;
     std::vector<int64_t> h_row_pre, h_wg_pre;
     std::vector<int32_t> h_slot_inst;
     PinnedTables staging;
@@ -52,14 +42,11 @@ namespace {
 
 hipError_t enqueue_ticks(ebc_batch* bt, int32_t ticks, hipStream_t s) {
     hipError_t e = launch_reset_batched(bt->d_desc, bt->d_row_pre, bt->count, bt->total_rows, s);
-    for (int32_t t = 0; t < ticks && e == hipSuccess; ++t) {
-        for (const Bucket& b : bt->buckets) {
-            e = launch_gains_batched(b.key, bt->d_desc, bt->d_slot_inst + b.slot_begin, bt->d_wg_pre + b.pre_off,
-                                     b.slots, b.total_wgs, t, s);
-            if (e != hipSuccess) return e;
-        }
-        e = launch_step_batched(bt->d_desc, bt->d_row_pre, bt->count, bt->total_rows, t, bt->long_rows, s);
-    }
+    bool all = false, some = false;  // instances that score every candidate at every step / lists
+    for (const ebc_dataset* ds : bt->ds) (greedy_lists(ds) ? some : all) = true;
+    for (int32_t t = 0; t < ticks && e == hipSuccess; ++t)
+        e = launch_tick(bt->buckets, bt->d_desc, bt->d_row_pre, bt->d_slot_inst, bt->d_wg_pre, bt->count,
+                        bt->total_rows, t, t == 0 || all, t > 0 && some, bt->long_rows, s);
     return e;
 }
 
@@ -119,7 +106,7 @@ ebc_status ebc_batch_create(ebc_dataset* const* ds, int32_t count, void* workspa
     bt->h_slot_inst.clear();
     bt->h_wg_pre.clear();
     for (int32_t key : keys) {
-        Bucket b{};
+        GainsBucket b{};
         b.key = key;
         b.slot_begin = int32_t(bt->h_slot_inst.size());
         b.pre_off = int32_t(bt->h_wg_pre.size());
@@ -127,6 +114,7 @@ ebc_status ebc_batch_create(ebc_dataset* const* ds, int32_t count, void* workspa
         bt->h_wg_pre.push_back(0);
         for (int32_t i = 0; i < count; ++i) {
             if (gains_bucket(ds[i]) != key) continue;
+            b.lists |= greedy_lists(ds[i]);
             const int64_t tile = gains_cand_tile(ds[i]);
             acc += (ds[i]->n_pad + tile - 1) / tile * ds[i]->v_splits;
             bt->h_slot_inst.push_back(i);
@@ -176,7 +164,6 @@ ebc_status ebc_greedy_batched(ebc_batch* bt, const int32_t* k, int32_t* const* s
     InstDesc* hd = reinterpret_cast<InstDesc*>(h + bt->tl.desc);
     for (int32_t i = 0; i < bt->count; ++i) {
         fill_desc(bt->ds[i], k[i], sel_out[i], f_out[i], gain_out ? gain_out[i] : nullptr, &hd[i]);
-        hd[i].lazy = 0;
         bt->ds[i]->stats.steps = k[i];
     }
     memcpy(h + bt->tl.row_pre, bt->h_row_pre.data(), bt->h_row_pre.size() * sizeof(int64_t));
@@ -214,7 +201,7 @@ ebc_status ebc_batch_info(ebc_batch* bt, int32_t* buckets, int64_t* gains_workgr
     if (buckets) *buckets = int32_t(bt->buckets.size());
     if (gains_workgroups_per_tick) {
         int64_t w = 0;
-        for (const Bucket& b : bt->buckets) w += b.total_wgs;
+        for (const GainsBucket& b : bt->buckets) w += b.total_wgs;
         *gains_workgroups_per_tick = w;
     }
     if (row_blocks_per_tick) *row_blocks_per_tick = bt->total_rows;

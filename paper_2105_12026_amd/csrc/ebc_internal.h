@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/ebc.h"
 
 namespace ebc {
@@ -148,6 +150,41 @@ __device__ inline int find_slot(const int64_t* __restrict__ pre, int count, int6
     return lo;
 }
 
+// Row of the 32 x 32 matrix result that register r of a lane in `half` holds.
+__device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r / 4) + 4 * half + (r % 4); }
+
+// float64 sums over the 32 columns (lanes of one half) of each of a lane's 16
+// result rows. Every exchange halves the rows a lane still carries (the pairs
+// added are those of a plain butterfly per row, 16 exchanges instead of 80);
+// lanes col and col ^ 1 end with the total of register row col >> 1.
+__device__ __forceinline__ double column_sums16(const float (&acc)[16], int col) {
+    double v[8];
+    const bool up16 = (col & 16) != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float other = __shfl_xor(up16 ? acc[i] : acc[i + 8], 16, 64);
+        v[i] = double(up16 ? acc[i + 8] : acc[i]) + double(other);
+    }
+#pragma unroll
+    for (int h = 4; h > 0; h >>= 1) {
+        const bool up = (col & (2 * h)) != 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const double send = up ? v[i] : v[i + h];
+            v[i] = (up ? v[i + h] : v[i]) + __shfl_xor(send, 2 * h, 64);
+        }
+    }
+    return v[0] + __shfl_xor(v[0], 1, 64);
+}
+
+// Thread id that the compiler takes as unknown here: kernels that run a body
+// in a loop must not keep its lane addresses in registers across the loop.
+__device__ __forceinline__ int fresh_tid() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 struct Layout {
     size_t off_xq, off_scale, off_mu, off_n64, off_m0, off_m64, off_hn, off_ha, off_hm, off_sel, off_part, off_gsum, off_bmax,
         off_barg, off_bcnt, off_wstage, off_wfinal, off_rpart, off_fpart, off_state, off_perm, off_inv, off_xqp,
@@ -260,7 +297,8 @@ struct PinnedTables {
 // Host helpers shared by the solo and batched paths.
 int64_t gains_chunk(const ebc_dataset* ds);
 int64_t gains_cand_tile(const ebc_dataset* ds);
-bool greedy_lazy(const ebc_dataset* ds);      // greedy steps of this dataset re-evaluate a list (lazy.h)
+bool greedy_lists(const ebc_dataset* ds);       // greedy steps of this dataset can score lists (lazy.h) ...
+bool greedy_lists_solo(const ebc_dataset* ds);  // ... and are faster with them when it runs alone
 int32_t gains_bucket(const ebc_dataset* ds);  // datasets with equal keys share a batched gains launch
 void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double* gain, InstDesc* out);
 
@@ -300,6 +338,13 @@ hipError_t launch_gains_wide_batched(int32_t dt, int32_t ksplit, const InstDesc*
                                      hipStream_t s);
 hipError_t launch_gains_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst,
                                 const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t, hipStream_t s);
+// ... of the heads (part 0) or lists (part 1) of the instances at a list step (lazy.h)
+hipError_t launch_gains_f32_list_batched(int32_t k_pad, bool trim, const InstDesc* descs, const int32_t* slot_inst,
+                                         int32_t slots, int32_t t, int32_t part, hipStream_t s);
+hipError_t launch_gains_lp_list_batched(int32_t dt, int32_t kc, const InstDesc* descs, const int32_t* slot_inst,
+                                        int32_t slots, int32_t t, int32_t part, hipStream_t s);
+hipError_t launch_gains_list_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst, int32_t slots,
+                                     int32_t t, int32_t part, hipStream_t s);
 // 32-row candidate blocks per wave in the ping-pong gains variant (3):
 // two where the registers allow, one for long rows.
 constexpr int pp_blocks(int dt, int kc) {
@@ -307,10 +352,21 @@ constexpr int pp_blocks(int dt, int kc) {
 }
 // Tile variant recorded by the autotuner for this dataset's key, or -1.
 int32_t tuned_variant(const ebc_dataset* ds);
-// long_rows: some instance has rows longer than kNarrowMaxK (their re-score
-// and update run in the long-row kernels)
-hipError_t launch_step_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count, int64_t total_rows,
-                               int32_t t, bool long_rows, hipStream_t s);
+// One gains launch set of a batched tick: instances of equal kernel.
+struct GainsBucket {
+    int32_t key;
+    int32_t slot_begin, slots;  // slots [slot_begin, slot_begin + slots) of slot_inst
+    int32_t pre_off;            // its prefix array starts at wg_pre[pre_off] (slots + 1 entries)
+    int64_t total_wgs;
+    bool lists;                 // some of its instances score lists after their first step
+};
+// One tick of a batch. full: some instance scores all of its candidates in
+// it; lists: some instance scores a list. long_rows: some instance has rows
+// longer than kNarrowMaxK (their re-score and update run in the long-row
+// kernels).
+hipError_t launch_tick(const std::vector<GainsBucket>& buckets, const InstDesc* descs, const int64_t* row_pre,
+                       const int32_t* slot_inst, const int64_t* wg_pre, int32_t count, int64_t total_rows, int32_t t,
+                       bool full, bool lists, bool long_rows, hipStream_t s);
 hipError_t launch_reset_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count, int64_t total_rows,
                                 hipStream_t s);
 

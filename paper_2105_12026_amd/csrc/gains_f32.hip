@@ -75,7 +75,7 @@ __device__ __forceinline__ void gains_f32_body(const GainsArgs& ga, int64_t bid)
     __shared__ float lds_hm[VT];
     float* lds_x = reinterpret_cast<float*>(lds_x4);
 
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int col = lane & 31;  // MFMA column within a 32-block
@@ -88,13 +88,13 @@ __device__ __forceinline__ void gains_f32_body(const GainsArgs& ga, int64_t bid)
     int split;
     int64_t ctile;
     if (v_splits % 8 == 0) {
-        const int64_t ntiles = (n_cand + kGainsCandTile - 1) / kGainsCandTile;
-        const int64_t r = bid / 8;
-        split = int(bid % 8) + 8 * int(r / ntiles);
+        const uint32_t ntiles = uint32_t((n_cand + kGainsCandTile - 1) / kGainsCandTile);
+        const uint32_t r = uint32_t(bid) / 8;
+        split = int(uint32_t(bid) % 8) + 8 * int(r / ntiles);
         ctile = r % ntiles;
     } else {
-        split = int(bid % v_splits);
-        ctile = bid / v_splits;
+        split = int(uint32_t(bid) % uint32_t(v_splits));
+        ctile = uint32_t(bid) / uint32_t(v_splits);
     }
 
     // ---- candidate rows of this wave, in registers (MFMA A operand) ----
@@ -130,18 +130,12 @@ __device__ __forceinline__ void gains_f32_body(const GainsArgs& ga, int64_t bid)
 #pragma unroll
         for (int j = 0; j < KH; ++j) a[j] = 0.0f;
     }
-    // -hn of the 16 candidate rows this lane holds in the MFMA result.
+    // -hn of the 16 candidate rows this lane holds in the MFMA result, from
+    // the lanes that loaded these rows
+    const float hc = crow >= 0 ? hn[crow] : 0.0f;
     float nhn[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int64_t p = ctile * kGainsCandTile + wave * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-        float v = 0.0f;
-        if (p < n_cand) {
-            const int64_t row = cand ? int64_t(cand[p]) : p;
-            if (row >= 0 && row < n_pad) v = hn[row];
-        }
-        nhn[r] = -v;
-    }
+    for (int r = 0; r < 16; ++r) nhn[r] = -__shfl(hc, acc_row(r, half), 64);
     float acc_sum[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc_sum[r] = 0.0f;
@@ -236,19 +230,9 @@ __device__ __forceinline__ void gains_f32_body(const GainsArgs& ga, int64_t bid)
     for (int r = 0; r < 16; ++r) acc_sum[r] += __builtin_amdgcn_fmed3f(accP[r], 0.0f, hmP);
 
     // ---- sum over the 32 columns (ground points) of each half, in float64 ----
-    // Lane (half*32 + r), r < 16, keeps the total of candidate row
-    // 8*(r/4) + 4*half + r%4.
-    double mine = 0.0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        double v = double(acc_sum[r]);
-#pragma unroll
-        for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (col == r) mine = v;
-    }
-    if (col < 16) {
-        const int r = col;
-        const int64_t p = ctile * kGainsCandTile + wave * 32 + 8 * (r / 4) + 4 * half + (r % 4);
+    const double mine = column_sums16(acc_sum, col);
+    if ((col & 1) == 0) {
+        const int64_t p = ctile * kGainsCandTile + wave * 32 + acc_row(col >> 1, half);
         if (p < n_cand) part[int64_t(split) * part_stride + p] = 2.0 * mine;
     }
 }
@@ -266,7 +250,7 @@ kb_gains_f32(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slo
              const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
     const int j = find_slot(wg_pre, slots, blockIdx.x);
     const InstDesc c = descs[slot_inst[j]];
-    if (c.t0 + t >= c.k) return;
+    if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
     gains_f32_body<KP, TRIM>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
 }
 
@@ -276,6 +260,14 @@ __global__ void __launch_bounds__(256) k_gains_f32_list(InstDesc c, int32_t part
     int64_t items;
     const GainsArgs ga = list_args(c, part, kGainsCandTile, &items);
     for (int64_t i = blockIdx.x; i < items; i += gridDim.x) gains_f32_body<KP, TRIM>(ga, i);
+}
+
+template <int KP, bool TRIM>
+__global__ void __launch_bounds__(256, 2)
+kb_gains_f32_list(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst, int32_t slots, int32_t t,
+                  int32_t part) {
+    list_walk(descs, slot_inst, slots, t, part, kGainsCandTile,
+              [](const GainsArgs& ga, int64_t pair) { gains_f32_body<KP, TRIM>(ga, pair); });
 }
 
 template <int KP>
@@ -306,13 +298,14 @@ hipError_t launch_gains_f32(const ebc_dataset* ds, const int32_t* cand, int64_t 
 }
 
 hipError_t launch_gains_f32_list(const InstDesc& c, int32_t part, hipStream_t s) {
+    const unsigned grid = list_grid(c, part, kGainsCandTile);
     switch (c.k_pad) {
 #define EBC_KP(K)                                                                                              \
     case K:                                                                                                    \
         if (c.d <= K - 4)                                                                                      \
-            hipLaunchKernelGGL((k_gains_f32_list<K, true>), dim3(kListGrid), dim3(256), 0, s, c, part);        \
+            hipLaunchKernelGGL((k_gains_f32_list<K, true>), dim3(grid), dim3(256), 0, s, c, part);        \
         else                                                                                                   \
-            hipLaunchKernelGGL((k_gains_f32_list<K, false>), dim3(kListGrid), dim3(256), 0, s, c, part);       \
+            hipLaunchKernelGGL((k_gains_f32_list<K, false>), dim3(grid), dim3(256), 0, s, c, part);       \
         break;
         EBC_F32_KPS(EBC_KP)
 #undef EBC_KP
@@ -334,6 +327,25 @@ hipError_t launch_gains_f32_batched(int32_t k_pad, bool trim, const InstDesc* de
         else                                                                                                  \
             hipLaunchKernelGGL((kb_gains_f32<K, false>), dim3(unsigned(total_wgs)), dim3(256), 0, s, descs,   \
                                slot_inst, wg_pre, slots, t);                                                  \
+        break;
+        EBC_F32_KPS(EBC_KP)
+#undef EBC_KP
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_gains_f32_list_batched(int32_t k_pad, bool trim, const InstDesc* descs, const int32_t* slot_inst,
+                                         int32_t slots, int32_t t, int32_t part, hipStream_t s) {
+    switch (k_pad) {
+#define EBC_KP(K)                                                                                               \
+    case K:                                                                                                     \
+        if (trim)                                                                                               \
+            hipLaunchKernelGGL((kb_gains_f32_list<K, true>), dim3(kListGridBatch), dim3(256), 0, s, descs, slot_inst, \
+                               slots, t, part);                                                                 \
+        else                                                                                                    \
+            hipLaunchKernelGGL((kb_gains_f32_list<K, false>), dim3(kListGridBatch), dim3(256), 0, s, descs,          \
+                               slot_inst, slots, t, part);                                                      \
         break;
         EBC_F32_KPS(EBC_KP)
 #undef EBC_KP

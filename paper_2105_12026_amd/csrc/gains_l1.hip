@@ -62,7 +62,7 @@ __device__ __forceinline__ void gains_l1_body(const L1Args& a, int64_t bid) {
     const float* lc = reinterpret_cast<const float*>(lc4);
     const float* lp = reinterpret_cast<const float*>(lp4);
 
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     const int tc = tid & 15, tv = tid >> 4;
     const int split = int(bid % a.v_splits);
     const int64_t ctile = bid / a.v_splits;
@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(256) k_gains_l1_list(InstDesc c, int32_t part)
 }  // namespace
 
 hipError_t launch_gains_l1_list(const InstDesc& c, int32_t part, hipStream_t s) {
-    hipLaunchKernelGGL(k_gains_l1_list, dim3(kListGrid), dim3(256), 0, s, c, part);
+    hipLaunchKernelGGL(k_gains_l1_list, dim3(list_grid(c, part, kL1Cand)), dim3(256), 0, s, c, part);
     return hipGetLastError();
 }
 

@@ -233,20 +233,11 @@ __device__ __forceinline__ void load_candidates(const GainsArgs& ga, int64_t wba
             for (int u = 0; u < HU; ++u) a[cb][u] = make_uint4(0, 0, 0, 0);
             sa[cb] = 127;
         }
-        // the lane holds result rows 8*(r/4) + 4*half + r%4 of this block
+        // -hn of the 16 result rows this lane holds, from the lanes that
+        // loaded these rows
+        const float hc = crow >= 0 ? ga.hn[crow] : 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t p = wbase + cb * 32 + 8 * (r / 4) + 4 * half + (r % 4);
-            float v = 0.0f;
-            if (p < n_cand) {
-                int64_t row = cand ? int64_t(cand[p]) : p;
-                if (row >= 0 && row < n_pad) {
-                    if (cand && ga.inv) row = ga.inv[row];
-                    v = ga.hn[row];
-                }
-            }
-            cinit[cb][r] = -v;
-        }
+        for (int r = 0; r < 16; ++r) cinit[cb][r] = -__shfl(hc, acc_row(r, half), 64);
     }
 }
 
@@ -258,17 +249,9 @@ __device__ __forceinline__ void store_partials(const GainsArgs& ga, int64_t wbas
                                                const float (&acc_sum)[CB][16], int ge) {
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
-        double mine = 0.0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            double v = double(acc_sum[cb][r]);
-#pragma unroll
-            for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (col == r) mine = v;
-        }
-        if (col < 16) {
-            const int r = col;
-            const int64_t p = wbase + cb * 32 + 8 * (r / 4) + 4 * half + (r % 4);
+        const double mine = column_sums16(acc_sum[cb], col);
+        if ((col & 1) == 0) {
+            const int64_t p = wbase + cb * 32 + acc_row(col >> 1, half);
             if (p < ga.n_cand) {
                 const int64_t at = (ga.perm && !ga.cand) ? int64_t(ga.perm[p]) : p;
                 ga.part[int64_t(split) * ga.part_stride + at] = ldexp(2.0 * mine, ge);  // exact: a power of two
@@ -299,8 +282,8 @@ __device__ __forceinline__ void gains_lp_body(const GainsArgs& ga, int64_t bid) 
     const int wave = tid >> 6;
     const int col = lane & 31;
     const int half = lane >> 5;
-    const int split = int(bid % v_splits);
-    const int64_t ctile = bid / v_splits;
+    const int split = int(uint32_t(bid) % uint32_t(v_splits));
+    const int64_t ctile = uint32_t(bid) / uint32_t(v_splits);
     const int64_t wbase = ctile * G::CAND_TILE + int64_t(wave) * (32 * CB);
 
     // ---- candidate rows (A operand) and -hn of the result rows, in registers ----
@@ -510,8 +493,8 @@ __device__ __forceinline__ void gains_lp_pp_body(const GainsArgs& ga, int64_t bi
     const int grp = wave >> 2;                                   // waves w and w+4 share a SIMD
     const int col = lane & 31;
     const int half = lane >> 5;
-    const int split = int(bid % ga.v_splits);
-    const int64_t ctile = bid / ga.v_splits;
+    const int split = int(uint32_t(bid) % uint32_t(ga.v_splits));
+    const int64_t ctile = uint32_t(bid) / uint32_t(ga.v_splits);
     const int64_t wbase = ctile * (2 * G::CAND_TILE) + int64_t(wave) * (32 * CB);
 
     uint4 a[CB][HU];
@@ -698,13 +681,13 @@ __device__ __forceinline__ void gains_lp_sp_body(const GainsArgs& ga, int64_t bi
     __shared__ uint4 lds0[G::STAGE];
     __shared__ uint4 lds1[G::STAGE];
 
-    const int tid = threadIdx.x;
+    const int tid = fresh_tid();
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave: scalar copy branches
     const int col = lane & 31;
     const int half = lane >> 5;
-    const int split = int(bid % ga.v_splits);
-    const int64_t ctile = bid / ga.v_splits;
+    const int split = int(uint32_t(bid) % uint32_t(ga.v_splits));
+    const int64_t ctile = uint32_t(bid) / uint32_t(ga.v_splits);
     const int64_t wbase = ctile * G::CAND_TILE + int64_t(wave) * (32 * CB);
 
     uint4 a[CB][HU];
@@ -753,7 +736,7 @@ kb_gains_lp_sp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ s
                const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
     const int j = find_slot(wg_pre, slots, blockIdx.x);
     const InstDesc c = descs[slot_inst[j]];
-    if (c.t0 + t >= c.k) return;
+    if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
     gains_lp_sp_body<DT, KC, CB, VTS>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
 }
 
@@ -781,6 +764,14 @@ __global__ void __launch_bounds__(256) k_gains_lp_list(InstDesc c, int32_t part)
     }
 }
 
+template <int DT, int KC, int CB, int VTS>
+__global__ void __launch_bounds__(256, 2)
+kb_gains_lp_list(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst, int32_t slots, int32_t t,
+                 int32_t part) {
+    list_walk(descs, slot_inst, slots, t, part, LpGeom<DT, KC, CB, VTS>::CAND_TILE,
+              [](const GainsArgs& ga, int64_t pair) { gains_lp_sp_body<DT, KC, CB, VTS>(ga, pair); });
+}
+
 template <int DT, int KC, int CB>
 __global__ void __launch_bounds__(512) k_gains_lp_pp(GainsArgs ga) {
     gains_lp_pp_body<DT, KC, CB>(ga, blockIdx.x);
@@ -792,7 +783,7 @@ kb_gains_lp_pp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ s
                const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
     const int j = find_slot(wg_pre, slots, blockIdx.x);
     const InstDesc c = descs[slot_inst[j]];
-    if (c.t0 + t >= c.k) return;
+    if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
     gains_lp_pp_body<DT, KC, CB>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
 }
 
@@ -809,7 +800,7 @@ kb_gains_lp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot
             const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
     const int j = find_slot(wg_pre, slots, blockIdx.x);
     const InstDesc c = descs[slot_inst[j]];
-    if (c.t0 + t >= c.k) return;
+    if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
     gains_lp_body<DT, KC, CB, PIPE>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
 }
 
@@ -900,10 +891,11 @@ hipError_t launch_gains_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n
 }
 
 hipError_t launch_gains_lp_list(const InstDesc& c, int32_t part, hipStream_t s) {
+    const unsigned grid = list_grid(c, part, list_tile(c.dt, 0));
     const int kc = c.k_pad / (c.dt == EBC_DT_FP8_E4M3 ? 64 : 16);
 #define EBC_LPL(DTV, K)                                                                                             \
     case K:                                                                                                         \
-        hipLaunchKernelGGL((k_gains_lp_list<DTV, K, 2, wide_stage(DTV, K)>), dim3(kListGrid), dim3(256), 0, s, c,   \
+        hipLaunchKernelGGL((k_gains_lp_list<DTV, K, 2, wide_stage(DTV, K)>), dim3(grid), dim3(256), 0, s, c,   \
                            part);                                                                                   \
         break;
     switch (c.dt) {
@@ -981,6 +973,40 @@ hipError_t launch_gains_lp_batched(int32_t dt, int32_t kc, int32_t variant, cons
         default: return hipErrorInvalidValue;
     }
 #undef EBC_LPB
+    return hipGetLastError();
+}
+
+hipError_t launch_gains_lp_list_batched(int32_t dt, int32_t kc, const InstDesc* descs, const int32_t* slot_inst,
+                                        int32_t slots, int32_t t, int32_t part, hipStream_t s) {
+#define EBC_LPL(DTV, K)                                                                                             \
+    case K:                                                                                                         \
+        hipLaunchKernelGGL((kb_gains_lp_list<DTV, K, 2, wide_stage(DTV, K)>), dim3(kListGridBatch), dim3(256), 0, s,     \
+                           descs, slot_inst, slots, t, part);                                                       \
+        break;
+    switch (dt) {
+        case EBC_DT_BF16:
+            switch (kc) {
+                EBC_LPL(EBC_DT_BF16, 1) EBC_LPL(EBC_DT_BF16, 2) EBC_LPL(EBC_DT_BF16, 3) EBC_LPL(EBC_DT_BF16, 4)
+                EBC_LPL(EBC_DT_BF16, 5) EBC_LPL(EBC_DT_BF16, 6) EBC_LPL(EBC_DT_BF16, 7) EBC_LPL(EBC_DT_BF16, 8)
+                default: return hipErrorInvalidValue;
+            }
+            break;
+        case EBC_DT_F16:
+            switch (kc) {
+                EBC_LPL(EBC_DT_F16, 1) EBC_LPL(EBC_DT_F16, 2) EBC_LPL(EBC_DT_F16, 3) EBC_LPL(EBC_DT_F16, 4)
+                EBC_LPL(EBC_DT_F16, 5) EBC_LPL(EBC_DT_F16, 6) EBC_LPL(EBC_DT_F16, 7) EBC_LPL(EBC_DT_F16, 8)
+                default: return hipErrorInvalidValue;
+            }
+            break;
+        case EBC_DT_FP8_E4M3:
+            switch (kc) {
+                EBC_LPL(EBC_DT_FP8_E4M3, 1) EBC_LPL(EBC_DT_FP8_E4M3, 2)
+                default: return hipErrorInvalidValue;
+            }
+            break;
+        default: return hipErrorInvalidValue;
+    }
+#undef EBC_LPL
     return hipGetLastError();
 }
 

@@ -46,35 +46,57 @@ __host__ __device__ inline float* list_m(const InstDesc& c) {
     return reinterpret_cast<float*>(list_rows(c) + c.n_pad);
 }
 
-// Work split of a list of cnt candidates in tiles of ct: enough chunks that
-// tiles * splits fills the chip several times (kListItems), chunks of whole
-// 256-point units, and partial sums that fit the buffer. Lists are short
-// against n (a few tiles) in most steps, so the ground set is cut much finer
-// than for a launch over all candidates.
-constexpr int kListItems = 4096;   // (tile, chunk) pairs wanted
-constexpr int kListUnit = 256;     // points
-constexpr int kListGrid = 1024;    // workgroups of a list launch; each walks its share of the pairs
+// Work split of a list of cnt candidates in tiles of ct rows. A few tiles (most
+// steps): the ground set is cut finely enough for tiles * splits to fill the
+// chip's workgroup slots once. Many tiles: chunks of about kListChunk points,
+// long enough that loading a pair's candidates and adding up its sums do not
+// count, and many enough that the last round of workgroups does not either.
+// Whole 256-point units; as many splits as the partial sums have room for;
+// splits padded to whole rounds over the 8 XCDs (a padded chunk is empty).
+constexpr int kListUnit = 256;
+constexpr int kListSlots = 512;   // 2 workgroups of 4 waves on each of 256 CUs
+constexpr int kListChunk = 1024;
 struct ListGeom {
-    int64_t tiles, chunk, stride;
-    int32_t splits;
+    int64_t chunk, stride;
+    int32_t tiles, splits;
 };
 __host__ __device__ inline ListGeom list_geom(const InstDesc& c, int64_t cnt, int32_t ct) {
     ListGeom g;
-    g.tiles = (cnt + ct - 1) / ct;
-    g.stride = g.tiles * ct;
-    const int64_t units = c.n_pad / kListUnit;
-    int64_t s = g.tiles > 0 ? kListItems / g.tiles : 1;
-    const int64_t cap = g.stride > 0 ? int64_t(c.v_splits - 1) * c.n_pad / g.stride : 1;
-    s = s < units ? s : units;
+    g.tiles = int32_t((cnt + ct - 1) / ct);
+    g.stride = int64_t(g.tiles) * ct;
+    const int32_t units = int32_t(c.n_pad / kListUnit);
+    const int32_t tiles = g.tiles > 0 ? g.tiles : 1;
+    const int32_t cap = int32_t((c.v_splits - 1) * (c.n_pad / ct) / tiles);
+    int32_t s = kListSlots / tiles;
+    const int32_t fine = units / (kListChunk / kListUnit);
+    s = s > fine ? s : fine;
     s = s < cap ? s : cap;
+    s = s < units ? s : units;
     s = s < 1 ? 1 : s;
-    if (s >= 8) s &= ~int64_t(7);  // whole rounds over the XCDs
-    g.chunk = (units + s - 1) / s * kListUnit;
-    g.splits = int32_t(s);
+    const int32_t per = (units + s - 1) / s;
+    s = (units + per - 1) / per;
+    const int32_t up = (s + 7) & ~7;
+    g.splits = s >= 8 && up <= cap ? up : s;
+    g.chunk = int64_t(per) * kListUnit;
     return g;
 }
+// Workgroups of a list launch over one instance: one per pair (the scheduler
+// balances them, and those past the list's end return at once); a longer list
+// than that is walked.
+constexpr int kListGridMax = 16384;
+inline unsigned list_grid(const InstDesc& c, int32_t part, int32_t ct) {
+    const int64_t most = part ? c.n_pad : list_heads_max(c.dt);
+    int64_t items = 0;
+    // the pairs do not grow monotonically with the count; kListSlots + tiles
+    // bounds them for few tiles, the geometry at the full count for many
+    const ListGeom g = list_geom(c, most, ct);
+    items = int64_t(g.tiles) * (g.splits > 8 ? g.splits : 8) + kListSlots + g.tiles;
+    return unsigned(items < kListGridMax ? items : kListGridMax);
+}
+constexpr int kListGridBatch = 4096;  // batched: pairs of many instances, walked
 
-// Rows and their number: part 0 the heads, part 1 the list.
+// Rows and their number: part 0 the heads, part 1 the list. Until their sums
+// are added the entries are slots of the grouped order where there is one.
 __device__ inline int32_t* list_part(const InstDesc& c, int32_t part) { return part ? list_rows(c) : c.b.bcnt; }
 __device__ inline int64_t list_count(const InstDesc& c, int32_t part) {
     return part ? c.b.state->list_len : c.b.state->list_heads;
@@ -89,8 +111,52 @@ __device__ inline GainsArgs list_args(const InstDesc& c, int32_t part, int32_t c
     a.v_splits = g.splits;
     a.chunk = g.chunk;
     a.part_stride = g.stride;
-    *items = g.tiles * g.splits;
+    a.inv = nullptr;  // the entries are slots
+    *items = int64_t(g.tiles) * g.splits;
     return a;
+}
+
+// Does step `step` of the instance score a list?
+__host__ __device__ inline bool list_step(const InstDesc& c, int32_t step) { return c.lazy != 0 && step > 0; }
+
+// Batched list launches: the workgroups walk the (tile, chunk) pairs of every
+// instance of a bucket that is at a list step. The pairs of 64 instances at a
+// time are counted on the device (the counts are not known to the host; each
+// wave does it for itself) and numbered in instance order; workgroup b takes
+// pairs b, b + gridDim.x, ... f(gains arguments, pair) runs the kernel body.
+template <class F>
+__device__ __forceinline__ void list_walk(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst,
+                                          int32_t slots, int32_t t, int32_t part, int32_t ct, F f) {
+    const int lane = threadIdx.x & 63;
+    int32_t next = blockIdx.x, before = 0;
+    for (int32_t s0 = 0; s0 < slots; s0 += 64) {
+        int32_t upto = 0;  // pairs of instances s0 .. s0 + lane
+        if (s0 + lane < slots) {
+            const InstDesc& c = descs[slot_inst[s0 + lane]];
+            if (list_step(c, c.t0 + t) && c.t0 + t < c.k) {
+                const ListGeom g = list_geom(c, list_count(c, part), ct);
+                upto = g.tiles * g.splits;
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t add = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += add;
+        }
+        const int32_t total = __builtin_amdgcn_readlane(upto, 63);
+        while (next < before + total) {
+            // the same for the whole workgroup: kept scalar
+            const int32_t at = next - before;
+            const int32_t j = __popcll(__builtin_amdgcn_ballot_w64(upto <= at));
+            const int32_t pair = j > 0 ? at - __builtin_amdgcn_readlane(upto, j - 1) : at;
+            const InstDesc c = descs[slot_inst[s0 + j]];
+            int64_t items;
+            f(list_args(c, part, ct, &items), int64_t(pair));
+            __syncthreads();  // the body's LDS is free again
+            next += gridDim.x;
+        }
+        before += total;
+    }
 }
 
 // Candidate tile of the list kernels.

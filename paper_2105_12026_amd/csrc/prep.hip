@@ -42,15 +42,18 @@ int64_t gains_cand_tile(const ebc_dataset* ds) {
     return ds->variant == 1 ? 512 : 256;
 }
 
-// A list step launches four kernels more than one that scores everything, and
+// Lists need room in the partial sums (lazy.h) and the short-row kernels. In
+// a batch, whose launches are shared, every such instance keeps them. Alone,
+// a list step launches four kernels more than one that scores everything, and
 // its two short gains launches take 20 to 40 us; it pays once the launch over
 // all candidates takes longer than about that. Measured crossovers (us per
 // greedy step, all candidates / lists): float32 d = 16: 8192 points 63 / 64,
 // 12000 93 / 76; d = 100: 3000 82 / 109, 4096 97 / 86; BF16 d = 64: 16384
 // 89 / 90, 24000 131 / 95; L1 d = 20: 4096 68 / 67. The line is drawn on the
 // launch's time, n_pad^2 pairs of k_pad products plus the clamp and sum.
-bool greedy_lazy(const ebc_dataset* ds) {
-    if (ds->prof || wide_rows(ds->k_pad) || ds->v_splits < 4) return false;
+bool greedy_lists(const ebc_dataset* ds) { return !wide_rows(ds->k_pad) && ds->v_splits >= 4; }
+bool greedy_lists_solo(const ebc_dataset* ds) {
+    if (!greedy_lists(ds)) return false;
     const double pairs = double(ds->n_pad) * double(ds->n_pad);
     double us;  // measured rates: 77 T products/s (float32), 20 (L1), 1250 (16 bit), 2500 (8 bit)
     if (ds->metric == 1)
@@ -86,7 +89,7 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
     c.dt = int32_t(ds->dt);
     c.variant = ds->variant;
     c.metric = ds->metric;
-    c.lazy = greedy_lazy(ds) ? 1 : 0;
+    c.lazy = greedy_lists(ds) ? 1 : 0;
     c.chunk = gains_chunk(ds);
     c.sel = sel;
     c.f = f;
@@ -102,6 +105,15 @@ hipError_t launch_gains_batched(int32_t bucket, const InstDesc* descs, const int
         return launch_gains_f32_batched(k_pad, variant == 1, descs, slot_inst, wg_pre, slots, total_wgs, t, s);
     const int32_t kc = k_pad / (dt == EBC_DT_FP8_E4M3 ? 64 : 16);
     return launch_gains_lp_batched(dt, kc, variant, descs, slot_inst, wg_pre, slots, total_wgs, t, s);
+}
+
+hipError_t launch_gains_list_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst, int32_t slots,
+                                     int32_t t, int32_t part, hipStream_t s) {
+    const int32_t dt = bucket / 100000, k_pad = (bucket % 100000) / 10, variant = bucket % 10;
+    if (dt == EBC_DT_F32)
+        return launch_gains_f32_list_batched(k_pad, variant == 1, descs, slot_inst, slots, t, part, s);
+    const int32_t kc = k_pad / (dt == EBC_DT_FP8_E4M3 ? 64 : 16);
+    return launch_gains_lp_list_batched(dt, kc, descs, slot_inst, slots, t, part, s);
 }
 
 int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {

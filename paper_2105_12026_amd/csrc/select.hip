@@ -862,7 +862,7 @@ __device__ void fsum_body(const InstDesc& c, int32_t t) {
                 e = c.b.bmax[i];
                 row = c.b.barg[i];
             }
-        list_part(c, 0)[h] = row;
+        list_part(c, 0)[h] = c.b.inv ? c.b.inv[row] : row;
     }
     if (threadIdx.x == 0) {
         c.b.state->list_heads = heads;
@@ -882,7 +882,7 @@ __device__ void list_sum_body(const InstDesc& c, int32_t part, int64_t first, in
     const Buffers& b = c.b;
     const int64_t cnt = list_count(c, part);
     const ListGeom g = list_geom(c, cnt, list_tile(c.dt, c.metric));
-    const int32_t* __restrict__ rows = list_part(c, part);
+    int32_t* __restrict__ rows = list_part(c, part);
     const int p = threadIdx.x % kListSumPos, q = threadIdx.x / kListSumPos;
     constexpr int Q = kListSumThreads / kListSumPos;
     for (int64_t p0 = first * kListSumPos; p0 < cnt; p0 += step * kListSumPos) {
@@ -893,7 +893,8 @@ __device__ void list_sum_body(const InstDesc& c, int32_t part, int64_t first, in
         __syncthreads();
         if (q == 0 && p0 + p < cnt) {
             for (int i = 1; i < Q; ++i) s += red[i][p];
-            const int64_t row = rows[p0 + p];
+            int32_t row = rows[p0 + p];
+            if (b.perm) rows[p0 + p] = row = b.perm[row];
             b.gsum[row] = b.selected[row] ? -INFINITY : s;
             list_m(c)[row] = float(b.m64[row]);
         }
@@ -939,7 +940,7 @@ __device__ void list_build_body(const InstDesc& c, int64_t blk) {
     if (!take) return;
     int at = base + __popcll(hit & ((uint64_t(1) << lane) - 1));
     for (int w = 0; w < wave; ++w) at += wave_n[w];
-    list_rows(c)[at] = int32_t(row);
+    list_rows(c)[at] = int32_t(i);
 }
 
 // The window out of the list (one block): the same candidates, and the same
@@ -1081,51 +1082,47 @@ __global__ void __launch_bounds__(kSelThreads) k_list_window(InstDesc c) { list_
 
 // ---- batched kernels: blocks of row_pre[i] .. row_pre[i+1] belong to instance i;
 // tick t runs step t0 + t of each instance; instances whose k is reached skip ----
-#define EBC_ROW_KERNEL(NAME, BODY)                                                                     \
+#define EBC_ROW_KERNEL(NAME, COND, BODY)                                                               \
     __global__ void __launch_bounds__(kBlock)                                                          \
         NAME(const InstDesc* __restrict__ descs, const int64_t* __restrict__ row_pre, int32_t count,   \
              int32_t t) {                                                                              \
         const int i = find_slot(row_pre, count, blockIdx.x);                                           \
         const InstDesc c = descs[i];                                                                   \
-        if (c.t0 + t >= c.k) return;                                                                   \
-        BODY(c, int64_t(blockIdx.x) - row_pre[i]);                                                     \
+        const int32_t step = c.t0 + t;                                                                 \
+        const int64_t blk = int64_t(blockIdx.x) - row_pre[i];                                          \
+        if (step < c.k && (COND)) BODY;                                                                \
     }
-EBC_ROW_KERNEL(kb_gsum, gsum_body)
-EBC_ROW_KERNEL(kb_wcount, wcount_body)
+EBC_ROW_KERNEL(kb_gsum, !list_step(c, step), gsum_body(c, blk))
+EBC_ROW_KERNEL(kb_wcount, !list_step(c, step), wcount_body(c, blk))
+EBC_ROW_KERNEL(kb_list_build, list_step(c, step), list_build_body(c, blk))
 // mixed batches: each re-score / update body runs only for its own row length
-__device__ __forceinline__ void rescore_short(const InstDesc& c, int64_t blk) {
-    if (!wide_rows(c.k_pad)) rescore_body(c, blk);
-}
-__device__ __forceinline__ void update_short(const InstDesc& c, int64_t blk) {
-    if (!wide_rows(c.k_pad)) update_body(c, blk, 1);
-}
-__device__ __forceinline__ void rescore_long(const InstDesc& c, int64_t blk) {
-    if (wide_rows(c.k_pad)) rescore_long_body(c, blk, blockIdx.y);
-}
 __device__ __forceinline__ void update_long(const InstDesc& c, int64_t blk) {
-    if (!wide_rows(c.k_pad)) return;
     if (long_split(c))
         update_split_body(c, blk);
     else
         update_long_body(c, blk);
 }
-__device__ __forceinline__ void dist_slices(const InstDesc& c, int64_t blk) {
-    if (long_split(c)) dist_slice_body(c, blk, blockIdx.y, update_slices(c), c.b.state->cstar);
-}
-__device__ __forceinline__ void dist_window(const InstDesc& c, int64_t blk) {
-    if (long_split(c)) dist_window_body(c, blk, blockIdx.y);
-}
-EBC_ROW_KERNEL(kb_rescore, rescore_short)
-EBC_ROW_KERNEL(kb_update, update_short)
-EBC_ROW_KERNEL(kb_rescore_long, rescore_long)
-EBC_ROW_KERNEL(kb_update_long, update_long)
-EBC_ROW_KERNEL(kb_dist_slices, dist_slices)
-EBC_ROW_KERNEL(kb_dist_window, dist_window)
+EBC_ROW_KERNEL(kb_rescore, !wide_rows(c.k_pad), rescore_body(c, blk))
+EBC_ROW_KERNEL(kb_update, !wide_rows(c.k_pad), update_body(c, blk, step))
+EBC_ROW_KERNEL(kb_rescore_long, wide_rows(c.k_pad), rescore_long_body(c, blk, blockIdx.y))
+EBC_ROW_KERNEL(kb_update_long, wide_rows(c.k_pad), update_long(c, blk))
+EBC_ROW_KERNEL(kb_dist_slices, long_split(c), dist_slice_body(c, blk, blockIdx.y, update_slices(c), c.b.state->cstar))
+EBC_ROW_KERNEL(kb_dist_window, long_split(c), dist_window_body(c, blk, blockIdx.y))
 #undef EBC_ROW_KERNEL
 
 __global__ void __launch_bounds__(kSelThreads) kb_wselect(const InstDesc* __restrict__ descs, int32_t t) {
     const InstDesc c = descs[blockIdx.x];
-    if (c.t0 + t < c.k) wselect_body(c);
+    if (c.t0 + t < c.k && !list_step(c, c.t0 + t)) wselect_body(c);
+}
+// lists: instance on blockIdx.y / blockIdx.x
+__global__ void __launch_bounds__(kListSumThreads) kb_list_sum(const InstDesc* __restrict__ descs, int32_t t,
+                                                               int32_t part) {
+    const InstDesc c = descs[blockIdx.y];
+    if (c.t0 + t < c.k && list_step(c, c.t0 + t)) list_sum_body(c, part, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(kSelThreads) kb_list_window(const InstDesc* __restrict__ descs, int32_t t) {
+    const InstDesc c = descs[blockIdx.x];
+    if (c.t0 + t < c.k && list_step(c, c.t0 + t)) list_window_body(c);
 }
 __global__ void __launch_bounds__(kBlock) kb_pick(const InstDesc* __restrict__ descs, int32_t t) {
     const InstDesc c = descs[blockIdx.x];
@@ -1140,9 +1137,11 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
                               double* gain_out, hipStream_t s, hipEvent_t ev_gains_done) {
     InstDesc c;
     fill_desc(ds, t + 1, sel_out, f_out, gain_out, &c);
+    // a timed step is a whole launch
+    if (ds->prof || !greedy_lists_solo(ds)) c.lazy = 0;
     const int nb = c.nb;
     hipError_t e = hipSuccess;
-    if (c.lazy && t > 0) {
+    if (list_step(c, t)) {
         if ((e = launch_list_step(c, s)) != hipSuccess) return e;
     } else {
         if ((e = launch_gains(ds, nullptr, ds->n_pad, s)) != hipSuccess) return e;
@@ -1189,12 +1188,32 @@ hipError_t launch_list_step(const InstDesc& c, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_step_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count, int64_t total_rows,
-                               int32_t t, bool long_rows, hipStream_t s) {
+hipError_t launch_tick(const std::vector<GainsBucket>& buckets, const InstDesc* descs, const int64_t* row_pre,
+                       const int32_t* slot_inst, const int64_t* wg_pre, int32_t count, int64_t total_rows, int32_t t,
+                       bool full, bool lists, bool long_rows, hipStream_t s) {
     const dim3 rows = dim3(unsigned(total_rows)), one = dim3(unsigned(count));
-    hipLaunchKernelGGL(kb_gsum, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
-    hipLaunchKernelGGL(kb_wcount, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
-    hipLaunchKernelGGL(kb_wselect, one, dim3(kSelThreads), 0, s, descs, t);
+    hipError_t e = hipSuccess;
+    if (full) {
+        for (const GainsBucket& b : buckets)
+            if ((e = launch_gains_batched(b.key, descs, slot_inst + b.slot_begin, wg_pre + b.pre_off, b.slots,
+                                          b.total_wgs, t, s)) != hipSuccess)
+                return e;
+        hipLaunchKernelGGL(kb_gsum, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
+        hipLaunchKernelGGL(kb_wcount, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
+        hipLaunchKernelGGL(kb_wselect, one, dim3(kSelThreads), 0, s, descs, t);
+    }
+    if (lists) {
+        for (int32_t part = 0; part < 2; ++part) {
+            for (const GainsBucket& b : buckets)
+                if (b.lists && (e = launch_gains_list_batched(b.key, descs, slot_inst + b.slot_begin, b.slots, t, part,
+                                                              s)) != hipSuccess)
+                    return e;
+            hipLaunchKernelGGL(kb_list_sum, dim3(part ? 32 : kListHeads / kListSumPos, unsigned(count)),
+                               dim3(kListSumThreads), 0, s, descs, t, part);
+            if (part == 0) hipLaunchKernelGGL(kb_list_build, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
+        }
+        hipLaunchKernelGGL(kb_list_window, one, dim3(kSelThreads), 0, s, descs, t);
+    }
     hipLaunchKernelGGL(kb_rescore, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
     if (long_rows) {
         hipLaunchKernelGGL(kb_dist_window, dim3(unsigned(total_rows), 16), dim3(kBlock), 0, s, descs, row_pre, count,

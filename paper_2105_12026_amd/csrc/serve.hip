@@ -5,8 +5,8 @@
 // step granularity): requests that arrive while others run join at the next
 // tick as slots and arena space free up, and each finished request is copied
 // out and its space released at the tick it completes. One tick issues one
-// gains launch per kernel bucket and seven step launches for all active
-// requests; each request computes exactly what a solo ebc_greedy computes.
+// gains launch per kernel bucket (two for lists, see lazy.h) and the step
+// launches for all active requests; each request computes exactly what a solo ebc_greedy computes.
 #include <string.h>
 
 #include <algorithm>
@@ -129,11 +129,7 @@ struct ebc_server {
     PinnedTables staging;
     std::vector<int64_t> h_row_pre, h_wg_pre;
     std::vector<int32_t> h_slot;
-    struct Bucket {
-        int32_t key, slot_begin, slots, pre_off;
-        int64_t total_wgs;
-    };
-    std::vector<Bucket> buckets;
+    std::vector<GainsBucket> buckets;
     int64_t total_rows = 0;
     bool dirty = true;
     std::deque<Request*> queue;
@@ -204,7 +200,7 @@ void rebuild_tables(ebc_server* sv) {
     sv->h_slot.clear();
     sv->h_wg_pre.clear();
     for (int32_t key : keys) {
-        ebc_server::Bucket b{};
+        GainsBucket b{};
         b.key = key;
         b.slot_begin = int32_t(sv->h_slot.size());
         b.pre_off = int32_t(sv->h_wg_pre.size());
@@ -213,6 +209,7 @@ void rebuild_tables(ebc_server* sv) {
         for (int32_t i = 0; i < count; ++i) {
             const ebc_dataset* ds = sv->active[i]->ds;
             if (gains_bucket(ds) != key) continue;
+            b.lists |= greedy_lists(ds);
             const int64_t tile = gains_cand_tile(ds);
             acc += (ds->n_pad + tile - 1) / tile * ds->v_splits;
             sv->h_slot.push_back(i);
@@ -361,22 +358,20 @@ ebc_status ebc_server_step(ebc_server* sv, int32_t* completed) {
     for (int32_t i = 0; i < count; ++i) {
         Request* r = sv->active[i];
         fill_desc(r->ds, r->k, r->sel_d, r->f_d, r->gain_d, &hd[i]);
-        hd[i].lazy = 0;
         hd[i].t0 = r->t;
     }
     memcpy(h + sv->tl.row_pre, sv->h_row_pre.data(), sv->h_row_pre.size() * sizeof(int64_t));
     memcpy(h + sv->tl.slot_inst, sv->h_slot.data(), sv->h_slot.size() * sizeof(int32_t));
     memcpy(h + sv->tl.wg_pre, sv->h_wg_pre.data(), sv->h_wg_pre.size() * sizeof(int64_t));
     e = sv->staging.submit(sv->base, sv->tl.total, sv->stream);
-    for (const auto& b : sv->buckets) {
-        if (e != hipSuccess) break;
-        e = launch_gains_batched(b.key, sv->d_desc, sv->d_slot + b.slot_begin, sv->d_wg_pre + b.pre_off, b.slots,
-                                 b.total_wgs, 0, sv->stream);
+    bool long_rows = false, full = false, lists = false;
+    for (const Request* r : sv->active) {
+        long_rows |= wide_rows(r->ds->k_pad);
+        (r->t > 0 && greedy_lists(r->ds) ? lists : full) = true;
     }
-    bool long_rows = false;
-    for (const Request* r : sv->active) long_rows |= wide_rows(r->ds->k_pad);
     if (e == hipSuccess)
-        e = launch_step_batched(sv->d_desc, sv->d_row_pre, count, sv->total_rows, 0, long_rows, sv->stream);
+        e = launch_tick(sv->buckets, sv->d_desc, sv->d_row_pre, sv->d_slot, sv->d_wg_pre, count, sv->total_rows, 0,
+                        full, lists, long_rows, sv->stream);
     if (e != hipSuccess) return EBC_E_DEVICE;
     ++sv->ticks;
     // finished requests: copy out at the end of this tick

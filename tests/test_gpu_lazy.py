@@ -90,3 +90,43 @@ def test_lists_after_other_calls(dtype, dist):
     g1 = ds.marginal_gains().cpu().numpy()
     ds.sync()
     assert all(np.array_equal(p, q) for p, q in zip(a, b)) and np.array_equal(g0, g1)
+
+
+# instances that keep lists and instances that do not, in every reduced type and float32, uneven k
+BATCH = [("curves", 30000, 64, 9, "bf16"), ("mixture", 700, 16, 7, "bf16"), ("outliers", 26001, 33, 12, "fp8"),
+         ("mixture", 20480, 100, 3, "f16"), ("sorted", 9000, 100, 10, "f32"), ("normal", 1500, 8, 5, "f32"),
+         ("curves", 300, 500, 4, "bf16"), ("few", 24000, 128, 9, "bf16")]
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_with_lists_equals_solo(graph):
+    dss = [ebc.Dataset(torch.from_numpy(points(*c[:3], i)).cuda(), dtype=c[4]) for i, c in enumerate(BATCH)]
+    ks = [c[3] for c in BATCH]
+    solo = [[t.cpu().numpy() for t in ds.greedy(k)] for ds, k in zip(dss, ks)]
+    batch = ebc.Batch(dss)
+    batch.set_graph(graph)
+    for _ in range(2):
+        got = batch.greedy(ks)
+        for ds in dss:
+            ds.sync()
+        for a, b in zip(solo, got):
+            assert all(np.array_equal(p, q.cpu().numpy()) for p, q in zip(a, b))
+
+
+def test_server_with_lists_equals_solo():
+    sv = ebc.Server(1 << 30, max_slots=3)
+    want, ids = [], []
+    for i, c in enumerate(BATCH):
+        x = points(*c[:3], i)
+        ds = ebc.Dataset(torch.from_numpy(x).cuda(), dtype=c[4])
+        want.append([t.cpu().numpy() for t in ds.greedy(c[3])])
+        ids.append(sv.submit(x, c[3], dtype=c[4]))
+    for _ in range(100):
+        sv.step()
+        if sv.stats()["completed"] == len(ids):
+            break
+    for rid, w in zip(ids, want):
+        r = sv.poll(rid)
+        assert r["state"] == "done"
+        assert np.array_equal(r["sel"], w[0]) and np.array_equal(r["f"], w[1]) and np.array_equal(r["gain"], w[2])
+    sv.close()

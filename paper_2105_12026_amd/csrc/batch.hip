@@ -28,6 +28,7 @@ struct ebc_batch {
     int64_t total_rows;
     bool long_rows;  // some instance has rows longer than kNarrowMaxK
     std::vector<GainsBucket> buckets;
+    std::vector<char> lists;  // instances that score lists after their first step
     std::vector<int64_t> h_row_pre, h_wg_pre;
     std::vector<int32_t> h_slot_inst;
     PinnedTables staging;
@@ -43,7 +44,7 @@ namespace {
 hipError_t enqueue_ticks(ebc_batch* bt, int32_t ticks, hipStream_t s) {
     hipError_t e = launch_reset_batched(bt->d_desc, bt->d_row_pre, bt->count, bt->total_rows, s);
     bool all = false, some = false;  // instances that score every candidate at every step / lists
-    for (const ebc_dataset* ds : bt->ds) (greedy_lists(ds) ? some : all) = true;
+    for (const char l : bt->lists) (l ? some : all) = true;
     for (int32_t t = 0; t < ticks && e == hipSuccess; ++t)
         e = launch_tick(bt->buckets, bt->d_desc, bt->d_row_pre, bt->d_slot_inst, bt->d_wg_pre, bt->count,
                         bt->total_rows, t, t == 0 || all, t > 0 && some, bt->long_rows, s);
@@ -105,16 +106,18 @@ ebc_status ebc_batch_create(ebc_dataset* const* ds, int32_t count, void* workspa
     }
     bt->h_slot_inst.clear();
     bt->h_wg_pre.clear();
+    bt->lists.assign(count, 0);
     for (int32_t key : keys) {
         GainsBucket b{};
         b.key = key;
         b.slot_begin = int32_t(bt->h_slot_inst.size());
         b.pre_off = int32_t(bt->h_wg_pre.size());
         int64_t acc = 0;
+        double worth = 0.0;
         bt->h_wg_pre.push_back(0);
         for (int32_t i = 0; i < count; ++i) {
             if (gains_bucket(ds[i]) != key) continue;
-            b.lists |= greedy_lists(ds[i]);
+            worth += greedy_lists_worth(ds[i]);
             const int64_t tile = gains_cand_tile(ds[i]);
             acc += (ds[i]->n_pad + tile - 1) / tile * ds[i]->v_splits;
             bt->h_slot_inst.push_back(i);
@@ -122,6 +125,11 @@ ebc_status ebc_batch_create(ebc_dataset* const* ds, int32_t count, void* workspa
         }
         b.slots = int32_t(bt->h_slot_inst.size()) - b.slot_begin;
         b.total_wgs = acc;
+        b.lists = worth > 1.0;
+        for (int32_t j = 0; j < b.slots; ++j) {
+            const int32_t i = bt->h_slot_inst[b.slot_begin + j];
+            bt->lists[i] = b.lists && greedy_lists_worth(ds[i]) > 0.0;
+        }
         bt->buckets.push_back(b);
     }
     if (bt->staging.init(L.total) != hipSuccess) {
@@ -164,6 +172,7 @@ ebc_status ebc_greedy_batched(ebc_batch* bt, const int32_t* k, int32_t* const* s
     InstDesc* hd = reinterpret_cast<InstDesc*>(h + bt->tl.desc);
     for (int32_t i = 0; i < bt->count; ++i) {
         fill_desc(bt->ds[i], k[i], sel_out[i], f_out[i], gain_out ? gain_out[i] : nullptr, &hd[i]);
+        hd[i].lazy = bt->lists[i];
         bt->ds[i]->stats.steps = k[i];
     }
     memcpy(h + bt->tl.row_pre, bt->h_row_pre.data(), bt->h_row_pre.size() * sizeof(int64_t));

@@ -36,7 +36,7 @@ struct DevState {
     int window_max;      // largest window seen in this greedy run
     int window_overflow; // steps whose window list overflowed kWindowCap
     int cstar;           // index picked by the last step
-    int pad0;
+    int crank;           // window position of that pick, -1 if it was not in the window
     double gstar;        // float64 gain of the last pick (unnormalised sum)
     double l0;           // L({e0}) = |V|^-1 sum ||v||^2
     double tau;          // relative window half-width for the gains dtype
@@ -297,8 +297,9 @@ struct PinnedTables {
 // Host helpers shared by the solo and batched paths.
 int64_t gains_chunk(const ebc_dataset* ds);
 int64_t gains_cand_tile(const ebc_dataset* ds);
-bool greedy_lists(const ebc_dataset* ds);       // greedy steps of this dataset can score lists (lazy.h) ...
-bool greedy_lists_solo(const ebc_dataset* ds);  // ... and are faster with them when it runs alone
+// How far scoring lists (lazy.h) pays in greedy steps of this dataset: above 1
+// it does when the dataset runs alone; 0 if it cannot.
+double greedy_lists_worth(const ebc_dataset* ds);
 int32_t gains_bucket(const ebc_dataset* ds);  // datasets with equal keys share a batched gains launch
 void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double* gain, InstDesc* out);
 
@@ -409,7 +410,7 @@ __host__ __device__ inline double window_tau(ebc_dtype dt) {
 __host__ __device__ inline double window_tau_abs(ebc_dtype dt) { return dt == EBC_DT_F32 ? 1e-4 : 1e-2; }
 hipError_t launch_gains_out(const ebc_dataset* ds, int64_t n_cand, double* out, hipStream_t s);
 hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out, double* f_out,
-                              double* gain_out, hipStream_t s, hipEvent_t ev_gains_done);
+                              double* gain_out, bool last, hipStream_t s, hipEvent_t ev_gains_done);
 // device scratch of one multi-set evaluation of l sets over n ground points
 size_t eval_sets_scratch_bytes(int64_t n, int64_t l);
 // `scratch`: at least eval_sets_scratch_bytes(ds->n, l) bytes, 256-byte aligned

@@ -42,27 +42,26 @@ int64_t gains_cand_tile(const ebc_dataset* ds) {
     return ds->variant == 1 ? 512 : 256;
 }
 
-// Lists need room in the partial sums (lazy.h) and the short-row kernels. In
-// a batch, whose launches are shared, every such instance keeps them. Alone,
-// a list step launches four kernels more than one that scores everything, and
-// its two short gains launches take 20 to 40 us; it pays once the launch over
-// all candidates takes longer than about that. Measured crossovers (us per
-// greedy step, all candidates / lists): float32 d = 16: 8192 points 63 / 64,
-// 12000 93 / 76; d = 100: 3000 82 / 109, 4096 97 / 86; BF16 d = 64: 16384
-// 89 / 90, 24000 131 / 95; L1 d = 20: 4096 68 / 67. The line is drawn on the
-// launch's time, n_pad^2 pairs of k_pad products plus the clamp and sum.
-bool greedy_lists(const ebc_dataset* ds) { return !wide_rows(ds->k_pad) && ds->v_splits >= 4; }
-bool greedy_lists_solo(const ebc_dataset* ds) {
-    if (!greedy_lists(ds)) return false;
+// Lists need room in the partial sums (lazy.h) and the short-row kernels.
+//
+// A list step launches five kernels more than one that scores everything; it
+// pays once the launch over all candidates takes longer than that. Measured
+// us per greedy step, all candidates / lists: float32 d = 16: 8192 points
+// 55 / 57, 12000 83 / 60; d = 100: 4096 58 / 70, 6000 97 / 75; BF16 d = 64:
+// 12000 62 / 64, 16384 75 / 69; FP16 d = 100: 8192 53 / 62, 12000 75 / 65;
+// FP8 d = 33: 16384 82 / 83, 24000 96 / 84; L1 d = 20: 4096 45 / 59, 6000
+// 76 / 60. The line is drawn on the time of the launch over all candidates:
+// n_pad^2 pairs at the products a pair costs plus a constant for its clamp
+// and sum and for the launch's unfilled rounds. Returned is that time in
+// units of the line: above 1 lists are faster for a dataset alone, and for a
+// bucket of a batch (which shares its launches) where the sum is above 1.
+double greedy_lists_worth(const ebc_dataset* ds) {
+    if (wide_rows(ds->k_pad) || ds->v_splits < 4) return 0.0;
     const double pairs = double(ds->n_pad) * double(ds->n_pad);
-    double us;  // measured rates: 77 T products/s (float32), 20 (L1), 1250 (16 bit), 2500 (8 bit)
-    if (ds->metric == 1)
-        us = pairs * ds->d / 20e6;
-    else if (ds->dt == EBC_DT_F32)
-        us = pairs * (ds->k_pad + 2) / 77e6;
-    else
-        us = pairs * (ds->k_pad / (ds->dt == EBC_DT_FP8_E4M3 ? 2.0 : 1.0) + 27) / 1250e6;
-    return us > 20.0;
+    if (ds->metric == 1) return pairs * (ds->d + 4) / 6.0e8;
+    if (ds->dt == EBC_DT_F32) return pairs * (ds->k_pad + 28) / 3.1e9;
+    const double products = ds->k_pad / (ds->dt == EBC_DT_FP8_E4M3 ? 2.0 : 1.0);
+    return pairs * (products + 27) / 1.5e10;
 }
 
 int32_t gains_bucket(const ebc_dataset* ds) {
@@ -89,7 +88,7 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
     c.dt = int32_t(ds->dt);
     c.variant = ds->variant;
     c.metric = ds->metric;
-    c.lazy = greedy_lists(ds) ? 1 : 0;
+    c.lazy = greedy_lists_worth(ds) > 1.0 ? 1 : 0;
     c.chunk = gains_chunk(ds);
     c.sel = sel;
     c.f = f;
@@ -136,8 +135,13 @@ int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {
     // slower, reduced precision measured no faster with 16).
     int64_t tiles = n_pad / kGainsCandTile;
     if (tiles >= 64) return (dt == EBC_DT_F32 && tiles < 1024) ? 16 : 8;
-    if (tiles >= 16) return 4;
-    return 1;
+    // Small ground sets: about two workgroups for each of the 256 CUs, chunks
+    // of at least one LDS tile (1000 x 16: 8 workgroups 23 us, 128 4.5 us).
+    int64_t v = 512 / tiles;
+    const int64_t most = n_pad / (dt == EBC_DT_F32 ? kGainsVTile : 256);
+    v = v < 16 ? v : 16;
+    v = v < most ? v : most;
+    return int32_t(v);
 }
 
 Layout layout(int64_t n, int32_t d, ebc_dtype dt) {
@@ -794,7 +798,7 @@ __global__ void k_state_init(DevState* st) {
         st->window_max = 0;
         st->window_overflow = 0;
         st->cstar = -1;
-        st->pad0 = 0;
+        st->crank = -1;
         st->gstar = 0.0;
         st->l0 = 0.0;
         st->tau = 0.0;

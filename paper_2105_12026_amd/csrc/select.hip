@@ -28,6 +28,34 @@ __device__ inline bool better(double ga, int ia, double gb, int ib) {
     return ga > gb || (ga == gb && ia < ib);
 }
 
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+    return v;
+}
+// Best (gain, index) of the wave, with an extra value that goes along.
+__device__ __forceinline__ void wave_best(double& g, int& i, int& extra) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double og = __shfl_xor(g, off, 64);
+        const int oi = __shfl_xor(i, off, 64), oe = __shfl_xor(extra, off, 64);
+        if (better(og, oi, g, i)) {
+            g = og;
+            i = oi;
+            extra = oe;
+        }
+    }
+}
+
+// Sum of 256 values of a block of 256 threads through red: pairs 128 apart,
+// then 64, 32, ... 1 (one fixed tree). The first wave returns it in lane 0.
+__device__ __forceinline__ double tree_sum256(const double* __restrict__ red, int lane) {
+    double s = (red[lane] + red[lane + 128]) + (red[lane + 64] + red[lane + 192]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    return s;
+}
+
 // Threshold of the re-score window from the global best float32 gain.
 __device__ double window_threshold(double gmax, const DevState* st) {
     return gmax - (st->tau * fabs(gmax) + st->tau_abs * st->nmax);
@@ -50,27 +78,30 @@ __device__ double block_gmax(const double* bmax, int nb, double* red) {
 
 // ---- gsum: per-chunk sums -> gsum, selected masked, block maxima ----
 __device__ void gsum_body(const InstDesc& c, int64_t blk) {
-    __shared__ double sg[kBlock];
-    __shared__ int si[kBlock];
+    __shared__ double sg[kBlock / 64];
+    __shared__ int si[kBlock / 64];
     const Buffers& b = c.b;
     const int64_t i = blk * kBlock + threadIdx.x;
     double g = 0.0;
+#pragma unroll 8
     for (int s = 0; s < c.v_splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
     if (b.selected[i]) g = -INFINITY;
     b.gsum[i] = g;
-    sg[threadIdx.x] = g;
-    si[threadIdx.x] = int(i);
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w && better(sg[threadIdx.x + w], si[threadIdx.x + w], sg[threadIdx.x], si[threadIdx.x])) {
-            sg[threadIdx.x] = sg[threadIdx.x + w];
-            si[threadIdx.x] = si[threadIdx.x + w];
-        }
-        __syncthreads();
+    int row = int(i), none = 0;
+    wave_best(g, row, none);
+    if ((threadIdx.x & 63) == 0) {
+        sg[threadIdx.x >> 6] = g;
+        si[threadIdx.x >> 6] = row;
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        b.bmax[blk] = sg[0];
-        b.barg[blk] = si[0];
+        for (int w = 1; w < kBlock / 64; ++w)
+            if (better(sg[w], si[w], g, row)) {
+                g = sg[w];
+                row = si[w];
+            }
+        b.bmax[blk] = g;
+        b.barg[blk] = row;
     }
 }
 
@@ -226,46 +257,74 @@ __device__ __forceinline__ void row_terms(const float* __restrict__ xv, bool vec
     for (; k < kn; ++k) dim_terms<METRIC, NJ>(double(xv[k]), cx + k, acc);
 }
 
+// Windows of at most stored_window(c) candidates keep their distances for the
+// update of the same step, in the partial sums (not needed between the window
+// and the next gains; lists keep their last chunk): 8 bytes a point read
+// there instead of a whole row.
+__host__ __device__ inline int stored_window(const InstDesc& c) {
+    return c.v_splits - 1 < kRescoreGroup ? c.v_splits - 1 : kRescoreGroup;
+}
+__device__ __forceinline__ bool window_has_distances(const InstDesc& c, int rank) {
+    return rank >= 0 && c.b.state->window_count <= stored_window(c);
+}
+
 // METRIC 0: squared Euclidean (the paper's d); 1: L1, sum of |x_vk - x_ck|.
-template <int METRIC>
-__device__ void rescore_impl(const InstDesc& c, int64_t blk, double* __restrict__ cx, double (*red)[kBlock]) {
+// One group of at most NJ window candidates from position g0.
+template <int METRIC, int NJ>
+__device__ __forceinline__ void rescore_group(const InstDesc& c, int64_t blk, int g0, int W, double* __restrict__ cx,
+                                              double (*red)[kBlock]) {
     const Buffers& b = c.b;
     const float* __restrict__ x = c.x;
     const int d = c.d;
-    const int W = b.state->window_count;
     const int64_t v = blk * kBlock + threadIdx.x;
     const bool live = v < c.n;
     const double mv = live ? b.m64[v] : 0.0;
     const float* __restrict__ xv = x + (live ? v : 0) * d;
     const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
-    for (int g0 = 0; g0 < W; g0 += kRescoreGroup) {
-        const int gn = (W - g0) < kRescoreGroup ? (W - g0) : kRescoreGroup;
-        double acc[kRescoreGroup];
+    const int gn = (W - g0) < NJ ? (W - g0) : NJ;
+    double acc[NJ];
 #pragma unroll
-        for (int j = 0; j < kRescoreGroup; ++j) acc[j] = 0.0;
-        for (int k0 = 0; k0 < d; k0 += kRescoreChunk) {
-            const int kn = (d - k0) < kRescoreChunk ? (d - k0) : kRescoreChunk;
-            __syncthreads();
-            for (int e = threadIdx.x; e < kRescoreGroup * kn; e += kBlock) {
-                const int j = e / kn, k = e % kn;
-                // rows past the group's end repeat its first candidate (their sums are not used)
-                cx[j * kRescoreChunk + k] = double(x[int64_t(b.wfinal[g0 + (j < gn ? j : 0)].idx) * d + k0 + k]);
-            }
-            __syncthreads();
-            if (live) row_terms<METRIC, kRescoreGroup>(xv + k0, vec, kn, cx, acc);
-        }
-#pragma unroll
-        for (int j = 0; j < kRescoreGroup; ++j) red[j][threadIdx.x] = live ? fmax(0.0, mv - acc[j]) : 0.0;
+    for (int j = 0; j < NJ; ++j) acc[j] = 0.0;
+    for (int k0 = 0; k0 < d; k0 += kRescoreChunk) {
+        const int kn = (d - k0) < kRescoreChunk ? (d - k0) : kRescoreChunk;
         __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) {
-#pragma unroll
-                for (int j = 0; j < kRescoreGroup; ++j) red[j][threadIdx.x] += red[j][threadIdx.x + w];
-            }
-            __syncthreads();
+        for (int e = threadIdx.x; e < NJ * kn; e += kBlock) {
+            const int j = e / kn, k = e % kn;
+            // rows past the group's end repeat its first candidate (their sums are not used)
+            cx[j * kRescoreChunk + k] = double(x[int64_t(b.wfinal[g0 + (j < gn ? j : 0)].idx) * d + k0 + k]);
         }
-        if (threadIdx.x < gn) b.rpart[blk * kWindowMax + g0 + threadIdx.x] = red[threadIdx.x][0];
+        __syncthreads();
+        if (live) row_terms<METRIC, NJ>(xv + k0, vec, kn, cx, acc);
     }
+    if (W <= stored_window(c) && live) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (j < gn) b.part[int64_t(g0 + j) * c.n_pad + v] = acc[j];
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) red[j][threadIdx.x] = live ? fmax(0.0, mv - acc[j]) : 0.0;
+    __syncthreads();
+    for (int j = wave; j < gn; j += kBlock / 64) {
+        const double sum = tree_sum256(red[j], lane);
+        if (lane == 0) b.rpart[blk * kWindowMax + g0 + j] = sum;
+    }
+}
+
+// Groups of 8; a window of 1 or 2 takes the kernel of its size (the LDS reads
+// of the staged candidates, one per candidate and dimension, are what bounds
+// it: 100000 x 100, W = 1: 17.4 -> 9 us).
+template <int METRIC>
+__device__ void rescore_impl(const InstDesc& c, int64_t blk, double* __restrict__ cx, double (*red)[kBlock]) {
+    const int W = c.b.state->window_count;
+    if (W == 1)
+        rescore_group<METRIC, 1>(c, blk, 0, W, cx, red);
+    else if (W == 2)
+        rescore_group<METRIC, 2>(c, blk, 0, W, cx, red);
+    else if (W <= 4)
+        rescore_group<METRIC, 4>(c, blk, 0, W, cx, red);
+    else
+        for (int g0 = 0; g0 < W; g0 += kRescoreGroup) rescore_group<METRIC, kRescoreGroup>(c, blk, g0, W, cx, red);
 }
 
 __device__ void rescore_body(const InstDesc& c, int64_t blk) {
@@ -282,96 +341,112 @@ __device__ __forceinline__ int rescore_rows(const InstDesc& c, int W);
 // ---- pick (one block per instance) ----
 // float64 gain of each window candidate = sum of the per-block sums: up to
 // kPickColumnRows of them, thread j adds candidate j's in block order;
-// otherwise, candidate by candidate, thread i takes blocks i, i+256, ...,
-// then a fixed tree. Best gain wins, ties to the lowest index. Records the
-// pick. A step with no valid candidate (only possible with non-finite input)
-// records -1 and flags it.
+// otherwise wave w takes candidates w, w + NT/64, ...: 256 running sums (i
+// takes blocks i, i+256, ...), then a fixed tree. Best gain wins, ties to the
+// lowest index. A step with no valid candidate (only possible with non-finite
+// input) picks -1. Every thread of the block gets the pick, its gain and its
+// position in the window (-1: chosen outside of it).
 constexpr int kPickColumnRows = 64;
+constexpr int kPickThreads = 1024;
 
-__device__ void pick_body(const InstDesc& c, int32_t t) {
-    __shared__ double red[kBlock];
+template <int NT>
+__device__ int pick_choose(const InstDesc& c, double* gain, int* rank) {
     __shared__ double sg[kWindowMax];
-    __shared__ int si[kWindowMax];
+    __shared__ int out_cs, out_rank;
+    __shared__ double out_gain;
     const Buffers& b = c.b;
+    const int tid = threadIdx.x;
     const int W = b.state->window_count;
     const int nbv = rescore_rows(c, W);
     if (nbv <= kPickColumnRows) {
-        for (int j = threadIdx.x; j < kWindowMax; j += kBlock) {
+        for (int j = tid; j < W; j += NT) {
             double s = 0.0;
-            if (j < W)
-                for (int blk = 0; blk < nbv; ++blk) s += b.rpart[int64_t(blk) * kWindowMax + j];
-            sg[j] = j < W ? s : -INFINITY;
-            si[j] = j < W ? b.wfinal[j].idx : 0x7fffffff;
+            for (int blk = 0; blk < nbv; ++blk) s += b.rpart[int64_t(blk) * kWindowMax + j];
+            sg[j] = s;
         }
-    }
-    for (int j = 0; j < kWindowMax && nbv > kPickColumnRows; ++j) {
-        double s = 0.0;
-        if (j < W)
-            for (int blk = threadIdx.x; blk < nbv; blk += kBlock) s += b.rpart[int64_t(blk) * kWindowMax + j];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            sg[j] = j < W ? red[0] : -INFINITY;
-            si[j] = j < W ? b.wfinal[j].idx : 0x7fffffff;
-        }
-        __syncthreads();
-        if (j + 1 >= W) break;
-    }
-    if (nbv > kPickColumnRows) {
-        for (int j = W + threadIdx.x; j < kWindowMax; j += kBlock) {
-            sg[j] = -INFINITY;
-            si[j] = 0x7fffffff;
+    } else {
+        const int lane = tid & 63;
+        for (int j = tid >> 6; j < W; j += NT / 64) {
+            double q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                q[i] = 0.0;
+                for (int blk = lane + 64 * i; blk < nbv; blk += 256) q[i] += b.rpart[int64_t(blk) * kWindowMax + j];
+            }
+            double s = (q[0] + q[2]) + (q[1] + q[3]);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+            if (lane == 0) sg[j] = s;
         }
     }
     __syncthreads();
-    const int j = threadIdx.x;
-    for (int w = kWindowMax / 2; w > 0; w >>= 1) {
-        if (j < w && better(sg[j + w], si[j + w], sg[j], si[j])) {
-            sg[j] = sg[j + w];
-            si[j] = si[j + w];
-        }
-        __syncthreads();
-    }
-    if (W > 0 && sg[0] == 0.0) {
-        // The best float64 gain of the window is 0: every point is covered, so
-        // every unselected point has gain 0 and the pick is the lowest
-        // unselected index (also when more zero-gain candidates than the
-        // window holds were ranked by their reduced-precision gains).
-        __shared__ int lowest[kBlock];
-        int lo = 0x7fffffff;
-        for (int64_t i = threadIdx.x; i < c.n; i += kBlock)
-            if (!b.selected[i]) {
-                lo = int(i);
-                break;
+    if (tid < 64) {
+        double g = -INFINITY;
+        int idx = 0x7fffffff, at = -1;
+        for (int j = tid; j < W; j += 64) {
+            const int i = b.wfinal[j].idx;
+            if (better(sg[j], i, g, idx)) {
+                g = sg[j];
+                idx = i;
+                at = j;
             }
-        lowest[j] = lo;
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if (j < w && lowest[j + w] < lowest[j]) lowest[j] = lowest[j + w];
-            __syncthreads();
         }
-        if (j == 0 && lowest[0] != 0x7fffffff) si[0] = lowest[0];
-        __syncthreads();
-    }
-    if (j == 0) {
-        const int cs = si[0];
-        if (W > 0 && cs >= 0 && int64_t(cs) < c.n) {
-            b.state->cstar = cs;
-            b.state->gstar = sg[0];
-            b.selected[cs] = 1;
-            c.sel[t] = cs;
-            if (c.gain) c.gain[t] = sg[0] / double(c.n);
-        } else {
-            b.state->cstar = -1;
-            atomicCAS(&b.state->error, 0, kDevErrNonFinite);
-            c.sel[t] = -1;
-            if (c.gain) c.gain[t] = NAN;
+        wave_best(g, idx, at);
+        if (W > 0 && g == 0.0) {
+            // The best float64 gain of the window is 0: every point is covered, so
+            // every unselected point has gain 0 and the pick is the lowest
+            // unselected index (also when more zero-gain candidates than the
+            // window holds were ranked by their reduced-precision gains).
+            int lo = 0x7fffffff;
+            for (int64_t i = tid; i < c.n; i += 64)
+                if (!b.selected[i]) {
+                    lo = int(i);
+                    break;
+                }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const int o = __shfl_xor(lo, off, 64);
+                lo = o < lo ? o : lo;
+            }
+            if (lo != 0x7fffffff && lo != idx) {
+                idx = lo;
+                at = -1;
+            }
+        }
+        if (tid == 0) {
+            out_cs = W > 0 && idx >= 0 && int64_t(idx) < c.n ? idx : -1;
+            out_rank = at;
+            out_gain = g;
         }
     }
+    __syncthreads();
+    *gain = out_gain;
+    *rank = out_rank;
+    return out_cs;
+}
+
+// Record the pick (one thread). mark: set `selected` here; where other blocks
+// may still look for an unselected point, a later kernel does it.
+__device__ void pick_record(const InstDesc& c, int32_t t, int cs, double gain, int rank, bool mark) {
+    const Buffers& b = c.b;
+    b.state->cstar = cs;
+    b.state->crank = rank;
+    c.sel[t] = cs;
+    if (cs >= 0) {
+        b.state->gstar = gain;
+        if (mark) b.selected[cs] = 1;
+        if (c.gain) c.gain[t] = gain / double(c.n);
+    } else {
+        atomicCAS(&b.state->error, 0, kDevErrNonFinite);
+        if (c.gain) c.gain[t] = NAN;
+    }
+}
+
+__device__ void pick_body(const InstDesc& c, int32_t t) {
+    double gain;
+    int rank;
+    const int cs = pick_choose<kPickThreads>(c, &gain, &rank);
+    if (threadIdx.x == 0) pick_record(c, t, cs, gain, rank, true);
 }
 
 // Estimate of candidate v's present gain, and the block's best one: the gain
@@ -379,7 +454,7 @@ __device__ void pick_body(const InstDesc& c, int32_t t) {
 // (old: m_v before this step, which is what step 0 scored every candidate
 // with). The best of each block goes to bmax / barg.
 __device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, double old, double mv,
-                                    double* __restrict__ red, int* __restrict__ ri) {
+                                    double* red, int* ri) {
     const Buffers& b = c.b;
     const int64_t v = blk * kBlock + threadIdx.x;
     float* __restrict__ lm = list_m(c);
@@ -390,25 +465,27 @@ __device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, d
         m_scored = lm[v];
     double est = -INFINITY;
     if (!b.selected[v]) est = b.gsum[v] * (m_scored > 0.0f ? mv / double(m_scored) : 1.0);
-    __syncthreads();
-    red[threadIdx.x] = est;
-    ri[threadIdx.x] = int(v);
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w && better(red[threadIdx.x + w], ri[threadIdx.x + w], red[threadIdx.x], ri[threadIdx.x])) {
-            red[threadIdx.x] = red[threadIdx.x + w];
-            ri[threadIdx.x] = ri[threadIdx.x + w];
-        }
-        __syncthreads();
+    int row = int(v), none = 0;
+    wave_best(est, row, none);
+    __syncthreads();  // red has been read
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = est;
+        ri[threadIdx.x >> 6] = row;
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        b.bmax[blk] = red[0];
-        b.barg[blk] = ri[0];
+        for (int w = 1; w < kBlock / 64; ++w)
+            if (better(red[w], ri[w], est, row)) {
+                est = red[w];
+                row = ri[w];
+            }
+        b.bmax[blk] = est;
+        b.barg[blk] = row;
     }
 }
 
 // ---- update: m_v <- min(m_v, d(v, c*)) in float64, per-block sums of m_v ----
-__device__ void update_body(const InstDesc& c, int64_t blk, int32_t t) {
+__device__ void update_body(const InstDesc& c, int64_t blk, int32_t t, int cs, int rank) {
     static_assert(kNarrowMaxK <= kRescoreChunk, "short rows fit one staged piece");
     __shared__ double cx[kRescoreChunk];
     __shared__ double red[kBlock];
@@ -416,8 +493,8 @@ __device__ void update_body(const InstDesc& c, int64_t blk, int32_t t) {
     const Buffers& b = c.b;
     const float* __restrict__ x = c.x;
     const int d = c.d;
-    const int cs = b.state->cstar;
-    if (cs >= 0)
+    const bool stored = window_has_distances(c, rank);
+    if (cs >= 0 && !stored)
         for (int k = threadIdx.x; k < d; k += kBlock) cx[k] = double(x[int64_t(cs) * d + k]);
     __syncthreads();
     const int64_t v = blk * kBlock + threadIdx.x;
@@ -427,7 +504,10 @@ __device__ void update_body(const InstDesc& c, int64_t blk, int32_t t) {
     } else if (v < c.n) {
         const bool vec = (d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
         double acc[1] = {0.0};
-        row_terms<0, 1>(x + v * d, vec, d, cx, acc);
+        if (stored)
+            acc[0] = b.part[int64_t(rank) * c.n_pad + v];
+        else
+            row_terms<0, 1>(x + v * d, vec, d, cx, acc);
         mv = old = b.m64[v];
         if (acc[0] < mv) {
             mv = acc[0];
@@ -437,30 +517,30 @@ __device__ void update_body(const InstDesc& c, int64_t blk, int32_t t) {
     }
     red[threadIdx.x] = mv;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 64) {
+        const double sum = tree_sum256(red, threadIdx.x);
+        if (threadIdx.x == 0) b.fpart[blk] = sum;
     }
-    if (threadIdx.x == 0) b.fpart[blk] = red[0];
     if (c.lazy) block_best_estimate(c, blk, t, old, mv, red, ri);
 }
 
 // ---- L1 update (any row length): m_v <- min(m_v, sum_k |x_vk - x_c*k|) in
 // float64, the new member's values staged in LDS 128 at a time; per-block
 // sums of m_v as in update_body ----
-__device__ void update_l1_body(const InstDesc& c, int64_t blk, int32_t t) {
+__device__ void update_l1_body(const InstDesc& c, int64_t blk, int32_t t, int cs, int rank) {
     __shared__ float cx[kRescoreChunk];
     __shared__ double red[kBlock];
     __shared__ int ri[kBlock];
     const Buffers& b = c.b;
     const float* __restrict__ x = c.x;
     const int d = c.d;
-    const int cs = b.state->cstar;
     const int64_t v = blk * kBlock + threadIdx.x;
     const bool live = v < c.n;
     const float* xv = x + (live ? v : 0) * d;
     double acc = 0.0;
-    for (int k0 = 0; k0 < d && cs >= 0; k0 += kRescoreChunk) {
+    const bool stored = window_has_distances(c, rank);
+    if (stored && live) acc = b.part[int64_t(rank) * c.n_pad + v];
+    for (int k0 = 0; k0 < d && cs >= 0 && !stored; k0 += kRescoreChunk) {
         const int kn = (d - k0) < kRescoreChunk ? (d - k0) : kRescoreChunk;
         __syncthreads();
         for (int k = threadIdx.x; k < kn; k += kBlock) cx[k] = x[int64_t(cs) * d + k0 + k];
@@ -479,11 +559,10 @@ __device__ void update_l1_body(const InstDesc& c, int64_t blk, int32_t t) {
     }
     red[threadIdx.x] = mv;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 64) {
+        const double sum = tree_sum256(red, threadIdx.x);
+        if (threadIdx.x == 0) b.fpart[blk] = sum;
     }
-    if (threadIdx.x == 0) b.fpart[blk] = red[0];
     if (c.lazy) block_best_estimate(c, blk, t, old, mv, red, ri);
 }
 
@@ -684,11 +763,10 @@ __device__ void update_long_body(const InstDesc& c, int64_t blk) {
     }
     red[threadIdx.x] = mv;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 64) {
+        const double sum = tree_sum256(red, threadIdx.x);
+        if (threadIdx.x == 0) b.fpart[blk] = sum;
     }
-    if (threadIdx.x == 0) b.fpart[blk] = red[0];
 }
 
 // Long rows with at least 4 ground-set chunks (small ground sets): the
@@ -722,7 +800,7 @@ __device__ void dist_slice_body(const InstDesc& c, int64_t blk, int q, int S, in
     if ((d & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
         const float4* __restrict__ a4 = reinterpret_cast<const float4*>(xv);
         const float4* __restrict__ c4 = reinterpret_cast<const float4*>(xc);
-#pragma unroll 4
+#pragma unroll 8
         for (int k4 = k0 / 4; k4 < k1 / 4; ++k4) {
             const float4 a = a4[k4], b = c4[k4];
             const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
@@ -748,33 +826,6 @@ __device__ __forceinline__ double slices_sum(const InstDesc& c, int64_t v, int S
     return s;
 }
 
-// m_v update from the slice sums (pass 2), per-block sums of m_v
-__device__ void update_split_body(const InstDesc& c, int64_t blk) {
-    __shared__ double red[kBlock];
-    const Buffers& b = c.b;
-    const int cs = b.state->cstar;
-    const int64_t v = blk * kBlock + threadIdx.x;
-    double mv = 0.0;
-    if (v < c.n) {
-        mv = b.m64[v];
-        if (cs >= 0) {
-            const double dist = slices_sum(c, v, update_slices(c));
-            if (dist < mv) {
-                mv = dist;
-                b.m64[v] = mv;
-                set_point_terms(b, v, mv);
-            }
-        }
-    }
-    red[threadIdx.x] = mv;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) b.fpart[blk] = red[0];
-}
-
 // Small re-score windows of long rows (at most v_splits/4, and 4,
 // candidates): the same two passes per candidate, each candidate's distances
 // over S = min(16, v_splits / W) slices; pass 1 over (candidate, slice) on
@@ -785,6 +836,48 @@ __host__ __device__ inline int split_window(const InstDesc& c) {
 __device__ __forceinline__ int window_slices(const InstDesc& c, int W) {
     const int s = c.v_splits / W;
     return s < 16 ? s : 16;
+}
+
+// Does the window's pass 1 hold the pick's distances (window position rank)?
+__device__ __forceinline__ bool window_has_slices(const InstDesc& c, int rank) {
+    return rank >= 0 && c.b.state->window_count <= split_window(c);
+}
+
+// m_v update from the slice sums of the pick (pass 2), per-block sums of m_v.
+// A small window's pass 1 has them already; otherwise dist_slices does.
+__device__ void update_split_body(const InstDesc& c, int64_t blk, int cs, int rank) {
+    __shared__ double red[kBlock];
+    const Buffers& b = c.b;
+    InstDesc w = c;
+    int S = update_slices(c);
+    if (window_has_slices(c, rank)) {
+        S = window_slices(c, b.state->window_count);
+        w.b.part = b.part + int64_t(S) * rank * c.n_pad;
+    }
+    const int64_t v = blk * kBlock + threadIdx.x;
+    double mv = 0.0;
+    if (v < c.n) {
+        mv = b.m64[v];
+        if (cs >= 0) {
+            const double dist = slices_sum(w, v, S);
+            if (dist < mv) {
+                mv = dist;
+                b.m64[v] = mv;
+                set_point_terms(b, v, mv);
+            }
+        }
+    }
+    red[threadIdx.x] = mv;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const double sum = tree_sum256(red, threadIdx.x);
+        if (threadIdx.x == 0) b.fpart[blk] = sum;
+    }
+}
+
+// Pass 1 of the update: the pick's slices, unless the window's pass 1 has them.
+__device__ void update_slices_body(const InstDesc& c, int64_t blk, int q, int cs, int rank) {
+    if (!window_has_slices(c, rank)) dist_slice_body(c, blk, q, update_slices(c), int64_t(cs));
 }
 
 // rpart rows a re-score of W candidates fills: one per 64-point sub-block
@@ -845,11 +938,11 @@ __device__ void fsum_body(const InstDesc& c, int32_t t) {
     for (int i = threadIdx.x; i < c.nb; i += kBlock) s += c.b.fpart[i];
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 64) s = tree_sum256(red, threadIdx.x);
+    if (threadIdx.x == 0) {
+        c.f[t] = c.b.state->l0 - s / double(c.n);
+        if (c.b.state->cstar >= 0) c.b.selected[c.b.state->cstar] = 1;  // where the pick has not
     }
-    if (threadIdx.x == 0) c.f[t] = c.b.state->l0 - red[0] / double(c.n);
     if (!c.lazy) return;
     // heads of the next step's list: the best estimate of each stretch
     const int bps = list_stretch(c);
@@ -907,21 +1000,14 @@ __device__ void list_sum_body(const InstDesc& c, int32_t part, int64_t first, in
 // Rows are taken in the grouped order where there is one, so that neighbours
 // in the list are neighbours in space (their tiles clamp together).
 __device__ void list_build_body(const InstDesc& c, int64_t blk) {
-    __shared__ double red[kBlock];
     __shared__ int wave_n[kBlock / 64];
     __shared__ int base;
     const Buffers& b = c.b;
     const int heads = b.state->list_heads;
     const int32_t* __restrict__ head = list_part(c, 0);
-    double best = -INFINITY;
-    for (int i = threadIdx.x; i < heads; i += kBlock) best = fmax(best, b.gsum[head[i]]);
-    red[threadIdx.x] = best;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    best = red[0];
+    double best = -INFINITY;  // each wave for itself
+    for (int i = threadIdx.x & 63; i < heads; i += 64) best = fmax(best, b.gsum[head[i]]);
+    best = wave_max(best);
     const double slack = 2.0 * (double(c.chunk) / 32.0 + 64.0) * 0x1p-24 * fabs(best);
     const double thr = window_threshold(best, b.state) - slack;
     const int64_t i = blk * kBlock + threadIdx.x;
@@ -943,46 +1029,50 @@ __device__ void list_build_body(const InstDesc& c, int64_t blk) {
     list_rows(c)[at] = int32_t(i);
 }
 
-// The window out of the list (one block): the same candidates, and the same
-// rules above kWindowMax and kWindowCap of them, as wcount and wselect.
-// Entries land in index or rank order, so nothing depends on the list's order.
-__device__ void list_window_body(const InstDesc& c) {
+// The window out of `len` candidates (one block): rows[0 .. len), or rows 0 ..
+// len - 1 where rows is null. The same candidates, and the same rules above
+// kWindowMax and kWindowCap of them, as wcount and wselect. Entries land in
+// index or rank order, so nothing depends on the order of `rows`.
+__device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows, int len) {
     __shared__ WindowEntry list[kWindowCap];
-    __shared__ double red[kSelThreads];
-    __shared__ int ri[kSelThreads];
+    __shared__ double wg[kSelThreads / 64];
+    __shared__ int wi[kSelThreads / 64];
     __shared__ int found;
     const Buffers& b = c.b;
-    const int tid = threadIdx.x;
-    const int len = b.state->list_len;
-    const int32_t* __restrict__ rows = list_rows(c);
-    double gb = -INFINITY;
-    int ib = 0x7fffffff;
+    const int tid = threadIdx.x, lane = tid & 63;
+    auto row_at = [&](int i) { return rows ? rows[i] : i; };
+    double gb = -INFINITY, g0 = -INFINITY;
+    int ib = 0x7fffffff, r0 = 0, none = 0;
     for (int i = tid; i < len; i += kSelThreads) {
-        const int r = rows[i];
+        const int r = row_at(i);
         const double g = b.gsum[r];
+        if (i == tid) {  // kept for the second pass
+            g0 = g;
+            r0 = r;
+        }
         if (better(g, r, gb, ib)) {
             gb = g;
             ib = r;
         }
     }
-    red[tid] = gb;
-    ri[tid] = ib;
+    wave_best(gb, ib, none);
+    if (lane == 0) {
+        wg[tid >> 6] = gb;
+        wi[tid >> 6] = ib;
+    }
     if (tid == 0) found = 0;
     __syncthreads();
-    for (int w = kSelThreads / 2; w > 0; w >>= 1) {
-        if (tid < w && better(red[tid + w], ri[tid + w], red[tid], ri[tid])) {
-            red[tid] = red[tid + w];
-            ri[tid] = ri[tid + w];
-        }
-        __syncthreads();
-    }
-    const double gmax = red[0];
-    const int first = ri[0];
+    gb = lane < kSelThreads / 64 ? wg[lane] : -INFINITY;
+    ib = lane < kSelThreads / 64 ? wi[lane] : 0x7fffffff;
+    wave_best(gb, ib, none);
+    const double gmax = gb;
+    const int first = ib;
     const double thr = window_threshold(gmax, b.state);
+    auto inside = [&](double g) { return g >= thr && g > -INFINITY; };
     for (int i = tid; i < len; i += kSelThreads) {
-        const int r = rows[i];
-        const double g = b.gsum[r];
-        if (!(g >= thr && g > -INFINITY)) continue;
+        const int r = i == tid ? r0 : row_at(i);
+        const double g = i == tid ? g0 : b.gsum[r];
+        if (!inside(g)) continue;
         const int at = atomicAdd(&found, 1);
         if (at >= kWindowCap) continue;
         list[at].g = g;
@@ -1011,9 +1101,8 @@ __device__ void list_window_body(const InstDesc& c) {
             __syncthreads();
             int k = 0;
             for (int i = tid; i < len; i += kSelThreads) {
-                const int r = rows[i];
-                const double g = b.gsum[r];
-                k += (g >= thr && g > -INFINITY && r <= mid && r != first) ? 1 : 0;
+                const int r = row_at(i);
+                k += (inside(b.gsum[r]) && r <= mid && r != first) ? 1 : 0;
             }
             if (k) atomicAdd(&found, k);
             __syncthreads();
@@ -1026,9 +1115,9 @@ __device__ void list_window_body(const InstDesc& c) {
         if (tid == 0) found = 0;
         __syncthreads();
         for (int i = tid; i < len; i += kSelThreads) {
-            const int r = rows[i];
+            const int r = row_at(i);
             const double g = b.gsum[r];
-            if (!(g >= thr && g > -INFINITY && r <= hi && r != first)) continue;
+            if (!(inside(g) && r <= hi && r != first)) continue;
             const int at = atomicAdd(&found, 1);
             if (at >= kWindowMax - 1) continue;
             list[at].g = g;
@@ -1057,20 +1146,86 @@ __device__ void list_window_body(const InstDesc& c) {
     }
 }
 
+__device__ void list_window_body(const InstDesc& c) { window_body(c, list_rows(c), c.b.state->list_len); }
+
+// ---- small ground sets (at most kSmallBlocks row blocks), solo, all
+// candidates scored: the stages that need one block run as one kernel, and
+// the pick is made by every block of the update for itself. 4 launches a step
+// (gains, select, re-score, update) instead of 8: at this size each costs 2
+// to 5 us and little else counts (1000 x 16, 5 steps with the data set: 208 -> 105 us) ----
+constexpr int kSmallBlocks = 16;
+
+// f of the previous step, the gain sums, the window.
+__device__ void select_small_body(const InstDesc& c, int32_t t) {
+    const Buffers& b = c.b;
+    const int tid = threadIdx.x;
+    const int prev = t > 0 ? b.state->cstar : -1;  // not marked by its step's blocks
+    if (t > 0 && tid < 64) {
+        // the tree of fsum over at most kSmallBlocks sums
+        double s = tid < c.nb ? b.fpart[tid] : 0.0;
+#pragma unroll
+        for (int off = kSmallBlocks / 2; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+        if (tid == 0) {
+            c.f[t - 1] = b.state->l0 - s / double(c.n);
+            if (prev >= 0) b.selected[prev] = 1;
+        }
+    }
+    for (int64_t i = tid; i < c.n_pad; i += kSelThreads) {
+        double g = 0.0;
+#pragma unroll 8
+        for (int s = 0; s < c.v_splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
+        b.gsum[i] = b.selected[i] || i == prev ? -INFINITY : g;
+    }
+    window_body(c, nullptr, int(c.n_pad));  // each thread reads the sums it wrote
+}
+
+__device__ int pick_small(const InstDesc& c, int32_t t, int64_t blk, int* rank) {
+    double gain;
+    const int cs = pick_choose<kBlock>(c, &gain, rank);
+    if (blk == 0 && threadIdx.x == 0) pick_record(c, t, cs, gain, *rank, false);
+    return cs;
+}
+
 // ---- solo kernels ----
 __global__ void __launch_bounds__(kBlock) k_gsum(InstDesc c) { gsum_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_wcount(InstDesc c) { wcount_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kSelThreads) k_wselect(InstDesc c) { wselect_body(c); }
 __global__ void __launch_bounds__(kBlock) k_rescore(InstDesc c) { rescore_body(c, blockIdx.x); }
-__global__ void __launch_bounds__(kBlock) k_pick(InstDesc c, int32_t t) { pick_body(c, t); }
-__global__ void __launch_bounds__(kBlock) k_update(InstDesc c, int32_t t) { update_body(c, blockIdx.x, t); }
-__global__ void __launch_bounds__(kBlock) k_update_l1(InstDesc c, int32_t t) { update_l1_body(c, blockIdx.x, t); }
+__global__ void __launch_bounds__(kPickThreads) k_pick(InstDesc c, int32_t t) { pick_body(c, t); }
+__global__ void __launch_bounds__(kBlock) k_update(InstDesc c, int32_t t) {
+    update_body(c, blockIdx.x, t, c.b.state->cstar, c.b.state->crank);
+}
+__global__ void __launch_bounds__(kBlock) k_update_l1(InstDesc c, int32_t t) {
+    update_l1_body(c, blockIdx.x, t, c.b.state->cstar, c.b.state->crank);
+}
 __global__ void __launch_bounds__(kBlock) k_rescore_long(InstDesc c) { rescore_long_body(c, blockIdx.x, blockIdx.y); }
 __global__ void __launch_bounds__(kBlock) k_update_long(InstDesc c) { update_long_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_dist_slices(InstDesc c) {
-    dist_slice_body(c, blockIdx.x, blockIdx.y, update_slices(c), int64_t(c.b.state->cstar));
+    update_slices_body(c, blockIdx.x, blockIdx.y, c.b.state->cstar, c.b.state->crank);
 }
-__global__ void __launch_bounds__(kBlock) k_update_split(InstDesc c) { update_split_body(c, blockIdx.x); }
+__global__ void __launch_bounds__(kBlock) k_update_split(InstDesc c) {
+    update_split_body(c, blockIdx.x, c.b.state->cstar, c.b.state->crank);
+}
+__global__ void __launch_bounds__(kSelThreads) k_select_small(InstDesc c, int32_t t) { select_small_body(c, t); }
+__global__ void __launch_bounds__(kBlock) k_update_small(InstDesc c, int32_t t) {
+    int rank;
+    const int cs = pick_small(c, t, blockIdx.x, &rank);
+    if (c.metric == 1)
+        update_l1_body(c, blockIdx.x, t, cs, rank);
+    else
+        update_body(c, blockIdx.x, t, cs, rank);
+}
+__global__ void __launch_bounds__(kBlock) k_slices_small(InstDesc c, int32_t t) {
+    double gain;
+    int rank;
+    const int cs = pick_choose<kBlock>(c, &gain, &rank);
+    update_slices_body(c, blockIdx.x, blockIdx.y, cs, rank);
+}
+__global__ void __launch_bounds__(kBlock) k_update_split_small(InstDesc c, int32_t t) {
+    int rank;
+    const int cs = pick_small(c, t, blockIdx.x, &rank);
+    update_split_body(c, blockIdx.x, cs, rank);
+}
 __global__ void __launch_bounds__(kBlock) k_dist_window(InstDesc c) { dist_window_body(c, blockIdx.x, blockIdx.y); }
 __global__ void __launch_bounds__(kBlock) k_rescore_split(InstDesc c) { rescore_split_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_fsum(InstDesc c, int32_t t) { fsum_body(c, t); }
@@ -1098,15 +1253,16 @@ EBC_ROW_KERNEL(kb_list_build, list_step(c, step), list_build_body(c, blk))
 // mixed batches: each re-score / update body runs only for its own row length
 __device__ __forceinline__ void update_long(const InstDesc& c, int64_t blk) {
     if (long_split(c))
-        update_split_body(c, blk);
+        update_split_body(c, blk, c.b.state->cstar, c.b.state->crank);
     else
         update_long_body(c, blk);
 }
 EBC_ROW_KERNEL(kb_rescore, !wide_rows(c.k_pad), rescore_body(c, blk))
-EBC_ROW_KERNEL(kb_update, !wide_rows(c.k_pad), update_body(c, blk, step))
+EBC_ROW_KERNEL(kb_update, !wide_rows(c.k_pad), update_body(c, blk, step, c.b.state->cstar, c.b.state->crank))
 EBC_ROW_KERNEL(kb_rescore_long, wide_rows(c.k_pad), rescore_long_body(c, blk, blockIdx.y))
 EBC_ROW_KERNEL(kb_update_long, wide_rows(c.k_pad), update_long(c, blk))
-EBC_ROW_KERNEL(kb_dist_slices, long_split(c), dist_slice_body(c, blk, blockIdx.y, update_slices(c), c.b.state->cstar))
+EBC_ROW_KERNEL(kb_dist_slices, long_split(c),
+               update_slices_body(c, blk, blockIdx.y, c.b.state->cstar, c.b.state->crank))
 EBC_ROW_KERNEL(kb_dist_window, long_split(c), dist_window_body(c, blk, blockIdx.y))
 #undef EBC_ROW_KERNEL
 
@@ -1124,7 +1280,7 @@ __global__ void __launch_bounds__(kSelThreads) kb_list_window(const InstDesc* __
     const InstDesc c = descs[blockIdx.x];
     if (c.t0 + t < c.k && list_step(c, c.t0 + t)) list_window_body(c);
 }
-__global__ void __launch_bounds__(kBlock) kb_pick(const InstDesc* __restrict__ descs, int32_t t) {
+__global__ void __launch_bounds__(kPickThreads) kb_pick(const InstDesc* __restrict__ descs, int32_t t) {
     const InstDesc c = descs[blockIdx.x];
     if (c.t0 + t < c.k) pick_body(c, c.t0 + t);
 }
@@ -1134,11 +1290,10 @@ __global__ void __launch_bounds__(kBlock) kb_fsum(const InstDesc* __restrict__ d
 }
 
 hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out, double* f_out,
-                              double* gain_out, hipStream_t s, hipEvent_t ev_gains_done) {
+                              double* gain_out, bool last, hipStream_t s, hipEvent_t ev_gains_done) {
     InstDesc c;
     fill_desc(ds, t + 1, sel_out, f_out, gain_out, &c);
-    // a timed step is a whole launch
-    if (ds->prof || !greedy_lists_solo(ds)) c.lazy = 0;
+    if (ds->prof) c.lazy = 0;  // a timed step is a whole launch
     const int nb = c.nb;
     hipError_t e = hipSuccess;
     if (list_step(c, t)) {
@@ -1146,19 +1301,34 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
     } else {
         if ((e = launch_gains(ds, nullptr, ds->n_pad, s)) != hipSuccess) return e;
         if (ev_gains_done && (e = hipEventRecord(ev_gains_done, s)) != hipSuccess) return e;
+        if (nb <= kSmallBlocks && c.lazy == 0 && (c.metric == 1 || !wide_rows(c.k_pad) || long_split(c))) {
+            hipLaunchKernelGGL(k_select_small, dim3(1), dim3(kSelThreads), 0, s, c, t);
+            if (c.metric == 0 && wide_rows(c.k_pad)) {
+                hipLaunchKernelGGL(k_dist_window, dim3(nb, 16), dim3(kBlock), 0, s, c);
+                hipLaunchKernelGGL(k_rescore_long, dim3(nb, 4 * kWindowMax / kRescoreGroup), dim3(kBlock), 0, s, c);
+                hipLaunchKernelGGL(k_slices_small, dim3(nb, update_slices(c)), dim3(kBlock), 0, s, c, t);
+                hipLaunchKernelGGL(k_update_split_small, dim3(nb), dim3(kBlock), 0, s, c, t);
+            } else {
+                hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
+                hipLaunchKernelGGL(k_update_small, dim3(nb), dim3(kBlock), 0, s, c, t);
+            }
+            // f(S_t) and the mark of the pick: the next step's select, or here
+            if (last) hipLaunchKernelGGL(k_fsum, dim3(1), dim3(kBlock), 0, s, c, t);
+            return hipGetLastError();
+        }
         hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_wcount, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_wselect, dim3(1), dim3(kSelThreads), 0, s, c);
     }
     if (c.metric == 1) {
         hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kBlock), 0, s, c, t);
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), 0, s, c, t);
         hipLaunchKernelGGL(k_update_l1, dim3(nb), dim3(kBlock), 0, s, c, t);
     } else if (wide_rows(c.k_pad)) {
         // small windows: pass 1 over slices of the dimension here, pass 2 inside k_rescore_long
         if (long_split(c)) hipLaunchKernelGGL(k_dist_window, dim3(nb, 16), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_rescore_long, dim3(nb, 4 * kWindowMax / kRescoreGroup), dim3(kBlock), 0, s, c);
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kBlock), 0, s, c, t);
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), 0, s, c, t);
         if (long_split(c)) {
             hipLaunchKernelGGL(k_dist_slices, dim3(nb, update_slices(c)), dim3(kBlock), 0, s, c);
             hipLaunchKernelGGL(k_update_split, dim3(nb), dim3(kBlock), 0, s, c);
@@ -1167,7 +1337,7 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
         }
     } else {
         hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
-        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kBlock), 0, s, c, t);
+        hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), 0, s, c, t);
         hipLaunchKernelGGL(k_update, dim3(nb), dim3(kBlock), 0, s, c, t);
     }
     hipLaunchKernelGGL(k_fsum, dim3(1), dim3(kBlock), 0, s, c, t);
@@ -1221,7 +1391,7 @@ hipError_t launch_tick(const std::vector<GainsBucket>& buckets, const InstDesc* 
         hipLaunchKernelGGL(kb_rescore_long, dim3(unsigned(total_rows), 4 * kWindowMax / kRescoreGroup), dim3(kBlock), 0, s,
                            descs, row_pre, count, t);
     }
-    hipLaunchKernelGGL(kb_pick, one, dim3(kBlock), 0, s, descs, t);
+    hipLaunchKernelGGL(kb_pick, one, dim3(kPickThreads), 0, s, descs, t);
     hipLaunchKernelGGL(kb_update, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
     if (long_rows) {
         hipLaunchKernelGGL(kb_dist_slices, dim3(unsigned(total_rows), 16), dim3(kBlock), 0, s, descs, row_pre, count,

@@ -89,6 +89,7 @@ struct Request {
     std::vector<float> xh;
     int state = kQueued;
     int32_t t = 0;  // steps done
+    bool lists = false;  // steps after the first score lists (lazy.h)
     size_t off = 0, bytes = 0;
     float* xd = nullptr;
     void* ws = nullptr;
@@ -181,6 +182,7 @@ ebc_status admit(ebc_server* sv, Request* r) {
     const int32_t v = tuned_variant(r->ds);
     if (v >= 0) r->ds->variant = v;
     r->state = kActive;
+    r->lists = greedy_lists_worth(r->ds) > 0.25;  // a tick's launches are shared by several requests
     r->t = 0;
     r->t_admit = now_s();
     return EBC_OK;
@@ -209,7 +211,7 @@ void rebuild_tables(ebc_server* sv) {
         for (int32_t i = 0; i < count; ++i) {
             const ebc_dataset* ds = sv->active[i]->ds;
             if (gains_bucket(ds) != key) continue;
-            b.lists |= greedy_lists(ds);
+            b.lists |= sv->active[i]->lists;
             const int64_t tile = gains_cand_tile(ds);
             acc += (ds->n_pad + tile - 1) / tile * ds->v_splits;
             sv->h_slot.push_back(i);
@@ -358,6 +360,7 @@ ebc_status ebc_server_step(ebc_server* sv, int32_t* completed) {
     for (int32_t i = 0; i < count; ++i) {
         Request* r = sv->active[i];
         fill_desc(r->ds, r->k, r->sel_d, r->f_d, r->gain_d, &hd[i]);
+        hd[i].lazy = r->lists;
         hd[i].t0 = r->t;
     }
     memcpy(h + sv->tl.row_pre, sv->h_row_pre.data(), sv->h_row_pre.size() * sizeof(int64_t));
@@ -367,7 +370,7 @@ ebc_status ebc_server_step(ebc_server* sv, int32_t* completed) {
     bool long_rows = false, full = false, lists = false;
     for (const Request* r : sv->active) {
         long_rows |= wide_rows(r->ds->k_pad);
-        (r->t > 0 && greedy_lists(r->ds) ? lists : full) = true;
+        (r->t > 0 && r->lists ? lists : full) = true;
     }
     if (e == hipSuccess)
         e = launch_tick(sv->buckets, sv->d_desc, sv->d_row_pre, sv->d_slot, sv->d_wg_pre, count, sv->total_rows, 0,

@@ -464,7 +464,7 @@ ebc_status start_stream(ebc_dataset* ds, double* m_max, int32_t* sel_tmp, double
                         DevState* st) {
     if (launch_reset_state(ds, s) != hipSuccess) return EBC_E_DEVICE;
     if (!(*m_max > 0.0)) {
-        if (launch_greedy_step(ds, 0, sel_tmp, f_tmp, nullptr, s, nullptr) != hipSuccess ||
+        if (launch_greedy_step(ds, 0, sel_tmp, f_tmp, nullptr, true, s, nullptr) != hipSuccess ||
             read_state(ds, st, s) != hipSuccess)
             return EBC_E_DEVICE;
         *m_max = st->gstar / double(ds->n);

@@ -130,3 +130,31 @@ def test_server_with_lists_equals_solo():
         assert r["state"] == "done"
         assert np.array_equal(r["sel"], w[0]) and np.array_equal(r["f"], w[1]) and np.array_equal(r["gain"], w[2])
     sv.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 257, 1000, 4096, 4097])
+@pytest.mark.parametrize("d,dtype", [(5, "f32"), (40, "bf16"), (200, "f32"), (131, "fp8")])
+def test_small_ground_sets_equal_a_batch_of_one(n, d, dtype):
+    """Solo runs on at most 4096 points take the fused stages, a batch the separate ones."""
+    x = torch.from_numpy(points("few" if n == 255 else "mixture", n, d, n + d)).cuda()
+    ds = ebc.Dataset(x, dtype=dtype)
+    k = min(n, 11)
+    solo = [t.cpu().numpy() for t in ds.greedy(k)]
+    ds.sync()
+    got = [t.cpu().numpy() for t in ebc.Batch([ds]).greedy([k])[0]]
+    ds.sync()
+    assert all(np.array_equal(a, b) for a, b in zip(solo, got))
+    assert len(set(solo[0].tolist())) == k
+
+
+@pytest.mark.parametrize("n,d", [(3, 4), (256, 31), (2049, 6)])
+def test_small_l1_against_oracle(n, d):
+    from oracle import ebc_oracle
+    x = points("mixture", n, d, n)
+    ds = ebc.Dataset(torch.from_numpy(x).cuda(), dist="l1")
+    k = min(n, 6)
+    sel, f, _ = ds.greedy(k)
+    ds.sync()
+    rsel, rf, _ = ebc_oracle.greedy(x, k, dist="l1")
+    assert sel.cpu().numpy().tolist() == rsel.tolist()
+    np.testing.assert_allclose(f.cpu().numpy(), rf, rtol=1e-12)

@@ -99,7 +99,11 @@ typedef enum {
 /* Exact device workspace that ebc_dataset_create needs for (n, d, dt), in
  * bytes; 0 if the arguments are invalid. The library allocates no device
  * memory of its own, so this is the whole device footprint of a dataset
- * besides the caller's input points. */
+ * besides the caller's input points. For rows of more than 128 values and at
+ * most 4096 points it includes, at its end, room for one float per pair of
+ * points (n rounded up to 256, squared), with which greedy steps after the
+ * first need no dot products; ebc_dataset_create accepts a workspace without
+ * it, and the served requests (ebc_request_bytes) do not count it. */
 EBC_API size_t ebc_dataset_bytes(int64_t n, int32_t d, ebc_dtype dt);
 
 /* Make the ground set V resident and precompute what every evaluation reuses

@@ -99,7 +99,7 @@ ebc_status ebc_dataset_create(const float* x, int64_t n, int32_t d, ebc_dtype dt
     if ((flags & EBC_FLAG_L1) && dt != EBC_DT_F32) return EBC_E_UNSUPPORTED;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return EBC_E_INVALID_ARG;
     const Layout L = layout(n, d, dt);
-    if (workspace_bytes < L.total) return EBC_E_INVALID_ARG;
+    if (workspace_bytes < L.least) return EBC_E_INVALID_ARG;
 
     ebc_dataset* ds = new (std::nothrow) ebc_dataset;
     if (!ds) return EBC_E_NOMEM;
@@ -137,6 +137,8 @@ ebc_status ebc_dataset_create(const float* x, int64_t n, int32_t d, ebc_dtype dt
     b.rpart = reinterpret_cast<double*>(w + L.off_rpart);
     b.fpart = reinterpret_cast<double*>(w + L.off_fpart);
     b.state = reinterpret_cast<DevState*>(w + L.off_state);
+    if (pair_matrix(ds->n_pad, ds->k_pad) && ds->metric == 0 && workspace_bytes >= L.total)
+        b.pairs = reinterpret_cast<float*>(w + L.off_pairs);
     if (grouped(ds->k_pad, dt)) {
         b.perm = reinterpret_cast<int32_t*>(w + L.off_perm);
         b.inv = reinterpret_cast<int32_t*>(w + L.off_inv);

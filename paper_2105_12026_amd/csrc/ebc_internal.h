@@ -93,6 +93,10 @@ struct Buffers {
     float* hap;         // [n_pad] ha in slot order (kept in step with ha)
     float* hmp;         // [n_pad] hm in slot order (kept in step with hm)
     int* scp;           // [n_pad] FP8 row scales in slot order (FP8 only)
+    // Pair matrix of a greedy run on few long rows (null elsewhere, and in
+    // workspaces without room for it): -d^(v, c) / 2 in float32, written by the
+    // first step's gains and read by the later ones.
+    float* pairs;       // [n_pad, n_pad]
     int32_t* gbucket;   // [n_pad] nearest pivot of each row (set-up only)
     int32_t* gcount;    // [nb, groups] per-block bucket counts, then slot offsets (set-up only)
 };
@@ -188,11 +192,16 @@ __device__ __forceinline__ int fresh_tid() {
 struct Layout {
     size_t off_xq, off_scale, off_mu, off_n64, off_m0, off_m64, off_hn, off_ha, off_hm, off_sel, off_part, off_gsum, off_bmax,
         off_barg, off_bcnt, off_wstage, off_wfinal, off_rpart, off_fpart, off_state, off_perm, off_inv, off_xqp,
-        off_hnp, off_hap, off_hmp, off_scp, off_gbucket, off_gcount, total;
+        off_hnp, off_hap, off_hmp, off_scp, off_gbucket, off_gcount, off_pairs, least, total;
+    // least: without the pair matrix, which a workspace may do without
 };
 
 // Datasets whose reduced-precision gains run in grouped order (see Buffers::perm).
 __host__ __device__ inline bool grouped(int32_t k_pad, ebc_dtype dt) { return dt != EBC_DT_F32 && !wide_rows(k_pad); }
+// Datasets whose greedy runs keep a pair matrix (Buffers::pairs): long rows, at
+// most 4096 points (64 MiB). A later step then reads 4 bytes a pair instead of
+// multiplying k_pad values.
+__host__ __device__ inline bool pair_matrix(int64_t n_pad, int32_t k_pad) { return wide_rows(k_pad) && n_pad <= 4096; }
 // Number of pivots (buckets) of the grouped order: one per 256 points, 1 .. 256.
 __host__ __device__ inline int32_t group_count(int64_t n) {
     const int64_t g = n / 256;
@@ -327,6 +336,13 @@ __host__ __device__ inline GainsArgs gains_args(const InstDesc& d, const int32_t
     return a;
 }
 
+// Does step `step` of a greedy run take its gains from the pair matrix?
+__host__ __device__ inline bool matrix_step(const InstDesc& c, int32_t step) { return c.b.pairs != nullptr && step > 0; }
+// Partial sums per candidate that a step's gains leave in `part`.
+__host__ __device__ inline int32_t gain_splits(const InstDesc& c, int32_t step) {
+    return matrix_step(c, step) ? 1 : c.v_splits;
+}
+
 // Batched launches over a device table of descriptors (see ebc_batch).
 hipError_t launch_gains_f32_batched(int32_t k_pad, bool trim, const InstDesc* descs, const int32_t* slot_inst,
                                     const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t,
@@ -379,6 +395,10 @@ hipError_t launch_load_m(const ebc_dataset* ds, const double* m, hipStream_t s);
 hipError_t launch_gains_f32(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 hipError_t launch_gains_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 hipError_t launch_gains_wide(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
+hipError_t launch_gains_wide_pairs(const InstDesc& c, hipStream_t s);   // gains, and the pair matrix
+hipError_t launch_gains_matrix(const InstDesc& c, hipStream_t s);       // gains from the pair matrix
+hipError_t launch_gains_matrix_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count,
+                                       int64_t total_rows, int32_t t, hipStream_t s);
 hipError_t launch_gains_l1(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 hipError_t launch_gains(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 // gains of the instance's heads (part 0) or list (part 1), see lazy.h

@@ -26,8 +26,10 @@ namespace ebc {
 
 namespace {
 
-template <int DT, int KS>
-__device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_pad, int64_t bid) {
+// PAIRS (KS = 4): also write the pair matrix, x_v . x_c - hn_c - hn_v.
+template <int DT, int KS, bool PAIRS = false>
+__device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_pad, int64_t bid,
+                                                float* __restrict__ pairs = nullptr) {
     using R = WideRow<DT>;
     using Piece = typename R::Piece;
     constexpr int B = R::kBatch;
@@ -169,12 +171,19 @@ __device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_p
             const int cbe = wave >> 1;  // the 32-point block whose clamps this wave takes
             const int64_t v = v0 + cbe * 32 + col;
             const float hav = ha[v], hmw = hm[v];
+            const float hnv = PAIRS ? hn[v] : 0.0f;
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
                 const int r = r0 + i;
                 float t = nhn[i] + hav;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) t += red[((w * 2 + cbe) * 16 + r) * 64 + lane];
+                if constexpr (PAIRS) {
+                    float e = nhn[i] - hnv;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) e += red[((w * 2 + cbe) * 16 + r) * 64 + lane];
+                    pairs[(cbase + acc_row(r, half)) * n_pad + v] = e;
+                }
                 acc_sum[i] += __builtin_amdgcn_fmed3f(t, 0.0f, hmw);
             }
             __syncthreads();  // red is rewritten by the next tile
@@ -210,6 +219,48 @@ __device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_p
     }
 }
 
+// Gains of one candidate from the pair matrix, by one wave: the term of point
+// v is med3(pair + hm_v, 0, hm_v). Four float32 sums a lane, added up in
+// float64. 4 bytes a pair are what bounds it: 1000 points (4 MB, in the L2s)
+// 84 -> 4 us a step against multiplying rows of 3524 values again.
+__device__ __forceinline__ void gains_matrix_row(const InstDesc& c, int64_t row) {
+    const int lane = threadIdx.x & 63;
+    const float4* __restrict__ e4 = reinterpret_cast<const float4*>(c.b.pairs + row * c.n_pad);
+    const float4* __restrict__ h4 = reinterpret_cast<const float4*>(c.b.hm);
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int64_t i = lane; i < c.n_pad / 4; i += 64) {
+        const float4 e = e4[i], h = h4[i];
+        a[0] += __builtin_amdgcn_fmed3f(e.x + h.x, 0.0f, h.x);
+        a[1] += __builtin_amdgcn_fmed3f(e.y + h.y, 0.0f, h.y);
+        a[2] += __builtin_amdgcn_fmed3f(e.z + h.z, 0.0f, h.z);
+        a[3] += __builtin_amdgcn_fmed3f(e.w + h.w, 0.0f, h.w);
+    }
+    double s = (double(a[0]) + double(a[1])) + (double(a[2]) + double(a[3]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) c.b.part[row] = 2.0 * s;
+}
+
+__global__ void __launch_bounds__(256) k_gains_matrix(InstDesc c) {
+    gains_matrix_row(c, int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6));
+}
+
+// Batched: row block on blockIdx.x, 16 candidates of it on blockIdx.y.
+__global__ void __launch_bounds__(256)
+kb_gains_matrix(const InstDesc* __restrict__ descs, const int64_t* __restrict__ row_pre, int32_t count, int32_t t) {
+    const int i = find_slot(row_pre, count, blockIdx.x);
+    const InstDesc c = descs[i];
+    if (c.t0 + t >= c.k || !matrix_step(c, c.t0 + t)) return;
+    const int64_t row = (int64_t(blockIdx.x) - row_pre[i]) * kBlock + blockIdx.y * 16 + (threadIdx.x >> 6) * 4;
+    for (int j = 0; j < 4; ++j) gains_matrix_row(c, row + j);
+}
+
+template <int DT>
+__global__ void __launch_bounds__(256) k_gains_wide_pairs(GainsArgs ga, int32_t k_pad, float* pairs) {
+    gains_wide_body<DT, 4, true>(ga, k_pad, blockIdx.x, pairs);
+}
+
 template <int DT, int KS>
 __global__ void __launch_bounds__(256) k_gains_wide(GainsArgs ga, int32_t k_pad) {
     gains_wide_body<DT, KS>(ga, k_pad, blockIdx.x);
@@ -223,7 +274,14 @@ kb_gains_wide(const InstDesc* __restrict__ descs, const int32_t* __restrict__ sl
               const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
     const int j = find_slot(wg_pre, slots, blockIdx.x);
     const InstDesc c = descs[slot_inst[j]];
-    if (c.t0 + t >= c.k) return;
+    if (c.t0 + t >= c.k || matrix_step(c, c.t0 + t)) return;
+    if constexpr (KS == 4) {
+        if (c.b.pairs) {
+            gains_wide_body<DT, KS, true>(gains_args(c, nullptr, c.n_pad), c.k_pad, int64_t(blockIdx.x) - wg_pre[j],
+                                          c.b.pairs);
+            return;
+        }
+    }
     gains_wide_body<DT, KS>(gains_args(c, nullptr, c.n_pad), c.k_pad, int64_t(blockIdx.x) - wg_pre[j]);
 }
 
@@ -256,6 +314,34 @@ void launch_wb(int32_t ks, const InstDesc* descs, const int32_t* slot_inst, cons
 }
 
 }  // namespace
+
+hipError_t launch_gains_wide_pairs(const InstDesc& c, hipStream_t s) {
+    const dim3 g = dim3(unsigned(c.n_pad / 32 * c.v_splits)), b = dim3(256);
+    const GainsArgs ga = gains_args(c, nullptr, c.n_pad);
+    switch (c.dt) {
+        case EBC_DT_F32: hipLaunchKernelGGL(k_gains_wide_pairs<EBC_DT_F32>, g, b, 0, s, ga, c.k_pad, c.b.pairs); break;
+        case EBC_DT_F16: hipLaunchKernelGGL(k_gains_wide_pairs<EBC_DT_F16>, g, b, 0, s, ga, c.k_pad, c.b.pairs); break;
+        case EBC_DT_BF16:
+            hipLaunchKernelGGL(k_gains_wide_pairs<EBC_DT_BF16>, g, b, 0, s, ga, c.k_pad, c.b.pairs);
+            break;
+        case EBC_DT_FP8_E4M3:
+            hipLaunchKernelGGL(k_gains_wide_pairs<EBC_DT_FP8_E4M3>, g, b, 0, s, ga, c.k_pad, c.b.pairs);
+            break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_gains_matrix(const InstDesc& c, hipStream_t s) {
+    hipLaunchKernelGGL(k_gains_matrix, dim3(unsigned(c.n_pad / 4)), dim3(256), 0, s, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_gains_matrix_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count,
+                                       int64_t total_rows, int32_t t, hipStream_t s) {
+    hipLaunchKernelGGL(kb_gains_matrix, dim3(unsigned(total_rows), kBlock / 16), dim3(256), 0, s, descs, row_pre, count, t);
+    return hipGetLastError();
+}
 
 hipError_t launch_gains_wide(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
     const int32_t ks = wide_ksplit(ds->n_pad);

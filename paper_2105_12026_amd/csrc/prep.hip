@@ -182,6 +182,8 @@ Layout layout(int64_t n, int32_t d, ebc_dtype dt) {
         L.off_gbucket = take(size_t(np) * sizeof(int32_t));
         L.off_gcount = take(size_t(np / kBlock) * group_count(n) * sizeof(int32_t));
     }
+    L.least = o;
+    L.off_pairs = pair_matrix(np, kp) ? take(size_t(np) * np * sizeof(float)) : 0;
     L.total = o;
     return L;
 }

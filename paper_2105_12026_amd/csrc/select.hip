@@ -77,14 +77,14 @@ __device__ double block_gmax(const double* bmax, int nb, double* red) {
 }
 
 // ---- gsum: per-chunk sums -> gsum, selected masked, block maxima ----
-__device__ void gsum_body(const InstDesc& c, int64_t blk) {
+__device__ void gsum_body(const InstDesc& c, int64_t blk, int32_t splits) {
     __shared__ double sg[kBlock / 64];
     __shared__ int si[kBlock / 64];
     const Buffers& b = c.b;
     const int64_t i = blk * kBlock + threadIdx.x;
     double g = 0.0;
 #pragma unroll 8
-    for (int s = 0; s < c.v_splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
+    for (int s = 0; s < splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
     if (b.selected[i]) g = -INFINITY;
     b.gsum[i] = g;
     int row = int(i), none = 0;
@@ -1156,7 +1156,7 @@ __device__ void list_window_body(const InstDesc& c) { window_body(c, list_rows(c
 constexpr int kSmallBlocks = 16;
 
 // f of the previous step, the gain sums, the window.
-__device__ void select_small_body(const InstDesc& c, int32_t t) {
+__device__ void select_small_body(const InstDesc& c, int32_t t, int32_t splits) {
     const Buffers& b = c.b;
     const int tid = threadIdx.x;
     const int prev = t > 0 ? b.state->cstar : -1;  // not marked by its step's blocks
@@ -1173,7 +1173,7 @@ __device__ void select_small_body(const InstDesc& c, int32_t t) {
     for (int64_t i = tid; i < c.n_pad; i += kSelThreads) {
         double g = 0.0;
 #pragma unroll 8
-        for (int s = 0; s < c.v_splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
+        for (int s = 0; s < splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
         b.gsum[i] = b.selected[i] || i == prev ? -INFINITY : g;
     }
     window_body(c, nullptr, int(c.n_pad));  // each thread reads the sums it wrote
@@ -1187,7 +1187,9 @@ __device__ int pick_small(const InstDesc& c, int32_t t, int64_t blk, int* rank) 
 }
 
 // ---- solo kernels ----
-__global__ void __launch_bounds__(kBlock) k_gsum(InstDesc c) { gsum_body(c, blockIdx.x); }
+__global__ void __launch_bounds__(kBlock) k_gsum(InstDesc c, int32_t splits) {
+    gsum_body(c, blockIdx.x, splits);
+}
 __global__ void __launch_bounds__(kBlock) k_wcount(InstDesc c) { wcount_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kSelThreads) k_wselect(InstDesc c) { wselect_body(c); }
 __global__ void __launch_bounds__(kBlock) k_rescore(InstDesc c) { rescore_body(c, blockIdx.x); }
@@ -1206,7 +1208,9 @@ __global__ void __launch_bounds__(kBlock) k_dist_slices(InstDesc c) {
 __global__ void __launch_bounds__(kBlock) k_update_split(InstDesc c) {
     update_split_body(c, blockIdx.x, c.b.state->cstar, c.b.state->crank);
 }
-__global__ void __launch_bounds__(kSelThreads) k_select_small(InstDesc c, int32_t t) { select_small_body(c, t); }
+__global__ void __launch_bounds__(kSelThreads) k_select_small(InstDesc c, int32_t t, int32_t splits) {
+    select_small_body(c, t, splits);
+}
 __global__ void __launch_bounds__(kBlock) k_update_small(InstDesc c, int32_t t) {
     int rank;
     const int cs = pick_small(c, t, blockIdx.x, &rank);
@@ -1247,7 +1251,7 @@ __global__ void __launch_bounds__(kSelThreads) k_list_window(InstDesc c) { list_
         const int64_t blk = int64_t(blockIdx.x) - row_pre[i];                                          \
         if (step < c.k && (COND)) BODY;                                                                \
     }
-EBC_ROW_KERNEL(kb_gsum, !list_step(c, step), gsum_body(c, blk))
+EBC_ROW_KERNEL(kb_gsum, !list_step(c, step), gsum_body(c, blk, gain_splits(c, step)))
 EBC_ROW_KERNEL(kb_wcount, !list_step(c, step), wcount_body(c, blk))
 EBC_ROW_KERNEL(kb_list_build, list_step(c, step), list_build_body(c, blk))
 // mixed batches: each re-score / update body runs only for its own row length
@@ -1293,16 +1297,25 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
                               double* gain_out, bool last, hipStream_t s, hipEvent_t ev_gains_done) {
     InstDesc c;
     fill_desc(ds, t + 1, sel_out, f_out, gain_out, &c);
-    if (ds->prof) c.lazy = 0;  // a timed step is a whole launch
+    if (ds->prof) {  // a timed step is a whole launch
+        c.lazy = 0;
+        c.b.pairs = nullptr;
+    }
     const int nb = c.nb;
     hipError_t e = hipSuccess;
     if (list_step(c, t)) {
         if ((e = launch_list_step(c, s)) != hipSuccess) return e;
     } else {
-        if ((e = launch_gains(ds, nullptr, ds->n_pad, s)) != hipSuccess) return e;
+        if (matrix_step(c, t))
+            e = launch_gains_matrix(c, s);
+        else if (c.b.pairs)
+            e = launch_gains_wide_pairs(c, s);
+        else
+            e = launch_gains(ds, nullptr, ds->n_pad, s);
+        if (e != hipSuccess) return e;
         if (ev_gains_done && (e = hipEventRecord(ev_gains_done, s)) != hipSuccess) return e;
         if (nb <= kSmallBlocks && c.lazy == 0 && (c.metric == 1 || !wide_rows(c.k_pad) || long_split(c))) {
-            hipLaunchKernelGGL(k_select_small, dim3(1), dim3(kSelThreads), 0, s, c, t);
+            hipLaunchKernelGGL(k_select_small, dim3(1), dim3(kSelThreads), 0, s, c, t, gain_splits(c, t));
             if (c.metric == 0 && wide_rows(c.k_pad)) {
                 hipLaunchKernelGGL(k_dist_window, dim3(nb, 16), dim3(kBlock), 0, s, c);
                 hipLaunchKernelGGL(k_rescore_long, dim3(nb, 4 * kWindowMax / kRescoreGroup), dim3(kBlock), 0, s, c);
@@ -1316,7 +1329,7 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
             if (last) hipLaunchKernelGGL(k_fsum, dim3(1), dim3(kBlock), 0, s, c, t);
             return hipGetLastError();
         }
-        hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(kBlock), 0, s, c, gain_splits(c, t));
         hipLaunchKernelGGL(k_wcount, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_wselect, dim3(1), dim3(kSelThreads), 0, s, c);
     }
@@ -1368,6 +1381,8 @@ hipError_t launch_tick(const std::vector<GainsBucket>& buckets, const InstDesc* 
             if ((e = launch_gains_batched(b.key, descs, slot_inst + b.slot_begin, wg_pre + b.pre_off, b.slots,
                                           b.total_wgs, t, s)) != hipSuccess)
                 return e;
+        if (long_rows && (e = launch_gains_matrix_batched(descs, row_pre, count, total_rows, t, s)) != hipSuccess)
+            return e;
         hipLaunchKernelGGL(kb_gsum, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
         hipLaunchKernelGGL(kb_wcount, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
         hipLaunchKernelGGL(kb_wselect, one, dim3(kSelThreads), 0, s, descs, t);

@@ -105,10 +105,11 @@ struct Request {
 };
 
 // Device footprint of one request inside the arena: its points, the dataset
-// workspace and the outputs.
+// workspace (without the pair matrix: room for more requests is worth more)
+// and the outputs.
 size_t request_bytes(int64_t n, int32_t d, int32_t k, ebc_dtype dt, size_t* ws_bytes) {
-    *ws_bytes = ebc_dataset_bytes(n, d, dt);
-    if (*ws_bytes == 0) return 0;
+    if (ebc_dataset_bytes(n, d, dt) == 0) return 0;
+    *ws_bytes = layout(n, d, dt).least;
     return a256(size_t(n) * d * sizeof(float)) + a256(*ws_bytes) + a256(size_t(k) * sizeof(int32_t)) +
            2 * a256(size_t(k) * sizeof(double));
 }

@@ -158,3 +158,33 @@ def test_small_l1_against_oracle(n, d):
     rsel, rf, _ = ebc_oracle.greedy(x, k, dist="l1")
     assert sel.cpu().numpy().tolist() == rsel.tolist()
     np.testing.assert_allclose(f.cpu().numpy(), rf, rtol=1e-12)
+
+
+@pytest.mark.parametrize("n,d,dtype,k", [(300, 129, "f32", 12), (1000, 777, "f32", 20), (1000, 777, "bf16", 20),
+                                         (513, 400, "f16", 9), (4096, 150, "fp8", 15), (4097, 150, "f32", 6)])
+def test_pair_matrix_picks_what_dot_products_pick(n, d, dtype, k):
+    """Long rows: a profiled run multiplies the rows at every step; a workspace
+    without room for the pair matrix makes every run do so."""
+    x = points("curves", n, d, n + d)
+    full, matrix = both(x, k, dtype)
+    assert matrix[0].tolist() == full[0].tolist()
+    assert np.array_equal(matrix[1], full[1]) and np.array_equal(matrix[2], full[2])
+    t = torch.from_numpy(x).cuda()
+    lib, nbytes = ebc.lib(), ebc.Dataset(t, dtype=dtype).workspace_bytes
+    n_pad = -(-n // 256) * 256
+    least = nbytes - (4 * n_pad * n_pad if n <= 4096 else 0)
+    ds = ebc.Dataset.__new__(ebc.Dataset)
+    ds.x, ds.n, ds.d, ds.dtype, ds.dist, ds._h = t, n, d, dtype, "sqeuclidean", None
+    ds.workspace = torch.empty(least, dtype=torch.uint8, device="cuda")
+    import ctypes
+    h = ctypes.c_void_p()
+    args = (ctypes.c_void_p(t.data_ptr()), n, d, ebc.DTYPES[dtype], 0, ctypes.c_void_p(ds.workspace.data_ptr()))
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert lib.ebc_dataset_create(*args, least - 1, stream, ctypes.byref(h)) == 1  # invalid argument, as before
+    assert lib.ebc_dataset_create(*args, least, stream, ctypes.byref(h)) == 0
+    ds._h = h
+    sel, f, _ = ds.greedy(k)
+    ds.sync()
+    assert sel.cpu().numpy().tolist() == full[0].tolist() and np.array_equal(f.cpu().numpy(), full[1])
+    got = [q.cpu().numpy() for q in ebc.Batch([ebc.Dataset(t, dtype=dtype), ds]).greedy([k, k])[0]]
+    assert np.array_equal(got[0], full[0]) and np.array_equal(got[1], full[1])

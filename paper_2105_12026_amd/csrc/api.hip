@@ -263,7 +263,7 @@ ebc_status ebc_marginal_gains(ebc_dataset* ds, const double* m, const int32_t* c
     for (int64_t p0 = 0; p0 < n_cand && e == hipSuccess; p0 += ds->n_pad) {
         const int64_t cnt = (n_cand - p0) < ds->n_pad ? (n_cand - p0) : ds->n_pad;
         const int32_t* c = cand ? cand + p0 : nullptr;
-        e = launch_gains(ds, c, cnt, s);
+        e = launch_gains_call(ds, c, cnt, s);
         if (e == hipSuccess) e = launch_gains_out(ds, cnt, gains_out + p0, s);
     }
     return from_hip(e);

@@ -211,6 +211,10 @@ __host__ __device__ inline int32_t group_count(int64_t n) {
 int64_t pad_rows(int64_t n);
 int32_t k_pad_for(int32_t d, ebc_dtype dt);
 int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt);
+// Chunks of ebc_marginal_gains: float32 sums end with a chunk, so its results
+// depend on them; greedy, whose float32 gains only choose what is re-scored,
+// may cut finer (v_splits_for, never fewer).
+int32_t call_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt);
 Layout layout(int64_t n, int32_t d, ebc_dtype dt);
 
 }  // namespace ebc
@@ -304,7 +308,7 @@ struct PinnedTables {
 };
 
 // Host helpers shared by the solo and batched paths.
-int64_t gains_chunk(const ebc_dataset* ds);
+int64_t gains_chunk(const ebc_dataset* ds, int32_t splits);
 int64_t gains_cand_tile(const ebc_dataset* ds);
 // How far scoring lists (lazy.h) pays in greedy steps of this dataset: above 1
 // it does when the dataset runs alone; 0 if it cannot.
@@ -392,15 +396,18 @@ hipError_t launch_prep(const ebc_dataset* ds, hipStream_t s);
 hipError_t launch_reset_state(const ebc_dataset* ds, hipStream_t s);
 hipError_t launch_set_e0(const ebc_dataset* ds, const float* e0, hipStream_t s);
 hipError_t launch_load_m(const ebc_dataset* ds, const double* m, hipStream_t s);
-hipError_t launch_gains_f32(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
-hipError_t launch_gains_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
-hipError_t launch_gains_wide(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
+hipError_t launch_gains_f32(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
+hipError_t launch_gains_lp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
+hipError_t launch_gains_wide(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
 hipError_t launch_gains_wide_pairs(const InstDesc& c, hipStream_t s);   // gains, and the pair matrix
 hipError_t launch_gains_matrix(const InstDesc& c, hipStream_t s);       // gains from the pair matrix
 hipError_t launch_gains_matrix_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count,
                                        int64_t total_rows, int32_t t, hipStream_t s);
-hipError_t launch_gains_l1(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
-hipError_t launch_gains(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
+hipError_t launch_gains_l1(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
+// gains of all rows as a greedy step wants them (part: v_splits x n_pad) ...
+hipError_t launch_gains(const ebc_dataset* ds, hipStream_t s);
+// ... and of ebc_marginal_gains (cand null: all rows; part: call_splits x n_pad)
+hipError_t launch_gains_call(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
 // gains of the instance's heads (part 0) or list (part 1), see lazy.h
 hipError_t launch_gains_f32_list(const InstDesc& c, int32_t part, hipStream_t s);
 hipError_t launch_gains_lp_list(const InstDesc& c, int32_t part, hipStream_t s);

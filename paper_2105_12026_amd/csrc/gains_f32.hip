@@ -271,25 +271,22 @@ kb_gains_f32_list(const InstDesc* __restrict__ descs, const int32_t* __restrict_
 }
 
 template <int KP>
-static void launch_kp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
-    const int64_t tiles = (n_cand + kGainsCandTile - 1) / kGainsCandTile;
-    InstDesc c;
-    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
+static void launch_kp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
+    const int64_t tiles = (ga.n_cand + kGainsCandTile - 1) / kGainsCandTile;
+    const dim3 grid = dim3(unsigned(tiles * ga.v_splits));
     if (ds->d <= KP - 4)  // the rows' last 4 padded slots are empty
-        hipLaunchKernelGGL((k_gains_f32<KP, true>), dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s,
-                           gains_args(c, cand, n_cand));
+        hipLaunchKernelGGL((k_gains_f32<KP, true>), grid, dim3(256), 0, s, ga);
     else
-        hipLaunchKernelGGL((k_gains_f32<KP, false>), dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s,
-                           gains_args(c, cand, n_cand));
+        hipLaunchKernelGGL((k_gains_f32<KP, false>), grid, dim3(256), 0, s, ga);
 }
 
 #define EBC_F32_KPS(X) \
     X(8) X(16) X(24) X(32) X(40) X(48) X(56) X(64) X(72) X(80) X(88) X(96) X(104) X(112) X(120) X(128)
 
-hipError_t launch_gains_f32(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+hipError_t launch_gains_f32(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     switch (ds->k_pad) {
 #define EBC_KP(K) \
-    case K: launch_kp<K>(ds, cand, n_cand, s); break;
+    case K: launch_kp<K>(ds, ga, s); break;
         EBC_F32_KPS(EBC_KP)
 #undef EBC_KP
         default: return hipErrorInvalidValue;

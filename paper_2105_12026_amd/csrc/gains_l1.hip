@@ -207,12 +207,12 @@ hipError_t launch_gains_l1_list(const InstDesc& c, int32_t part, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_gains_l1(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+hipError_t launch_gains_l1(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     InstDesc c;
     fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
-    const L1Args a = l1_args(c, gains_args(c, cand, n_cand));
-    const int64_t tiles = (n_cand + kL1Cand - 1) / kL1Cand;
-    hipLaunchKernelGGL(k_gains_l1, dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s, a);
+    const L1Args a = l1_args(c, ga);
+    const int64_t tiles = (ga.n_cand + kL1Cand - 1) / kL1Cand;
+    hipLaunchKernelGGL(k_gains_l1, dim3(unsigned(tiles * ga.v_splits)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

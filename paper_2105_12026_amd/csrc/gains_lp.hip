@@ -805,33 +805,24 @@ kb_gains_lp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot
 }
 
 template <int DT, int KC, int CB, bool PIPE>
-static void launch_lp_v(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+static void launch_lp_v(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     using G = LpGeom<DT, KC, CB>;
-    const int64_t tiles = (n_cand + G::CAND_TILE - 1) / G::CAND_TILE;
-    InstDesc c;
-    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
-    hipLaunchKernelGGL((k_gains_lp<DT, KC, CB, PIPE>), dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s,
-                       gains_args(c, cand, n_cand));
+    const int64_t tiles = (ga.n_cand + G::CAND_TILE - 1) / G::CAND_TILE;
+    hipLaunchKernelGGL((k_gains_lp<DT, KC, CB, PIPE>), dim3(unsigned(tiles * ga.v_splits)), dim3(256), 0, s, ga);
 }
 
 template <int DT, int KC, int CB, int VTS>
-static void launch_lp_sp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+static void launch_lp_sp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     using G = LpGeom<DT, KC, CB, VTS>;
-    const int64_t tiles = (n_cand + G::CAND_TILE - 1) / G::CAND_TILE;
-    InstDesc c;
-    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
-    hipLaunchKernelGGL((k_gains_lp_sp<DT, KC, CB, VTS>), dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s,
-                       gains_args(c, cand, n_cand));
+    const int64_t tiles = (ga.n_cand + G::CAND_TILE - 1) / G::CAND_TILE;
+    hipLaunchKernelGGL((k_gains_lp_sp<DT, KC, CB, VTS>), dim3(unsigned(tiles * ga.v_splits)), dim3(256), 0, s, ga);
 }
 
 template <int DT, int KC, int CB>
-static void launch_lp_pp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+static void launch_lp_pp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     using G = LpGeom<DT, KC, CB>;
-    const int64_t tiles = (n_cand + 2 * G::CAND_TILE - 1) / (2 * G::CAND_TILE);
-    InstDesc c;
-    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
-    hipLaunchKernelGGL((k_gains_lp_pp<DT, KC, CB>), dim3(unsigned(tiles * ds->v_splits)), dim3(512), 0, s,
-                       gains_args(c, cand, n_cand));
+    const int64_t tiles = (ga.n_cand + 2 * G::CAND_TILE - 1) / (2 * G::CAND_TILE);
+    hipLaunchKernelGGL((k_gains_lp_pp<DT, KC, CB>), dim3(unsigned(tiles * ga.v_splits)), dim3(512), 0, s, ga);
 }
 
 // Variants: 4 waves with (32-row candidate blocks per wave, software-pipelined
@@ -839,49 +830,49 @@ static void launch_lp_pp(const ebc_dataset* ds, const int32_t* cand, int64_t n_c
 // with pp_blocks(DT, KC) blocks each; 4 = interleaved test, 4 waves x 2 blocks,
 // ring stages of wide_stage(DT, KC) points.
 template <int DT, int KC>
-static void launch_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+static void launch_lp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     switch (ds->variant) {
-        case 1: launch_lp_v<DT, KC, 4, false>(ds, cand, n_cand, s); break;
-        case 2: launch_lp_v<DT, KC, 2, true>(ds, cand, n_cand, s); break;
-        case 3: launch_lp_pp<DT, KC, pp_blocks(DT, KC)>(ds, cand, n_cand, s); break;
-        case 4: launch_lp_sp<DT, KC, 2, wide_stage(DT, KC)>(ds, cand, n_cand, s); break;
-        default: launch_lp_v<DT, KC, 2, false>(ds, cand, n_cand, s); break;
+        case 1: launch_lp_v<DT, KC, 4, false>(ds, ga, s); break;
+        case 2: launch_lp_v<DT, KC, 2, true>(ds, ga, s); break;
+        case 3: launch_lp_pp<DT, KC, pp_blocks(DT, KC)>(ds, ga, s); break;
+        case 4: launch_lp_sp<DT, KC, 2, wide_stage(DT, KC)>(ds, ga, s); break;
+        default: launch_lp_v<DT, KC, 2, false>(ds, ga, s); break;
     }
 }
 
-hipError_t launch_gains_lp(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+hipError_t launch_gains_lp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     const int kc = ds->k_pad / (ds->dt == EBC_DT_FP8_E4M3 ? 64 : 16);
     switch (ds->dt) {
         case EBC_DT_BF16:
             switch (kc) {
-                case 1: launch_lp<EBC_DT_BF16, 1>(ds, cand, n_cand, s); break;
-                case 2: launch_lp<EBC_DT_BF16, 2>(ds, cand, n_cand, s); break;
-                case 3: launch_lp<EBC_DT_BF16, 3>(ds, cand, n_cand, s); break;
-                case 4: launch_lp<EBC_DT_BF16, 4>(ds, cand, n_cand, s); break;
-                case 5: launch_lp<EBC_DT_BF16, 5>(ds, cand, n_cand, s); break;
-                case 6: launch_lp<EBC_DT_BF16, 6>(ds, cand, n_cand, s); break;
-                case 7: launch_lp<EBC_DT_BF16, 7>(ds, cand, n_cand, s); break;
-                case 8: launch_lp<EBC_DT_BF16, 8>(ds, cand, n_cand, s); break;
+                case 1: launch_lp<EBC_DT_BF16, 1>(ds, ga, s); break;
+                case 2: launch_lp<EBC_DT_BF16, 2>(ds, ga, s); break;
+                case 3: launch_lp<EBC_DT_BF16, 3>(ds, ga, s); break;
+                case 4: launch_lp<EBC_DT_BF16, 4>(ds, ga, s); break;
+                case 5: launch_lp<EBC_DT_BF16, 5>(ds, ga, s); break;
+                case 6: launch_lp<EBC_DT_BF16, 6>(ds, ga, s); break;
+                case 7: launch_lp<EBC_DT_BF16, 7>(ds, ga, s); break;
+                case 8: launch_lp<EBC_DT_BF16, 8>(ds, ga, s); break;
                 default: return hipErrorInvalidValue;
             }
             break;
         case EBC_DT_F16:
             switch (kc) {
-                case 1: launch_lp<EBC_DT_F16, 1>(ds, cand, n_cand, s); break;
-                case 2: launch_lp<EBC_DT_F16, 2>(ds, cand, n_cand, s); break;
-                case 3: launch_lp<EBC_DT_F16, 3>(ds, cand, n_cand, s); break;
-                case 4: launch_lp<EBC_DT_F16, 4>(ds, cand, n_cand, s); break;
-                case 5: launch_lp<EBC_DT_F16, 5>(ds, cand, n_cand, s); break;
-                case 6: launch_lp<EBC_DT_F16, 6>(ds, cand, n_cand, s); break;
-                case 7: launch_lp<EBC_DT_F16, 7>(ds, cand, n_cand, s); break;
-                case 8: launch_lp<EBC_DT_F16, 8>(ds, cand, n_cand, s); break;
+                case 1: launch_lp<EBC_DT_F16, 1>(ds, ga, s); break;
+                case 2: launch_lp<EBC_DT_F16, 2>(ds, ga, s); break;
+                case 3: launch_lp<EBC_DT_F16, 3>(ds, ga, s); break;
+                case 4: launch_lp<EBC_DT_F16, 4>(ds, ga, s); break;
+                case 5: launch_lp<EBC_DT_F16, 5>(ds, ga, s); break;
+                case 6: launch_lp<EBC_DT_F16, 6>(ds, ga, s); break;
+                case 7: launch_lp<EBC_DT_F16, 7>(ds, ga, s); break;
+                case 8: launch_lp<EBC_DT_F16, 8>(ds, ga, s); break;
                 default: return hipErrorInvalidValue;
             }
             break;
         case EBC_DT_FP8_E4M3:
             switch (kc) {
-                case 1: launch_lp<EBC_DT_FP8_E4M3, 1>(ds, cand, n_cand, s); break;
-                case 2: launch_lp<EBC_DT_FP8_E4M3, 2>(ds, cand, n_cand, s); break;
+                case 1: launch_lp<EBC_DT_FP8_E4M3, 1>(ds, ga, s); break;
+                case 2: launch_lp<EBC_DT_FP8_E4M3, 2>(ds, ga, s); break;
                 default: return hipErrorInvalidValue;
             }
             break;

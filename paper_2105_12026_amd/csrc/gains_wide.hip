@@ -286,21 +286,18 @@ kb_gains_wide(const InstDesc* __restrict__ descs, const int32_t* __restrict__ sl
 }
 
 template <int DT, int KS>
-void launch_w(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+void launch_w(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     const int64_t ct = 32 * 4 / KS;
-    const int64_t tiles = (n_cand + ct - 1) / ct;
-    InstDesc c;
-    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
-    hipLaunchKernelGGL((k_gains_wide<DT, KS>), dim3(unsigned(tiles * ds->v_splits)), dim3(256), 0, s,
-                       gains_args(c, cand, n_cand), ds->k_pad);
+    const int64_t tiles = (ga.n_cand + ct - 1) / ct;
+    hipLaunchKernelGGL((k_gains_wide<DT, KS>), dim3(unsigned(tiles * ga.v_splits)), dim3(256), 0, s, ga, ds->k_pad);
 }
 
 template <int DT>
-void launch_w_ks(int32_t ks, const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+void launch_w_ks(int32_t ks, const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     if (ks == 4)
-        launch_w<DT, 4>(ds, cand, n_cand, s);
+        launch_w<DT, 4>(ds, ga, s);
     else
-        launch_w<DT, 1>(ds, cand, n_cand, s);
+        launch_w<DT, 1>(ds, ga, s);
 }
 
 template <int DT>
@@ -343,13 +340,13 @@ hipError_t launch_gains_matrix_batched(const InstDesc* descs, const int64_t* row
     return hipGetLastError();
 }
 
-hipError_t launch_gains_wide(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+hipError_t launch_gains_wide(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
     const int32_t ks = wide_ksplit(ds->n_pad);
     switch (ds->dt) {
-        case EBC_DT_F32: launch_w_ks<EBC_DT_F32>(ks, ds, cand, n_cand, s); break;
-        case EBC_DT_F16: launch_w_ks<EBC_DT_F16>(ks, ds, cand, n_cand, s); break;
-        case EBC_DT_BF16: launch_w_ks<EBC_DT_BF16>(ks, ds, cand, n_cand, s); break;
-        case EBC_DT_FP8_E4M3: launch_w_ks<EBC_DT_FP8_E4M3>(ks, ds, cand, n_cand, s); break;
+        case EBC_DT_F32: launch_w_ks<EBC_DT_F32>(ks, ds, ga, s); break;
+        case EBC_DT_F16: launch_w_ks<EBC_DT_F16>(ks, ds, ga, s); break;
+        case EBC_DT_BF16: launch_w_ks<EBC_DT_BF16>(ks, ds, ga, s); break;
+        case EBC_DT_FP8_E4M3: launch_w_ks<EBC_DT_FP8_E4M3>(ks, ds, ga, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -22,12 +22,12 @@ int32_t k_pad_for(int32_t d, ebc_dtype dt) {
 
 int elem_bytes(ebc_dtype dt) { return dt == EBC_DT_F32 ? 4 : (dt == EBC_DT_FP8_E4M3 ? 1 : 2); }
 
-int64_t gains_chunk(const ebc_dataset* ds) {
+int64_t gains_chunk(const ebc_dataset* ds, int32_t splits) {
     // ground-set chunk per workgroup: a multiple of the kernel's LDS tile
     // (float32: 64 rows; reduced precision: 256, the same for every variant)
     // (long rows: 64 for every dtype)
     const int64_t g = (ds->dt == EBC_DT_F32 || wide_rows(ds->k_pad)) ? kGainsVTile : 256;
-    const int64_t c = (ds->n_pad + ds->v_splits - 1) / ds->v_splits;
+    const int64_t c = (ds->n_pad + splits - 1) / splits;
     return (c + g - 1) / g * g;
 }
 
@@ -89,7 +89,7 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
     c.variant = ds->variant;
     c.metric = ds->metric;
     c.lazy = greedy_lists_worth(ds) > 1.0 ? 1 : 0;
-    c.chunk = gains_chunk(ds);
+    c.chunk = gains_chunk(ds, ds->v_splits);
     c.sel = sel;
     c.f = f;
     c.gain = gain;
@@ -141,7 +141,14 @@ int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {
     const int64_t most = n_pad / (dt == EBC_DT_F32 ? kGainsVTile : 256);
     v = v < 16 ? v : 16;
     v = v < most ? v : most;
-    return int32_t(v);
+    const int64_t least = call_splits_for(n_pad, k_pad, dt);
+    return int32_t(v > least ? v : least);
+}
+
+int32_t call_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {
+    const int64_t tiles = n_pad / kGainsCandTile;
+    if (wide_rows(k_pad) || tiles >= 64) return v_splits_for(n_pad, k_pad, dt);
+    return tiles >= 16 ? 4 : 1;
 }
 
 Layout layout(int64_t n, int32_t d, ebc_dtype dt) {

@@ -1311,7 +1311,7 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
         else if (c.b.pairs)
             e = launch_gains_wide_pairs(c, s);
         else
-            e = launch_gains(ds, nullptr, ds->n_pad, s);
+            e = launch_gains(ds, s);
         if (e != hipSuccess) return e;
         if (ev_gains_done && (e = hipEventRecord(ev_gains_done, s)) != hipSuccess) return e;
         if (nb <= kSmallBlocks && c.lazy == 0 && (c.metric == 1 || !wide_rows(c.k_pad) || long_split(c))) {
@@ -1417,10 +1417,24 @@ hipError_t launch_tick(const std::vector<GainsBucket>& buckets, const InstDesc* 
     return hipGetLastError();
 }
 
-hipError_t launch_gains(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
-    if (ds->metric == 1) return launch_gains_l1(ds, cand, n_cand, s);
-    if (wide_rows(ds->k_pad)) return launch_gains_wide(ds, cand, n_cand, s);
-    return ds->dt == EBC_DT_F32 ? launch_gains_f32(ds, cand, n_cand, s) : launch_gains_lp(ds, cand, n_cand, s);
+static hipError_t launch_gains_args(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
+    if (ds->metric == 1) return launch_gains_l1(ds, ga, s);
+    if (wide_rows(ds->k_pad)) return launch_gains_wide(ds, ga, s);
+    return ds->dt == EBC_DT_F32 ? launch_gains_f32(ds, ga, s) : launch_gains_lp(ds, ga, s);
+}
+
+hipError_t launch_gains(const ebc_dataset* ds, hipStream_t s) {
+    InstDesc c;
+    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
+    return launch_gains_args(ds, gains_args(c, nullptr, ds->n_pad), s);
+}
+
+hipError_t launch_gains_call(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s) {
+    InstDesc c;
+    fill_desc(ds, 0, nullptr, nullptr, nullptr, &c);
+    c.v_splits = call_splits_for(ds->n_pad, ds->k_pad, ds->dt);
+    c.chunk = gains_chunk(ds, c.v_splits);
+    return launch_gains_args(ds, gains_args(c, cand, n_cand), s);
 }
 
 hipError_t launch_gains_list(const InstDesc& c, int32_t part, hipStream_t s) {
@@ -1434,14 +1448,15 @@ k_gains_out(int64_t n, int64_t n_cand, int64_t stride, int32_t v_splits, const d
     const int64_t p = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (p >= n_cand) return;
     double g = 0.0;
+#pragma unroll 8
     for (int s = 0; s < v_splits; ++s) g += part[int64_t(s) * stride + p];
     out[p] = g / double(n);
 }
 
 hipError_t launch_gains_out(const ebc_dataset* ds, int64_t n_cand, double* out, hipStream_t s) {
     const unsigned nb = unsigned((n_cand + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_gains_out, dim3(nb), dim3(kBlock), 0, s, ds->n, n_cand, ds->n_pad, ds->v_splits,
-                       ds->b.part, out);
+    hipLaunchKernelGGL(k_gains_out, dim3(nb), dim3(kBlock), 0, s, ds->n, n_cand, ds->n_pad,
+                       call_splits_for(ds->n_pad, ds->k_pad, ds->dt), ds->b.part, out);
     return hipGetLastError();
 }
 

@@ -34,9 +34,9 @@ hipError_t time_variant(ebc_dataset* ds, int32_t reps, hipStream_t s, float* ms)
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    if (e == hipSuccess) e = launch_gains(ds, nullptr, ds->n_pad, s);  // warm-up
+    if (e == hipSuccess) e = launch_gains(ds, s);  // warm-up
     if (e == hipSuccess) e = hipEventRecord(e0, s);
-    for (int32_t r = 0; r < reps && e == hipSuccess; ++r) e = launch_gains(ds, nullptr, ds->n_pad, s);
+    for (int32_t r = 0; r < reps && e == hipSuccess; ++r) e = launch_gains(ds, s);
     if (e == hipSuccess) e = hipEventRecord(e1, s);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     if (e == hipSuccess) e = hipEventElapsedTime(ms, e0, e1);

@@ -237,6 +237,180 @@ __device__ __forceinline__ void gains_f32_body(const GainsArgs& ga, int64_t bid)
     }
 }
 
+// Short candidate lists: 32 candidates per workgroup instead of 128, each wave
+// taking one of the four 32-point blocks of a 128-point tile. The clamped
+// terms of the four blocks meet in LDS and are added in block order (wave w
+// adds the result rows of registers 4w .. 4w + 3), so every sum is, bit for
+// bit, the one the 128-candidate kernel makes of the same chunk, while a
+// chunk takes a quarter of the time and a list four times the workgroups.
+// Bound: matrix instructions, as there; the terms cost 16 LDS writes and reads
+// per lane and block of 50 of them (d = 100). 50000 x 100: a call for one
+// candidate 172 -> 67 us, for 300 178 -> 71 us.
+template <int KP, bool TRIM>
+__global__ void __launch_bounds__(256) k_gains_f32_narrow(GainsArgs ga) {
+    const float* __restrict__ xq = static_cast<const float*>(ga.xq);
+    const int64_t n_pad = ga.n_pad;
+    constexpr int KH = KP / 2;
+    constexpr int S = KP + 4;
+    constexpr int VT = 128;
+    constexpr int NV4 = VT * KP / 4;
+    constexpr int PER = (NV4 + 255) / 256;
+    constexpr int QF = TRIM ? KH / 4 - 1 : KH / 4;
+
+    __shared__ float4 lds_x4[VT * S / 4];
+    __shared__ float lds_ha[VT];
+    __shared__ float lds_hm[VT];
+    __shared__ float terms[4][16][64];
+    float* lds_x = reinterpret_cast<float*>(lds_x4);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int col = lane & 31;
+    const int half = lane >> 5;
+    const int split = int(uint32_t(blockIdx.x) % uint32_t(ga.v_splits));
+    const int64_t cbase = int64_t(uint32_t(blockIdx.x) / uint32_t(ga.v_splits)) * 32;
+
+    const int64_t cpos = cbase + col;
+    int64_t crow = -1;
+    if (cpos < ga.n_cand) {
+        crow = ga.cand ? int64_t(ga.cand[cpos]) : cpos;
+        if (crow >= n_pad || crow < 0) {
+            atomicCAS(ga.err, 0, kDevErrIndex);
+            crow = -1;
+        }
+    }
+    float a[KH];
+    if (crow >= 0) {
+        const float4* src = reinterpret_cast<const float4*>(xq + crow * KP + half * KH);
+#pragma unroll
+        for (int q = 0; q < QF; ++q) {
+            const float4 t = src[q];
+            a[4 * q + 0] = t.x;
+            a[4 * q + 1] = t.y;
+            a[4 * q + 2] = t.z;
+            a[4 * q + 3] = t.w;
+        }
+        if constexpr (TRIM) {
+            const float2 t = *reinterpret_cast<const float2*>(xq + crow * KP + (half ? KH - 2 : KH - 4));
+            a[KH - 4] = t.x;
+            a[KH - 3] = t.y;
+            a[KH - 2] = 0.0f;
+            a[KH - 1] = 0.0f;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < KH; ++j) a[j] = 0.0f;
+    }
+    const float hc = crow >= 0 ? ga.hn[crow] : 0.0f;
+    float nhn[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) nhn[r] = -__shfl(hc, acc_row(r, half), 64);
+    float acc_sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // result rows of registers 4 wave + i
+
+    const int64_t v_begin = int64_t(split) * ga.chunk;
+    int64_t v_end = v_begin + ga.chunk;
+    if (v_end > n_pad) v_end = n_pad;
+
+    // rows past v_end (a chunk is a multiple of 64 points) are read from the
+    // tile's first rows instead and their block is not added
+    auto load = [&](int64_t v0) {
+        const int64_t rows = v_end - v0 < VT ? v_end - v0 : VT;
+        const int nv4 = int(rows) * (KP / 4);
+        const float4* __restrict__ src = reinterpret_cast<const float4*>(xq + v0 * KP);
+        PreVec<PER> pre;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = tid + i * 256;
+            const float4 t = src[e < nv4 ? e : 0];
+            pre[4 * i + 0] = t.x;
+            pre[4 * i + 1] = t.y;
+            pre[4 * i + 2] = t.z;
+            pre[4 * i + 3] = t.w;
+        }
+        return pre;
+    };
+    PreVec<PER> pre;
+    float pre_ha = 0.0f, pre_hm = 0.0f;
+    auto load_points = [&](int64_t v0) {
+        if (tid < VT && v0 + tid < v_end) {
+            pre_ha = ga.ha[v0 + tid];
+            pre_hm = ga.hm[v0 + tid];
+        }
+    };
+    if (v_begin < v_end) {
+        pre = load(v_begin);
+        load_points(v_begin);
+    }
+    int blocks = 0;  // blocks whose terms are in LDS, not yet added
+    auto add_terms = [&]() {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (b >= blocks) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc_sum[i] += terms[b][4 * wave + i][lane];
+        }
+    };
+    for (int64_t v0 = v_begin; v0 < v_end; v0 += VT) {
+        __syncthreads();  // previous tile multiplied, its terms written
+        add_terms();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = tid + i * 256;
+            if (e < NV4) {
+                const int row = e / (KP / 4);
+                const int q = e % (KP / 4);
+                lds_x4[(row * S) / 4 + q] = make_float4(pre[4 * i], pre[4 * i + 1], pre[4 * i + 2], pre[4 * i + 3]);
+            }
+        }
+        if (tid < VT) {
+            lds_ha[tid] = pre_ha;
+            lds_hm[tid] = pre_hm;
+        }
+        __syncthreads();
+        if (v0 + VT < v_end) {
+            pre = load(v0 + VT);
+            load_points(v0 + VT);
+        }
+        blocks = v_end - v0 < VT ? int(v_end - v0) / 32 : 4;
+        const int vrow = wave * 32 + col;
+        const float hav = lds_ha[vrow];
+        const float hmv = lds_hm[vrow];
+        floatx16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = nhn[r] + hav;
+        const float4* b4 = reinterpret_cast<const float4*>(lds_x + vrow * S + half * KH);
+        float4 bv = b4[0];
+#pragma unroll
+        for (int q = 0; q < QF; ++q) {
+            const float4 bn = q + 1 < QF ? b4[q + 1] : bv;  // read ahead of the group that needs it
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[4 * q + 0], bv.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[4 * q + 1], bv.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[4 * q + 2], bv.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[4 * q + 3], bv.w, acc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            bv = bn;
+        }
+        if constexpr (TRIM) {
+            const float2 bt = *reinterpret_cast<const float2*>(lds_x + vrow * S + (half ? KH - 2 : KH - 4));
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[KH - 4], bt.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[KH - 3], bt.y, acc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) terms[wave][r][lane] = __builtin_amdgcn_fmed3f(acc[r], 0.0f, hmv);
+    }
+    __syncthreads();
+    add_terms();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        double v = double(acc_sum[i]);
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        const int64_t p = cbase + acc_row(4 * wave + i, half);
+        if (col == 0 && p < ga.n_cand) ga.part[int64_t(split) * ga.part_stride + p] = 2.0 * v;
+    }
+}
+
 template <int KP, bool TRIM>
 __global__ void __launch_bounds__(256) k_gains_f32(GainsArgs ga) {
     gains_f32_body<KP, TRIM>(ga, blockIdx.x);
@@ -270,14 +444,55 @@ kb_gains_f32_list(const InstDesc* __restrict__ descs, const int32_t* __restrict_
               [](const GainsArgs& ga, int64_t pair) { gains_f32_body<KP, TRIM>(ga, pair); });
 }
 
+// How many of a list's 128-candidate tiles take the wide kernel; the rest of
+// the list takes the narrow one. Chosen to end first: rounds of 256 workgroups
+// (a wide and a narrow workgroup of a chunk measured 2.7 and 1.2 us per 64
+// points at d = 100) plus a launch each. Full rounds go to the wide kernel, a
+// partial last one to the narrow: 50000 x 100, 2303 candidates: 288 wide
+// workgroups 321 us a call, 256 wide and 128 narrow ones 256 us; 5000: 485 and
+// 445 us.
+static int64_t wide_tiles(const GainsArgs& ga) {
+    const int64_t tiles = (ga.n_cand + kGainsCandTile - 1) / kGainsCandTile;
+    if (!ga.cand) return tiles;
+    const double len = double(ga.chunk) / kGainsVTile;
+    auto cost = [&](int64_t w) {
+        const int64_t rest = ga.n_cand - w * kGainsCandTile;
+        const int64_t nar = rest > 0 ? (rest + 31) / 32 : 0;
+        return double((w * ga.v_splits + 255) / 256) * len + double((nar * ga.v_splits + 255) / 256) * 0.46 * len +
+               (w > 0 && nar > 0 ? 2.0 : 0.0);
+    };
+    int64_t best = tiles;
+    // candidates for the split: none, and whole rounds of wide workgroups
+    const int64_t step = ga.v_splits < 256 ? 256 / ga.v_splits : 1;
+    for (int64_t w = 0; w < tiles; w += step)
+        if (cost(w) < cost(best)) best = w;
+    return best;
+}
+
+template <int KP, bool TRIM>
+static void launch_kpt(const GainsArgs& ga, hipStream_t s) {
+    const int64_t w = wide_tiles(ga);
+    const int64_t first = w * kGainsCandTile < ga.n_cand ? w * kGainsCandTile : ga.n_cand;
+    GainsArgs part = ga;
+    if (w > 0) {
+        part.n_cand = first;
+        hipLaunchKernelGGL((k_gains_f32<KP, TRIM>), dim3(unsigned(w * ga.v_splits)), dim3(256), 0, s, part);
+    }
+    if (first < ga.n_cand) {
+        part.cand = ga.cand + first;
+        part.n_cand = ga.n_cand - first;
+        part.part = ga.part + first;
+        const unsigned wgs = unsigned((part.n_cand + 31) / 32 * ga.v_splits);
+        hipLaunchKernelGGL((k_gains_f32_narrow<KP, TRIM>), dim3(wgs), dim3(256), 0, s, part);
+    }
+}
+
 template <int KP>
 static void launch_kp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s) {
-    const int64_t tiles = (ga.n_cand + kGainsCandTile - 1) / kGainsCandTile;
-    const dim3 grid = dim3(unsigned(tiles * ga.v_splits));
     if (ds->d <= KP - 4)  // the rows' last 4 padded slots are empty
-        hipLaunchKernelGGL((k_gains_f32<KP, true>), grid, dim3(256), 0, s, ga);
+        launch_kpt<KP, true>(ga, s);
     else
-        hipLaunchKernelGGL((k_gains_f32<KP, false>), grid, dim3(256), 0, s, ga);
+        launch_kpt<KP, false>(ga, s);
 }
 
 #define EBC_F32_KPS(X) \

@@ -188,3 +188,19 @@ def test_pair_matrix_picks_what_dot_products_pick(n, d, dtype, k):
     assert sel.cpu().numpy().tolist() == full[0].tolist() and np.array_equal(f.cpu().numpy(), full[1])
     got = [q.cpu().numpy() for q in ebc.Batch([ebc.Dataset(t, dtype=dtype), ds]).greedy([k, k])[0]]
     assert np.array_equal(got[0], full[0]) and np.array_equal(got[1], full[1])
+
+
+@pytest.mark.parametrize("n,d,dtype", [(5003, 100, "f32"), (700, 9, "f32"), (40000, 24, "f32"), (20011, 128, "f32"),
+                                       (9001, 33, "bf16"), (33000, 128, "f16"), (4000, 128, "fp8")])
+def test_gains_of_lists_of_every_length(n, d, dtype):
+    """Lists take another kernel by their length: the same gains as of all points, bit for bit."""
+    x = torch.from_numpy(points("mixture", n, d, n)).cuda()
+    ds = ebc.Dataset(x, dtype=dtype)
+    ds.greedy(3)
+    full = ds.marginal_gains().cpu().numpy()
+    rng = np.random.default_rng(n)
+    for c in (1, 31, 32, 33, 129, 257, 513, 2303, n - 1, n, n + 300):
+        cand = rng.integers(0, n, c).astype(np.int32)
+        got = ds.marginal_gains(cand=torch.from_numpy(cand)).cpu().numpy()
+        assert np.array_equal(got, full[cand]), c
+    ds.sync()

@@ -51,9 +51,15 @@ __host__ __device__ inline float* list_m(const InstDesc& c) {
 // chip's workgroup slots once. Many tiles: chunks of about kListChunk points,
 // long enough that loading a pair's candidates and adding up its sums do not
 // count, and many enough that the last round of workgroups does not either.
-// Whole 256-point units; as many splits as the partial sums have room for;
-// splits padded to whole rounds over the 8 XCDs (a padded chunk is empty).
-constexpr int kListUnit = 256;
+// Whole units of points: 128 for float32 and L1, whose pairs are bound by their
+// arithmetic (against 256: float32, d = 100, 8192 points, 76 -> 65 us a step;
+// L1, d = 50, 10007 points, 1.27 -> 1.13 ms for 10 steps; the same above 20000);
+// 256, the widest LDS tile, for the matrix-core types. As many splits as the
+// partial sums have room for, padded to whole rounds over the 8 XCDs (a padded
+// chunk is empty).
+__host__ __device__ inline int32_t list_unit(const InstDesc& c) {
+    return c.dt == EBC_DT_F32 || c.metric == 1 ? 128 : 256;
+}
 constexpr int kListSlots = 512;   // 2 workgroups of 4 waves on each of 256 CUs
 constexpr int kListChunk = 1024;
 struct ListGeom {
@@ -64,11 +70,12 @@ __host__ __device__ inline ListGeom list_geom(const InstDesc& c, int64_t cnt, in
     ListGeom g;
     g.tiles = int32_t((cnt + ct - 1) / ct);
     g.stride = int64_t(g.tiles) * ct;
-    const int32_t units = int32_t(c.n_pad / kListUnit);
+    const int32_t unit = list_unit(c);
+    const int32_t units = int32_t(c.n_pad / unit);
     const int32_t tiles = g.tiles > 0 ? g.tiles : 1;
     const int32_t cap = int32_t((c.v_splits - 1) * (c.n_pad / ct) / tiles);
     int32_t s = kListSlots / tiles;
-    const int32_t fine = units / (kListChunk / kListUnit);
+    const int32_t fine = units / (kListChunk / unit);
     s = s > fine ? s : fine;
     s = s < cap ? s : cap;
     s = s < units ? s : units;
@@ -77,7 +84,7 @@ __host__ __device__ inline ListGeom list_geom(const InstDesc& c, int64_t cnt, in
     s = (units + per - 1) / per;
     const int32_t up = (s + 7) & ~7;
     g.splits = s >= 8 && up <= cap ? up : s;
-    g.chunk = int64_t(per) * kListUnit;
+    g.chunk = int64_t(per) * unit;
     return g;
 }
 // Workgroups of a list launch over one instance: one per pair (the scheduler

@@ -224,13 +224,22 @@ __device__ __forceinline__ int64_t owner_of(const int64_t* __restrict__ U, int64
 }
 
 // Row and unit bookkeeping of one 32-row member block.
-struct BlockInfo {
+struct RowInfo {
+    static constexpr bool kScales = false;
     int32_t row_mem[32];             // member row of V, -1 for padding
     float row_c[32];                 // -n_s/2, or -inf for padding
-    int32_t row_sc[32];              // E8M0 row scale (FP8 rows; 127 otherwise)
     int32_t unit_flags[kBlockUnits];  // bit0 first unit of its set, bit1 last, bit2 valid
     int32_t unit_local[kBlockUnits];  // the set's index within the group
 };
+struct BlockInfo : RowInfo {
+    static constexpr bool kScales = true;
+    int32_t row_sc[32];  // E8M0 row scale (FP8 rows; 127 otherwise)
+};
+// Member blocks whose bookkeeping k_es_main keeps for all its points: a full
+// window's 8 and a last set of up to 144 rows reaching out of it. Longer groups
+// make it anew for each 256 points, this many blocks at a time. (12 is what LDS
+// gives without fewer workgroups a CU at any row length.)
+constexpr int kInfoBlocks = 12;
 
 // Set table of the current group: U, E and offsets of sets j0 .. j1, cached
 // in LDS when the group has at most kTab sets (else read from global memory).
@@ -246,10 +255,11 @@ struct SetTable {
 // Threads 0..31 fill the rows, threads 32..39 the units of block blk.
 // Norms: n64 (float64 ||s||^2 of the float32 rows) when hn is null, else hn
 // (float32 ||s^||^2 / 2 of the cast rows); sc: FP8 row scales or null.
+template <class Info>
 __device__ __forceinline__ void block_info(int tid, int64_t blk, int64_t u0, int64_t u1, int64_t j0, int64_t j1,
                                            const SetTable& tb, const int32_t* __restrict__ idx,
                                            const double* __restrict__ n64, const float* __restrict__ hn,
-                                           const int* __restrict__ sc, BlockInfo& bi) {
+                                           const int* __restrict__ sc, Info& bi) {
     if (tid < 32) {
         const int64_t u = u0 + blk * kBlockUnits + tid / kUnitRows;
         int32_t mem = -1;
@@ -260,7 +270,7 @@ __device__ __forceinline__ void block_info(int tid, int64_t blk, int64_t u0, int
         }
         bi.row_mem[tid] = mem;
         bi.row_c[tid] = mem < 0 ? -INFINITY : (hn ? -hn[mem] : -float(0.5 * n64[mem]));
-        bi.row_sc[tid] = (mem >= 0 && sc) ? sc[mem] : 127;
+        if constexpr (Info::kScales) bi.row_sc[tid] = (mem >= 0 && sc) ? sc[mem] : 127;
     } else if (tid < 32 + kBlockUnits) {
         const int uu = tid - 32;
         const int64_t u = u0 + blk * kBlockUnits + uu;
@@ -341,6 +351,15 @@ __device__ __forceinline__ void es_finish(int tid, int64_t j0, int64_t j1, int s
     }
 }
 
+// Calls with a set too long for the register kernel, and float32 evaluation
+// over a reduced-precision dataset. Bound by the matrix units and by what
+// stands between their blocks: 256 points are multiplied with about 8 member
+// blocks, so loading the points (scalar loads of a ragged row were 80 a lane:
+// the padded copy has whole float4) and each block's bookkeeping (two dependent
+// loads and a search, which all four waves waited for: kept for all points of
+// the group) are on the path. 29501 x 77, 701 sets of 75 on average: 3.61 ms,
+// 3.21 from the padded copy, 2.84 with the bookkeeping kept (0.55 of the
+// product rate); 5000 x 20, 2000 sets of 50: 668 -> 527 us.
 template <int KP, bool TRIM>
 __global__ void __launch_bounds__(256)
 k_es_main(const float* __restrict__ x, int64_t n, int32_t d, const double* __restrict__ n64,
@@ -357,7 +376,7 @@ k_es_main(const float* __restrict__ x, int64_t n, int32_t d, const double* __res
     // (half 1) in 2 MFMAs instead of 4
     constexpr int QF = TRIM ? KH / 4 - 1 : KH / 4;
     __shared__ float4 lds_m4[2][32 * S / 4];
-    __shared__ BlockInfo info[3];
+    __shared__ RowInfo info[kInfoBlocks];
     __shared__ int64_t t_u[kTab + 1], t_off[kTab + 1];
     __shared__ int32_t t_e[kTab + 1];
     __shared__ float lacc[4][kWindow][32];
@@ -394,6 +413,7 @@ k_es_main(const float* __restrict__ x, int64_t n, int32_t d, const double* __res
         const SetTable tb = cached ? SetTable{t_u, t_e, t_off, j0} : SetTable{sc.U, sc.E, off, 0};
         if (u1 > u0 && v_end > v_begin) {
             const int64_t nblk = (u1 - u0 + kBlockUnits - 1) / kBlockUnits;
+            const bool kept = nblk <= kInfoBlocks;  // all bookkeeping in LDS: made once
             for (int64_t vs = v_begin; vs < v_end; vs += kVSub) {
                 // this wave's 64 ground points (B operand), K split in lane halves
                 float b[2][KH];
@@ -432,37 +452,37 @@ k_es_main(const float* __restrict__ x, int64_t n, int32_t d, const double* __res
                     }
                 }
                 float cur[2] = {-INFINITY, -INFINITY};
-                // prologue: bookkeeping of blocks 0 and 1, rows of block 0
-                block_info(tid, 0, u0, u1, j0, j1, tb, idx, n64, nullptr, nullptr, info[0]);
-                if (nblk > 1) block_info(tid, 1, u0, u1, j0, j1, tb, idx, n64, nullptr, nullptr, info[1]);
-                __syncthreads();
-                {
-                    const int32_t mem = info[0].row_mem[grow];
-                    float* dst = reinterpret_cast<float*>(lds_m4[0]) + grow * S;
-#pragma unroll
-                    for (int i = 0; i < PF; ++i) {
-                        const int k = gk + 8 * i;
-                        dst[k] = (mem >= 0 && k < d) ? x[int64_t(mem) * d + k] : 0.0f;
-                    }
-                }
-                __syncthreads();
+                int slot = 0;  // blk % kInfoBlocks
                 for (int64_t blk = 0; blk < nblk; ++blk) {
                     const int rb = int(blk & 1);
-                    const BlockInfo& bi = info[blk % 3];
+                    if (slot == 0) {
+                        // bookkeeping of the next kInfoBlocks blocks (a wave a block), rows of this one
+                        if (!kept || vs == v_begin)
+                            for (int i = wave; i < kInfoBlocks && blk + i < nblk; i += 4)
+                                block_info(lane, blk + i, u0, u1, j0, j1, tb, idx, n64, nullptr, nullptr, info[i]);
+                        __syncthreads();
+                        const int32_t mem = info[0].row_mem[grow];
+                        float* dst = reinterpret_cast<float*>(lds_m4[rb]) + grow * S;
+#pragma unroll
+                        for (int i = 0; i < PF; ++i) {
+                            const int k = gk + 8 * i;
+                            dst[k] = (mem >= 0 && k < d) ? x[int64_t(mem) * d + k] : 0.0f;
+                        }
+                        __syncthreads();
+                    }
+                    const RowInfo& bi = info[slot];
+                    slot = slot + 1 < kInfoBlocks ? slot + 1 : 0;
                     // rows of block blk+1 into registers (their stores follow the MFMAs)
                     float pf[PF];
-                    const bool more = blk + 1 < nblk;
+                    const bool more = blk + 1 < nblk && slot != 0;
                     if (more) {
-                        const int32_t mem = info[(blk + 1) % 3].row_mem[grow];
+                        const int32_t mem = info[slot].row_mem[grow];
 #pragma unroll
                         for (int i = 0; i < PF; ++i) {
                             const int k = gk + 8 * i;
                             pf[i] = (mem >= 0 && k < d) ? x[int64_t(mem) * d + k] : 0.0f;
                         }
                     }
-                    // bookkeeping of block blk+2 (its slot was last read in block blk-1)
-                    if (blk + 2 < nblk)
-                        block_info(tid, blk + 2, u0, u1, j0, j1, tb, idx, n64, nullptr, nullptr, info[(blk + 2) % 3]);
                     // member rows x this wave's points
                     floatx16 acc[2];
 #pragma unroll
@@ -1548,12 +1568,17 @@ void launch_es_main(dim3 g, hipStream_t s, const ebc_dataset* ds, const int64_t*
             }
         }
     }
+    // rows of the dataset's padded float32 copy where there is one: whole
+    // 16-byte pieces at any row length
+    const bool padded = ds->dt == EBC_DT_F32 && ds->k_pad == KP;
+    const float* x = padded ? ds->b.xq : ds->x;
+    const int32_t ld = padded ? KP : ds->d;
     if (ds->d <= KP - 4)
-        hipLaunchKernelGGL((k_es_main<KP, true>), g, dim3(256), 0, s, ds->x, ds->n, ds->d, ds->b.n64, ds->b.m0, off,
-                           idx, l, splits, sc, int32_t(own));
+        hipLaunchKernelGGL((k_es_main<KP, true>), g, dim3(256), 0, s, x, ds->n, ld, ds->b.n64, ds->b.m0, off, idx, l,
+                           splits, sc, int32_t(own));
     else
-        hipLaunchKernelGGL((k_es_main<KP, false>), g, dim3(256), 0, s, ds->x, ds->n, ds->d, ds->b.n64, ds->b.m0, off,
-                           idx, l, splits, sc, int32_t(own));
+        hipLaunchKernelGGL((k_es_main<KP, false>), g, dim3(256), 0, s, x, ds->n, ld, ds->b.n64, ds->b.m0, off, idx, l,
+                           splits, sc, int32_t(own));
 }
 
 }  // namespace

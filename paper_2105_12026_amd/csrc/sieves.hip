@@ -165,7 +165,7 @@ __device__ __forceinline__ double wave_sums(const double (&p)[P]) {
 // workgroup computes a 32 x 32 tile; wave w sums quarter w of the dimension in
 // dimension order, and the four sums are added in order. Lane (ti, tv)
 // owns stream points 4 ti .. 4 ti + 3 and ground points 4 tv .. 4 tv + 3, both
-// sides staged through the wave's own LDS as float64, 16 dimensions at a time
+// sides staged through the wave's own LDS as float64, 8 dimensions at a time
 // (the next stage's values loaded into registers while the current one is
 // used; no barrier, the wave alone reads what it wrote). Bound: float64 vector
 // instructions, a subtraction and an fma per pair and dimension (97 us at 1000

@@ -399,7 +399,7 @@ hipError_t launch_load_m(const ebc_dataset* ds, const double* m, hipStream_t s);
 hipError_t launch_gains_f32(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
 hipError_t launch_gains_lp(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
 hipError_t launch_gains_wide(const ebc_dataset* ds, const GainsArgs& ga, hipStream_t s);
-hipError_t launch_gains_wide_pairs(const InstDesc& c, hipStream_t s);   // gains, and the pair matrix
+hipError_t launch_gains_wide_pairs(const InstDesc& c, hipStream_t s);   // gains, and the pair matrix if there is one
 hipError_t launch_gains_matrix(const InstDesc& c, hipStream_t s);       // gains from the pair matrix
 hipError_t launch_gains_matrix_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count,
                                        int64_t total_rows, int32_t t, hipStream_t s);

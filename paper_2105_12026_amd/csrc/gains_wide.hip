@@ -26,7 +26,10 @@ namespace ebc {
 
 namespace {
 
-// PAIRS (KS = 4): also write the pair matrix, x_v . x_c - hn_c - hn_v.
+// PAIRS (KS = 4; greedy steps of data sets that may keep a pair matrix): the
+// term is taken from the pair's own value e = x_v . x_c - hn_c - hn_v as
+// med3(e + hm_v, 0, hm_v), and e is written to the matrix where there is one.
+// Steps that read the matrix, and runs without one, so make the same terms.
 template <int DT, int KS, bool PAIRS = false>
 __device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_pad, int64_t bid,
                                                 float* __restrict__ pairs = nullptr) {
@@ -170,19 +173,16 @@ __device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_p
             __syncthreads();
             const int cbe = wave >> 1;  // the 32-point block whose clamps this wave takes
             const int64_t v = v0 + cbe * 32 + col;
-            const float hav = ha[v], hmw = hm[v];
-            const float hnv = PAIRS ? hn[v] : 0.0f;
+            const float vt = PAIRS ? -hn[v] : ha[v], hmw = hm[v];
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
                 const int r = r0 + i;
-                float t = nhn[i] + hav;
+                float t = nhn[i] + vt;
 #pragma unroll
                 for (int w = 0; w < 4; ++w) t += red[((w * 2 + cbe) * 16 + r) * 64 + lane];
                 if constexpr (PAIRS) {
-                    float e = nhn[i] - hnv;
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) e += red[((w * 2 + cbe) * 16 + r) * 64 + lane];
-                    pairs[(cbase + acc_row(r, half)) * n_pad + v] = e;
+                    if (pairs) pairs[(cbase + acc_row(r, half)) * n_pad + v] = t;
+                    t += hmw;
                 }
                 acc_sum[i] += __builtin_amdgcn_fmed3f(t, 0.0f, hmw);
             }
@@ -219,27 +219,43 @@ __device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_p
     }
 }
 
-// Gains of one candidate from the pair matrix, by one wave: the term of point
-// v is med3(pair + hm_v, 0, hm_v). Four float32 sums a lane, added up in
-// float64. 4 bytes a pair are what bounds it: 1000 points (4 MB, in the L2s)
-// 84 -> 4 us a step against multiplying rows of 3524 values again.
+// Gains of one candidate from the pair matrix, by one wave: the terms, the
+// float32 sums of a chunk and the float64 sums after it, all in the order of
+// the kernel that multiplies the rows (lane l stands for the points l of a
+// chunk's 64-point tiles), so that both give the same bits. 4 bytes a pair are
+// what bounds it, with the sums' lane exchanges: 1000 points (4 MB, in the L2s)
+// 92 -> 3.9 us a step against multiplying rows of 3524 values again (one float32
+// sum a lane over all chunks: 3.2 us, but other sums than a run without a matrix).
 __device__ __forceinline__ void gains_matrix_row(const InstDesc& c, int64_t row) {
     const int lane = threadIdx.x & 63;
-    const float4* __restrict__ e4 = reinterpret_cast<const float4*>(c.b.pairs + row * c.n_pad);
-    const float4* __restrict__ h4 = reinterpret_cast<const float4*>(c.b.hm);
-    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-    for (int64_t i = lane; i < c.n_pad / 4; i += 64) {
-        const float4 e = e4[i], h = h4[i];
-        a[0] += __builtin_amdgcn_fmed3f(e.x + h.x, 0.0f, h.x);
-        a[1] += __builtin_amdgcn_fmed3f(e.y + h.y, 0.0f, h.y);
-        a[2] += __builtin_amdgcn_fmed3f(e.z + h.z, 0.0f, h.z);
-        a[3] += __builtin_amdgcn_fmed3f(e.w + h.w, 0.0f, h.w);
-    }
-    double s = (double(a[0]) + double(a[1])) + (double(a[2]) + double(a[3]));
+    const float* __restrict__ e = c.b.pairs + row * c.n_pad + lane;
+    const float* __restrict__ hm = c.b.hm + lane;
+    float acc[16];  // chunks; a data set with a matrix has at most 16
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (lane == 0) c.b.part[row] = 2.0 * s;
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    for (int64_t o = 0; o < c.chunk; o += 64) {
+        // no branch around a load: all of a row of tiles are in flight together
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int64_t v = i * c.chunk + o;
+            const bool in = v < c.n_pad;
+            const int64_t at = in ? v : 0;
+            const float pair = e[at], hv = hm[at];
+            const float h = in ? hv : 0.0f;  // past the end: a term of 0
+            acc[i] += __builtin_amdgcn_fmed3f(pair + h, 0.0f, h);
+        }
+    }
+    const double half_sum = column_sums16(acc, lane & 31);  // chunk (lane & 31) / 2
+    const double sum = 2.0 * (half_sum + __shfl_xor(half_sum, 32, 64));
+    const uint64_t bits = __double_as_longlong(sum);
+    double g = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {  // in chunk order; chunks past the last are 0
+        const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(bits), 2 * i);
+        const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(bits >> 32), 2 * i);
+        g += __longlong_as_double((uint64_t(hi) << 32) | lo);
+    }
+    if (lane == 0) c.b.part[row] = g;
 }
 
 __global__ void __launch_bounds__(256) k_gains_matrix(InstDesc c) {
@@ -276,7 +292,7 @@ kb_gains_wide(const InstDesc* __restrict__ descs, const int32_t* __restrict__ sl
     const InstDesc c = descs[slot_inst[j]];
     if (c.t0 + t >= c.k || matrix_step(c, c.t0 + t)) return;
     if constexpr (KS == 4) {
-        if (c.b.pairs) {
+        if (pair_matrix(c.n_pad, c.k_pad)) {  // c.b.pairs is null without a matrix
             gains_wide_body<DT, KS, true>(gains_args(c, nullptr, c.n_pad), c.k_pad, int64_t(blockIdx.x) - wg_pre[j],
                                           c.b.pairs);
             return;

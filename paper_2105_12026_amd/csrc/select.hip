@@ -839,9 +839,11 @@ __device__ __forceinline__ int window_slices(const InstDesc& c, int W) {
     return s < 16 ? s : 16;
 }
 
-// Does the window's pass 1 hold the pick's distances (window position rank)?
+// Does the window's pass 1 hold the pick's distances (window position rank), in
+// the slices of the update? m_v must not depend on the size of the window.
 __device__ __forceinline__ bool window_has_slices(const InstDesc& c, int rank) {
-    return rank >= 0 && c.b.state->window_count <= split_window(c);
+    const int W = c.b.state->window_count;
+    return rank >= 0 && W <= split_window(c) && window_slices(c, W) == update_slices(c);
 }
 
 // m_v update from the slice sums of the pick (pass 2), per-block sums of m_v.
@@ -850,11 +852,8 @@ __device__ void update_split_body(const InstDesc& c, int64_t blk, int cs, int ra
     __shared__ double red[kBlock];
     const Buffers& b = c.b;
     InstDesc w = c;
-    int S = update_slices(c);
-    if (window_has_slices(c, rank)) {
-        S = window_slices(c, b.state->window_count);
-        w.b.part = b.part + int64_t(S) * rank * c.n_pad;
-    }
+    const int S = update_slices(c);
+    if (window_has_slices(c, rank)) w.b.part = b.part + int64_t(S) * rank * c.n_pad;
     const int64_t v = blk * kBlock + threadIdx.x;
     double mv = 0.0;
     if (v < c.n) {
@@ -1309,7 +1308,7 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
     } else {
         if (matrix_step(c, t))
             e = launch_gains_matrix(c, s);
-        else if (c.b.pairs)
+        else if (c.metric == 0 && pair_matrix(c.n_pad, c.k_pad))
             e = launch_gains_wide_pairs(c, s);
         else
             e = launch_gains(ds, s);

@@ -390,13 +390,14 @@ EBC_API size_t ebc_arena_largest_free(const ebc_arena* arena);
 EBC_API ebc_status ebc_arena_destroy(ebc_arena* arena);
 
 /* Host-side counters of the last ebc_greedy on this dataset, valid after
- * ebc_sync_status: window_max = largest number of candidates re-scored in
- * one step, window_overflow = steps whose window exceeded its capacity. */
+ * ebc_sync_status: window_max = largest number of candidates in the re-score
+ * window of one step, window_overflow = steps whose window exceeded its
+ * capacity, list_steps = steps that scored a list instead of all points. */
 typedef struct {
     int32_t window_max;
     int32_t window_overflow;
     int32_t steps;
-    int32_t reserved;
+    int32_t list_steps;
 } ebc_greedy_stats;
 
 /* Wait for `stream`, then return the first deferred device error of this

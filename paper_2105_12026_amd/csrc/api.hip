@@ -287,7 +287,7 @@ hipError_t capture_greedy(ebc_dataset* ds, int32_t k, int32_t* sel_out, double* 
     if ((e = hipStreamBeginCapture(ds->cap_stream, hipStreamCaptureModeRelaxed)) != hipSuccess) return e;
     hipError_t le = launch_reset_state(ds, ds->cap_stream);
     for (int32_t t = 0; t < k && le == hipSuccess; ++t)
-        le = launch_greedy_step(ds, t, sel_out, f_out, gain_out, t + 1 == k, ds->cap_stream, nullptr);
+        le = launch_greedy_step(ds, t, k, sel_out, f_out, gain_out, ds->cap_stream, nullptr);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(ds->cap_stream, &g);
     if (le != hipSuccess) e = le;
@@ -321,6 +321,7 @@ ebc_status ebc_greedy(ebc_dataset* ds, int32_t k, int32_t* sel_out, double* f_ou
     if (!sel_out || !f_out) return EBC_E_INVALID_ARG;
     hipStream_t s = as_stream(stream);
     ds->stats.steps = k;
+    ds->stats.list_steps = ds->prof ? 0 : greedy_list_steps(ds, k);
     if (ds->graph_on && !ds->prof) {
         hipError_t e = hipSuccess;
         if (!(ds->gexec && ds->g_k == k && ds->g_variant == ds->variant && ds->g_sel == sel_out &&
@@ -334,10 +335,9 @@ ebc_status ebc_greedy(ebc_dataset* ds, int32_t k, int32_t* sel_out, double* f_ou
         hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
         if (ds->prof && (e = ds->prof->next(ev)) != hipSuccess) break;
         if (ev[0] && (e = hipEventRecord(ev[0], s)) != hipSuccess) break;
-        e = launch_greedy_step(ds, t, sel_out, f_out, gain_out, t + 1 == k, s, ev[1]);
+        e = launch_greedy_step(ds, t, k, sel_out, f_out, gain_out, s, ev[1]);
         if (e == hipSuccess && ev[2]) e = hipEventRecord(ev[2], s);
     }
-    ds->stats.steps = k;
     return from_hip(e);
 }
 

@@ -174,6 +174,7 @@ ebc_status ebc_greedy_batched(ebc_batch* bt, const int32_t* k, int32_t* const* s
         fill_desc(bt->ds[i], k[i], sel_out[i], f_out[i], gain_out ? gain_out[i] : nullptr, &hd[i]);
         hd[i].lazy = bt->lists[i];
         bt->ds[i]->stats.steps = k[i];
+        bt->ds[i]->stats.list_steps = bt->lists[i] && k[i] > 0 ? k[i] - 1 : 0;
     }
     memcpy(h + bt->tl.row_pre, bt->h_row_pre.data(), bt->h_row_pre.size() * sizeof(int64_t));
     memcpy(h + bt->tl.slot_inst, bt->h_slot_inst.data(), bt->h_slot_inst.size() * sizeof(int32_t));

@@ -47,7 +47,7 @@ struct DevState {
                          // their clamped terms by 2^-gexp into [0, 1]
     int32_t list_heads;  // heads and list of the current step (see lazy.h)
     int32_t list_len;
-    int32_t pad1;
+    int32_t list_exact;  // its candidates that are scored again in the full step's chunks
 };
 
 struct WindowEntry {
@@ -313,6 +313,8 @@ int64_t gains_cand_tile(const ebc_dataset* ds);
 // How far scoring lists (lazy.h) pays in greedy steps of this dataset: above 1
 // it does when the dataset runs alone; 0 if it cannot.
 double greedy_lists_worth(const ebc_dataset* ds);
+// Steps of a greedy run of k steps, alone, that score lists.
+int32_t greedy_list_steps(const ebc_dataset* ds, int32_t k);
 int32_t gains_bucket(const ebc_dataset* ds);  // datasets with equal keys share a batched gains launch
 void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double* gain, InstDesc* out);
 
@@ -359,7 +361,7 @@ hipError_t launch_gains_wide_batched(int32_t dt, int32_t ksplit, const InstDesc*
                                      hipStream_t s);
 hipError_t launch_gains_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst,
                                 const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t, hipStream_t s);
-// ... of the heads (part 0) or lists (part 1) of the instances at a list step (lazy.h)
+// ... of the heads (part 0), lists (1) or recounts (2) of the instances at a list step (lazy.h)
 hipError_t launch_gains_f32_list_batched(int32_t k_pad, bool trim, const InstDesc* descs, const int32_t* slot_inst,
                                          int32_t slots, int32_t t, int32_t part, hipStream_t s);
 hipError_t launch_gains_lp_list_batched(int32_t dt, int32_t kc, const InstDesc* descs, const int32_t* slot_inst,
@@ -408,7 +410,7 @@ hipError_t launch_gains_l1(const ebc_dataset* ds, const GainsArgs& ga, hipStream
 hipError_t launch_gains(const ebc_dataset* ds, hipStream_t s);
 // ... and of ebc_marginal_gains (cand null: all rows; part: call_splits x n_pad)
 hipError_t launch_gains_call(const ebc_dataset* ds, const int32_t* cand, int64_t n_cand, hipStream_t s);
-// gains of the instance's heads (part 0) or list (part 1), see lazy.h
+// gains of the instance's heads (part 0), list (part 1) or recount (part 2), see lazy.h
 hipError_t launch_gains_f32_list(const InstDesc& c, int32_t part, hipStream_t s);
 hipError_t launch_gains_lp_list(const InstDesc& c, int32_t part, hipStream_t s);
 hipError_t launch_gains_l1_list(const InstDesc& c, int32_t part, hipStream_t s);
@@ -436,8 +438,9 @@ __host__ __device__ inline double window_tau(ebc_dtype dt) {
 }
 __host__ __device__ inline double window_tau_abs(ebc_dtype dt) { return dt == EBC_DT_F32 ? 1e-4 : 1e-2; }
 hipError_t launch_gains_out(const ebc_dataset* ds, int64_t n_cand, double* out, hipStream_t s);
-hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out, double* f_out,
-                              double* gain_out, bool last, hipStream_t s, hipEvent_t ev_gains_done);
+// step t of a run of k
+hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t k, int32_t* sel_out, double* f_out,
+                              double* gain_out, hipStream_t s, hipEvent_t ev_gains_done);
 // device scratch of one multi-set evaluation of l sets over n ground points
 size_t eval_sets_scratch_bytes(int64_t n, int64_t l);
 // `scratch`: at least eval_sets_scratch_bytes(ds->n, l) bytes, 256-byte aligned

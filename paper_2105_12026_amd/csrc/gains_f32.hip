@@ -553,10 +553,10 @@ hipError_t launch_gains_f32_list_batched(int32_t k_pad, bool trim, const InstDes
 #define EBC_KP(K)                                                                                               \
     case K:                                                                                                     \
         if (trim)                                                                                               \
-            hipLaunchKernelGGL((kb_gains_f32_list<K, true>), dim3(kListGridBatch), dim3(256), 0, s, descs, slot_inst, \
+            hipLaunchKernelGGL((kb_gains_f32_list<K, true>), dim3(list_grid_batched(part)), dim3(256), 0, s, descs, slot_inst, \
                                slots, t, part);                                                                 \
         else                                                                                                    \
-            hipLaunchKernelGGL((kb_gains_f32_list<K, false>), dim3(kListGridBatch), dim3(256), 0, s, descs,          \
+            hipLaunchKernelGGL((kb_gains_f32_list<K, false>), dim3(list_grid_batched(part)), dim3(256), 0, s, descs,          \
                                slot_inst, slots, t, part);                                                      \
         break;
         EBC_F32_KPS(EBC_KP)

@@ -971,7 +971,7 @@ hipError_t launch_gains_lp_list_batched(int32_t dt, int32_t kc, const InstDesc* 
                                         int32_t slots, int32_t t, int32_t part, hipStream_t s) {
 #define EBC_LPL(DTV, K)                                                                                             \
     case K:                                                                                                         \
-        hipLaunchKernelGGL((kb_gains_lp_list<DTV, K, 2, wide_stage(DTV, K)>), dim3(kListGridBatch), dim3(256), 0, s,     \
+        hipLaunchKernelGGL((kb_gains_lp_list<DTV, K, 2, wide_stage(DTV, K)>), dim3(list_grid_batched(part)), dim3(256), 0, s,     \
                            descs, slot_inst, slots, t, part);                                                       \
         break;
     switch (dt) {

@@ -13,20 +13,30 @@
 //      below the window.
 // The heads are scored again with the list, so that equal candidates get
 // equal sums (the two launches cut the ground set differently).
+//   3. the recount: where more candidates come near the window of the list's
+//      best than are re-scored (kWindowMax), which of them are kept depends on
+//      the last bit of every sum. The near ones are scored once more with the
+//      chunks of a step that scores all candidates: the same sums, bit for bit,
+//      hence the same window. A list of more than half of the points is cut
+//      that way from the start. Otherwise (nearly always) the recount's launch
+//      finds nothing to do (2 us, and the launch).
 // The window, its float64 re-score and the pick are those of a step that
 // scores all candidates: the same candidates enter it. Over a run a candidate
 // is scored 1.1 to 1.7 times instead of k times; the rest is launches. 100000 x
 // 100 float32, k = 50: 730 -> 37 ms; 200000 x 64 bfloat16, k = 100: 418 -> 25
 // ms; 10007 x 50 L1, k = 10: 2.68 -> 1.12 ms.
 //
-// Bound of the rounding: old and new sums may be cut into chunks differently,
-// so a float32 lane sum of t non-negative terms may differ by t * 2^-24 of
-// itself; the list takes everything within twice that of the window.
+// Bound of the rounding: a float32 lane sum of t non-negative terms is within
+// t * 2^-24 of itself (relative), and a lane of a chunk of p points adds p / 32.
+// Between a candidate's old sum and the window of a step that scores all lie
+// four such sums: the best head's, the one that step would have for it, the
+// candidate's old one and the one that step would have. Between the list's sums
+// and that step's there are as many. The list, and the recount, take everything
+// that far below the window (list_slack).
 //
-// A dataset keeps, in the last chunk of its partial sums (read by step 0
-// before they are written): the list (int32 rows) and each row's m at the
-// time it was scored (float32); the heads lie in bcnt (at most one per row
-// block), which only steps that score every candidate use.
+// A dataset keeps its list (int32 rows) and each row's m at the time it was
+// scored (float32) in wstage, and its heads in bcnt (at most one per row
+// block): only steps that score every candidate use these.
 #pragma once
 
 #include "ebc_internal.h"
@@ -42,9 +52,7 @@ __host__ __device__ inline int list_stretch(const InstDesc& c) {
     return (c.nb + h - 1) / h;
 }
 
-__host__ __device__ inline int32_t* list_rows(const InstDesc& c) {
-    return reinterpret_cast<int32_t*>(c.b.part + int64_t(c.v_splits - 1) * c.n_pad);
-}
+__host__ __device__ inline int32_t* list_rows(const InstDesc& c) { return reinterpret_cast<int32_t*>(c.b.wstage); }
 __host__ __device__ inline float* list_m(const InstDesc& c) {
     return reinterpret_cast<float*>(list_rows(c) + c.n_pad);
 }
@@ -69,14 +77,21 @@ struct ListGeom {
     int64_t chunk, stride;
     int32_t tiles, splits;
 };
-__host__ __device__ inline ListGeom list_geom(const InstDesc& c, int64_t cnt, int32_t ct) {
+// Does a list of cnt candidates take the chunks of a step that scores all?
+__host__ __device__ inline bool list_full_cut(const InstDesc& c, int64_t cnt) { return 2 * cnt > c.n_pad; }
+__host__ __device__ inline ListGeom list_geom(const InstDesc& c, int64_t cnt, int32_t ct, bool full_cut) {
     ListGeom g;
     g.tiles = int32_t((cnt + ct - 1) / ct);
     g.stride = int64_t(g.tiles) * ct;
+    if (full_cut) {
+        g.splits = c.v_splits;
+        g.chunk = c.chunk;
+        return g;
+    }
     const int32_t unit = list_unit(c);
     const int32_t units = int32_t(c.n_pad / unit);
     const int32_t tiles = g.tiles > 0 ? g.tiles : 1;
-    const int32_t cap = int32_t((c.v_splits - 1) * (c.n_pad / ct) / tiles);
+    const int32_t cap = int32_t(c.v_splits * (c.n_pad / ct) / tiles);
     int32_t s = kListSlots / tiles;
     const int32_t fine = units / (kListChunk / unit);
     s = s > fine ? s : fine;
@@ -90,33 +105,51 @@ __host__ __device__ inline ListGeom list_geom(const InstDesc& c, int64_t cnt, in
     g.chunk = int64_t(per) * unit;
     return g;
 }
+// Half-width of what may lie between a sum and the window of a step that scores
+// all, for a best gain g: four float32 sums of the longest chunk any of them has
+// (16 terms more for the float64 sums behind them).
+__device__ inline double list_slack(const InstDesc& c, double g) {
+    const int32_t unit = list_unit(c), units = int32_t(c.n_pad / unit);
+    int32_t s = units / (kListChunk / unit);  // fewest chunks of list_geom
+    s = s < c.v_splits ? s : c.v_splits;
+    s = s < 1 ? 1 : s;
+    const int64_t longest = int64_t((units + s - 1) / s) * unit;
+    const int64_t p = c.chunk > longest ? c.chunk : longest;
+    return 4.0 * (double(p) / 32.0 + 16.0) * 0x1p-24 * fabs(g);
+}
 // Workgroups of a list launch over one instance: one per pair (the scheduler
 // balances them, and those past the list's end return at once); a longer list
 // than that is walked.
 constexpr int kListGridMax = 16384;
 inline unsigned list_grid(const InstDesc& c, int32_t part, int32_t ct) {
-    const int64_t most = part ? c.n_pad : list_heads_max(c.dt);
-    int64_t items = 0;
-    // the pairs do not grow monotonically with the count; kListSlots + tiles
-    // bounds them for few tiles, the geometry at the full count for many
-    const ListGeom g = list_geom(c, most, ct);
-    items = int64_t(g.tiles) * (g.splits > 8 ? g.splits : 8) + kListSlots + g.tiles;
+    if (part == 2) return kListSlots;  // nearly always empty
+    int64_t items = int64_t(c.v_splits) * (c.n_pad / ct);  // what the partial sums have room for
+    if (part == 0) {
+        const ListGeom g = list_geom(c, list_heads_max(c.dt), ct, false);
+        items = int64_t(g.tiles) * (g.splits > 8 ? g.splits : 8) + kListSlots + g.tiles;
+    }
     return unsigned(items < kListGridMax ? items : kListGridMax);
 }
-constexpr int kListGridBatch = 4096;  // batched: pairs of many instances, walked
+// Batched: pairs of many instances, walked.
+inline unsigned list_grid_batched(int32_t part) { return part == 2 ? kListSlots : 4096; }
 
-// Rows and their number: part 0 the heads, part 1 the list. Until their sums
-// are added the entries are slots of the grouped order where there is one.
+// Rows and their number: part 0 the heads, part 1 the list, part 2 the recount.
+// Until their sums are added the entries are slots of the grouped order where
+// there is one.
 __device__ inline int32_t* list_part(const InstDesc& c, int32_t part) { return part ? list_rows(c) : c.b.bcnt; }
 __device__ inline int64_t list_count(const InstDesc& c, int32_t part) {
-    return part ? c.b.state->list_len : c.b.state->list_heads;
+    const DevState* st = c.b.state;
+    return part == 0 ? st->list_heads : (part == 1 ? st->list_len : st->list_exact);
+}
+__device__ inline ListGeom list_part_geom(const InstDesc& c, int32_t part, int64_t cnt, int32_t ct) {
+    return list_geom(c, cnt, ct, part == 2 || (part == 1 && list_full_cut(c, cnt)));
 }
 
 // Gains-kernel arguments of a part of the list, and the number of (tile,
 // chunk) pairs; candidate tiles of ct rows.
 __device__ inline GainsArgs list_args(const InstDesc& c, int32_t part, int32_t ct, int64_t* items) {
     const int64_t cnt = list_count(c, part);
-    const ListGeom g = list_geom(c, cnt, ct);
+    const ListGeom g = list_part_geom(c, part, cnt, ct);
     GainsArgs a = gains_args(c, list_part(c, part), cnt);
     a.v_splits = g.splits;
     a.chunk = g.chunk;
@@ -144,7 +177,7 @@ __device__ __forceinline__ void list_walk(const InstDesc* __restrict__ descs, co
         if (s0 + lane < slots) {
             const InstDesc& c = descs[slot_inst[s0 + lane]];
             if (list_step(c, c.t0 + t) && c.t0 + t < c.k) {
-                const ListGeom g = list_geom(c, list_count(c, part), ct);
+                const ListGeom g = list_part_geom(c, part, list_count(c, part), ct);
                 upto = g.tiles * g.splits;
             }
         }

@@ -64,6 +64,10 @@ double greedy_lists_worth(const ebc_dataset* ds) {
     return pairs * (products + 27) / 1.5e10;
 }
 
+int32_t greedy_list_steps(const ebc_dataset* ds, int32_t k) {
+    return k > 0 && greedy_lists_worth(ds) > 1.0 ? k - 1 : 0;
+}
+
 int32_t gains_bucket(const ebc_dataset* ds) {
     // last digit: the tile variant (reduced precision), for long rows the K
     // split, for float32 whether the rows' last 4 padded slots are empty (the
@@ -88,7 +92,7 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
     c.dt = int32_t(ds->dt);
     c.variant = ds->variant;
     c.metric = ds->metric;
-    c.lazy = greedy_lists_worth(ds) > 1.0 ? 1 : 0;
+    c.lazy = greedy_list_steps(ds, k) > 0 ? 1 : 0;
     c.chunk = gains_chunk(ds, ds->v_splits);
     c.sel = sel;
     c.f = f;
@@ -852,7 +856,7 @@ __global__ void k_state_init(DevState* st) {
         st->gexp = 0;
         st->list_heads = 0;
         st->list_len = 0;
-        st->pad1 = 0;
+        st->list_exact = 0;
     }
 }
 

@@ -13,7 +13,8 @@
 // first three stages by
 //   k_list_sum    per-chunk sums of the heads or the list -> gsum
 //   k_list_build  candidates whose old gain reaches the window of the best head
-//   k_list_window the window out of the list
+//   k_list_window the window out of the list, or which of it to score again
+// where k_rescore makes the window out of the candidates scored again;
 // and k_update / k_fsum also choose the heads of the next step's list.
 // No step reads anything back to the host; all sums run in a fixed order.
 #include <math.h>
@@ -259,13 +260,14 @@ __device__ __forceinline__ void row_terms(const float* __restrict__ xv, bool vec
 
 // Windows of at most stored_window(c) candidates keep their distances for the
 // update of the same step, in the partial sums (not needed between the window
-// and the next gains; lists keep their last chunk): 8 bytes a point read
-// there instead of a whole row.
-__host__ __device__ inline int stored_window(const InstDesc& c) {
-    return c.v_splits - 1 < kRescoreGroup ? c.v_splits - 1 : kRescoreGroup;
+// and the next gains, but while row blocks may still read a recount's there):
+// 8 bytes a point read there instead of a whole row.
+__device__ __forceinline__ bool distances_stored(const InstDesc& c) {
+    const int most = c.v_splits < kRescoreGroup ? c.v_splits : kRescoreGroup;
+    return c.b.state->window_count <= most && !(c.lazy && c.b.state->list_exact > 0);
 }
 __device__ __forceinline__ bool window_has_distances(const InstDesc& c, int rank) {
-    return rank >= 0 && c.b.state->window_count <= stored_window(c);
+    return rank >= 0 && distances_stored(c);
 }
 
 // METRIC 0: squared Euclidean (the paper's d); 1: L1, sum of |x_vk - x_ck|.
@@ -296,7 +298,7 @@ __device__ __forceinline__ void rescore_group(const InstDesc& c, int64_t blk, in
         __syncthreads();
         if (live) row_terms<METRIC, NJ>(xv + k0, vec, kn, cx, acc);
     }
-    if (W <= stored_window(c) && live) {
+    if (distances_stored(c) && live) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             if (j < gn) b.part[int64_t(g0 + j) * c.n_pad + v] = acc[j];
@@ -327,7 +329,10 @@ __device__ void rescore_impl(const InstDesc& c, int64_t blk, double* __restrict_
         for (int g0 = 0; g0 < W; g0 += kRescoreGroup) rescore_group<METRIC, kRescoreGroup>(c, blk, g0, W, cx, red);
 }
 
+__device__ void list_exact_body(const InstDesc& c, bool count);
+
 __device__ void rescore_body(const InstDesc& c, int64_t blk) {
+    if (c.lazy && c.b.state->list_exact > 0) list_exact_body(c, blk == 0);  // lazy.h
     __shared__ double cx[kRescoreGroup * kRescoreChunk];
     __shared__ double red[kRescoreGroup][kBlock];
     if (c.metric == 1)
@@ -960,6 +965,7 @@ __device__ void fsum_body(const InstDesc& c, int32_t t) {
     if (threadIdx.x == 0) {
         c.b.state->list_heads = heads;
         c.b.state->list_len = 0;
+        c.b.state->list_exact = 0;
     }
 }
 
@@ -974,7 +980,7 @@ __device__ void list_sum_body(const InstDesc& c, int32_t part, int64_t first, in
     __shared__ double red[kListSumThreads / kListSumPos][kListSumPos];
     const Buffers& b = c.b;
     const int64_t cnt = list_count(c, part);
-    const ListGeom g = list_geom(c, cnt, list_tile(c.dt, c.metric));
+    const ListGeom g = list_part_geom(c, part, cnt, list_tile(c.dt, c.metric));
     int32_t* __restrict__ rows = list_part(c, part);
     const int p = threadIdx.x % kListSumPos, q = threadIdx.x / kListSumPos;
     constexpr int Q = kListSumThreads / kListSumPos;
@@ -996,7 +1002,7 @@ __device__ void list_sum_body(const InstDesc& c, int32_t part, int64_t first, in
 }
 
 // Append every unselected candidate whose last gain reaches the window of the
-// best head, less the rounding of a gain (lazy.h).
+// best head, less the rounding of the sums (lazy.h).
 // Rows are taken in the grouped order where there is one, so that neighbours
 // in the list are neighbours in space (their tiles clamp together).
 __device__ void list_build_body(const InstDesc& c, int64_t blk) {
@@ -1008,8 +1014,7 @@ __device__ void list_build_body(const InstDesc& c, int64_t blk) {
     double best = -INFINITY;  // each wave for itself
     for (int i = threadIdx.x & 63; i < heads; i += 64) best = fmax(best, b.gsum[head[i]]);
     best = wave_max(best);
-    const double slack = 2.0 * (double(c.chunk) / 32.0 + 64.0) * 0x1p-24 * fabs(best);
-    const double thr = window_threshold(best, b.state) - slack;
+    const double thr = window_threshold(best, b.state) - list_slack(c, best);
     const int64_t i = blk * kBlock + threadIdx.x;
     const int64_t row = b.perm ? int64_t(b.perm[i]) : i;
     const bool take = !b.selected[row] && b.gsum[row] >= thr;
@@ -1032,18 +1037,27 @@ __device__ void list_build_body(const InstDesc& c, int64_t blk) {
 // The window out of `len` candidates (one block): rows[0 .. len), or rows 0 ..
 // len - 1 where rows is null. The same candidates, and the same rules above
 // kWindowMax and kWindowCap of them, as wcount and wselect. Entries land in
-// index or rank order, so nothing depends on the order of `rows`.
-__device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows, int len) {
+// index or rank order, so nothing depends on the order of `rows`. perm
+// non-null: `rows` holds slots of the grouped order. count: this block counts
+// the window in the statistics (several blocks may make the same window).
+// lower non-null (sums of other chunks than those of a step that scores all):
+// where more than kWindowMax candidates reach the window or come as near as its
+// rounding, no window is made, *lower is the gain they reach and false returned.
+template <int NT>
+__device__ bool window_body(const InstDesc& c, const int32_t* __restrict__ rows, const int32_t* __restrict__ perm,
+                            int len, double* lower, bool count) {
     __shared__ WindowEntry list[kWindowCap];
-    __shared__ double wg[kSelThreads / 64];
-    __shared__ int wi[kSelThreads / 64];
+    __shared__ int hist[256];
+    __shared__ int close;
+    __shared__ double wg[NT / 64];
+    __shared__ int wi[NT / 64];
     __shared__ int found;
     const Buffers& b = c.b;
     const int tid = threadIdx.x, lane = tid & 63;
-    auto row_at = [&](int i) { return rows ? rows[i] : i; };
+    auto row_at = [&](int i) { return !rows ? i : (perm ? perm[rows[i]] : rows[i]); };
     double gb = -INFINITY, g0 = -INFINITY;
     int ib = 0x7fffffff, r0 = 0, none = 0;
-    for (int i = tid; i < len; i += kSelThreads) {
+    for (int i = tid; i < len; i += NT) {
         const int r = row_at(i);
         const double g = b.gsum[r];
         if (i == tid) {  // kept for the second pass
@@ -1060,18 +1074,20 @@ __device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows,
         wg[tid >> 6] = gb;
         wi[tid >> 6] = ib;
     }
-    if (tid == 0) found = 0;
+    if (tid == 0) found = close = 0;
     __syncthreads();
-    gb = lane < kSelThreads / 64 ? wg[lane] : -INFINITY;
-    ib = lane < kSelThreads / 64 ? wi[lane] : 0x7fffffff;
+    gb = lane < NT / 64 ? wg[lane] : -INFINITY;
+    ib = lane < NT / 64 ? wi[lane] : 0x7fffffff;
     wave_best(gb, ib, none);
     const double gmax = gb;
     const int first = ib;
     const double thr = window_threshold(gmax, b.state);
     auto inside = [&](double g) { return g >= thr && g > -INFINITY; };
-    for (int i = tid; i < len; i += kSelThreads) {
+    const double low = lower ? thr - list_slack(c, gmax) : thr;
+    for (int i = tid; i < len; i += NT) {
         const int r = i == tid ? r0 : row_at(i);
         const double g = i == tid ? g0 : b.gsum[r];
+        if (lower && g >= low && g > -INFINITY) atomicAdd(&close, 1);
         if (!inside(g)) continue;
         const int at = atomicAdd(&found, 1);
         if (at >= kWindowCap) continue;
@@ -1080,10 +1096,14 @@ __device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows,
         list[at].pad = 0;
     }
     __syncthreads();
-    const int total = found;
+    const int total = found, near = close;
     __syncthreads();  // every wave has read it: found is reused below
+    if (lower && near > kWindowMax) {
+        *lower = low;
+        return false;
+    }
     if (total <= kWindowCap) {
-        for (int i = tid; i < total; i += kSelThreads) {
+        for (int i = tid; i < total; i += NT) {
             int rank = 0;
             if (total <= kWindowMax)
                 for (int j = 0; j < total; ++j) rank += list[j].idx < list[i].idx ? 1 : 0;
@@ -1092,29 +1112,45 @@ __device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows,
             if (rank < kWindowMax) b.wfinal[rank] = list[i];
         }
     } else {
-        // overflow: the best one, then the lowest indices among the others.
-        // The largest index taken is found by bisection (indices are distinct).
-        int lo = -1, hi = int(c.n);  // count(index <= lo) < kWindowMax - 1 <= count(index <= hi)
-        while (hi - lo > 1) {
-            const int mid = lo + (hi - lo) / 2;
-            if (tid == 0) found = 0;
+        // overflow: the best one, then the lowest indices among the others. The
+        // largest index taken, byte by byte from the top: of the indices that
+        // share the bytes so far, how many have each next byte?
+        int hi = 0, need = kWindowMax - 1, shift = 0;
+        while (int64_t(c.n) >> (shift + 8)) shift += 8;
+        for (; shift >= 0; shift -= 8) {
+            for (int i = tid; i < 256; i += NT) hist[i] = 0;
             __syncthreads();
-            int k = 0;
-            for (int i = tid; i < len; i += kSelThreads) {
+            for (int i = tid; i < len; i += NT) {
                 const int r = row_at(i);
-                k += (inside(b.gsum[r]) && r <= mid && r != first) ? 1 : 0;
+                if (inside(b.gsum[r]) && r != first && int64_t(r) >> (shift + 8) == int64_t(hi) >> (shift + 8))
+                    atomicAdd(&hist[(r >> shift) & 255], 1);
             }
-            if (k) atomicAdd(&found, k);
             __syncthreads();
-            if (found >= kWindowMax - 1)
-                hi = mid;
-            else
-                lo = mid;
-            __syncthreads();
+            // each wave for itself: the byte with which `need` indices are reached
+            int n4[4], upto = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) upto += n4[i] = hist[4 * lane + i];
+            const int own = upto;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int add = __shfl_up(upto, off, 64);
+                if (lane >= off) upto += add;
+            }
+            const int at = __popcll(__builtin_amdgcn_ballot_w64(upto < need));  // its four bytes
+            int before = upto - own, byte = 4 * lane;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (byte == 4 * lane + i && before + n4[i] < need) {
+                    before += n4[i];
+                    ++byte;
+                }
+            need -= __shfl(before, at, 64);
+            hi |= __shfl(byte, at, 64) << shift;
+            __syncthreads();  // hist is cleared again
         }
         if (tid == 0) found = 0;
         __syncthreads();
-        for (int i = tid; i < len; i += kSelThreads) {
+        for (int i = tid; i < len; i += NT) {
             const int r = row_at(i);
             const double g = b.gsum[r];
             if (!(inside(g) && r <= hi && r != first)) continue;
@@ -1125,7 +1161,7 @@ __device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows,
             list[at].pad = 0;
         }
         __syncthreads();
-        for (int i = tid; i < kWindowMax - 1; i += kSelThreads) {
+        for (int i = tid; i < kWindowMax - 1; i += NT) {
             int rank = 0;
             for (int j = 0; j < kWindowMax - 1; ++j) rank += list[j].idx < list[i].idx ? 1 : 0;
             b.wfinal[1 + rank] = list[i];
@@ -1139,14 +1175,52 @@ __device__ void window_body(const InstDesc& c, const int32_t* __restrict__ rows,
         }
     }
     if (tid == 0) {
-        const int W = total < kWindowMax ? total : kWindowMax;
-        b.state->window_count = W;
-        if (total > b.state->window_max) b.state->window_max = total;
-        if (total > kWindowCap) b.state->window_overflow += 1;
+        b.state->window_count = total < kWindowMax ? total : kWindowMax;
+        if (count && total > b.state->window_max) b.state->window_max = total;
+        if (count && total > kWindowCap) b.state->window_overflow += 1;
     }
+    return true;
 }
 
-__device__ void list_window_body(const InstDesc& c) { window_body(c, list_rows(c), c.b.state->list_len); }
+// The window out of the list, or the candidates of the recount (lazy.h).
+__device__ void list_window_body(const InstDesc& c) {
+    __shared__ int kept;
+    const Buffers& b = c.b;
+    const int len = b.state->list_len, tid = threadIdx.x;
+    int32_t* rows = list_rows(c);
+    double lower;
+    if (tid == 0) kept = 0;
+    if (!window_body<kSelThreads>(c, rows, nullptr, len, list_full_cut(c, len) ? nullptr : &lower, true))
+        for (int i0 = 0; i0 < len; i0 += kSelThreads) {
+            const int row = i0 + tid < len ? rows[i0 + tid] : -1;
+            const double g = row >= 0 ? b.gsum[row] : -INFINITY;
+            __syncthreads();  // entries up to here have been read: those kept take their places
+            if (g >= lower && g > -INFINITY) rows[atomicAdd(&kept, 1)] = b.inv ? b.inv[row] : row;
+            __syncthreads();
+        }
+    if (tid == 0) b.state->list_exact = kept;
+}
+
+// The recount's sums, added as gsum_body does, and the window out of them. Rare,
+// and then one of the row blocks' own stages: every block makes the same sums
+// and the same window and writes the same values, so none waits for another and
+// the steps without a recount pay no launch for it.
+__device__ void list_exact_body(const InstDesc& c, bool count) {
+    const Buffers& b = c.b;
+    const int len = b.state->list_exact;
+    const ListGeom g = list_part_geom(c, 2, len, list_tile(c.dt, c.metric));
+    const int32_t* rows = list_rows(c);
+    for (int i = threadIdx.x; i < len; i += kBlock) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int q = 0; q < g.splits; ++q) s += b.part[int64_t(q) * g.stride + i];
+        const int32_t row = b.perm ? b.perm[rows[i]] : rows[i];
+        b.gsum[row] = b.selected[row] ? -INFINITY : s;
+    }
+    __syncthreads();
+    window_body<kBlock>(c, rows, b.perm, len, nullptr, count);
+    __syncthreads();
+}
 
 // ---- small ground sets (at most kSmallBlocks row blocks), solo, all
 // candidates scored: the stages that need one block run as one kernel, and
@@ -1176,7 +1250,7 @@ __device__ void select_small_body(const InstDesc& c, int32_t t, int32_t splits) 
         for (int s = 0; s < splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
         b.gsum[i] = b.selected[i] || i == prev ? -INFINITY : g;
     }
-    window_body(c, nullptr, int(c.n_pad));  // each thread reads the sums it wrote
+    window_body<kSelThreads>(c, nullptr, nullptr, int(c.n_pad), nullptr, true);  // each thread reads the sums it wrote
 }
 
 __device__ int pick_small(const InstDesc& c, int32_t t, int64_t blk, int* rank) {
@@ -1293,10 +1367,10 @@ __global__ void __launch_bounds__(kBlock) kb_fsum(const InstDesc* __restrict__ d
     if (c.t0 + t < c.k) fsum_body(c, c.t0 + t);
 }
 
-hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out, double* f_out,
-                              double* gain_out, bool last, hipStream_t s, hipEvent_t ev_gains_done) {
+hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t k, int32_t* sel_out, double* f_out,
+                              double* gain_out, hipStream_t s, hipEvent_t ev_gains_done) {
     InstDesc c;
-    fill_desc(ds, t + 1, sel_out, f_out, gain_out, &c);
+    fill_desc(ds, k, sel_out, f_out, gain_out, &c);
     if (ds->prof) {  // a timed step is a whole launch
         c.lazy = 0;
         c.b.pairs = nullptr;
@@ -1326,7 +1400,7 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
                 hipLaunchKernelGGL(k_update_small, dim3(nb), dim3(kBlock), 0, s, c, t);
             }
             // f(S_t) and the mark of the pick: the next step's select, or here
-            if (last) hipLaunchKernelGGL(k_fsum, dim3(1), dim3(kBlock), 0, s, c, t);
+            if (t + 1 == k) hipLaunchKernelGGL(k_fsum, dim3(1), dim3(kBlock), 0, s, c, t);
             return hipGetLastError();
         }
         hipLaunchKernelGGL(k_gsum, dim3(nb), dim3(kBlock), 0, s, c, gain_splits(c, t));
@@ -1360,14 +1434,15 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t* sel_out
 // Gains, sums, list and window of a step that scores a list.
 hipError_t launch_list_step(const InstDesc& c, hipStream_t s) {
     const unsigned sums = 256;  // workgroups; each walks its share of the list
-    for (int32_t part = 0; part < 2; ++part) {
+    for (int32_t part = 0; part < 3; ++part) {
         const hipError_t e = launch_gains_list(c, part, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_list_sum, dim3(part ? sums : kListHeads / kListSumPos), dim3(kListSumThreads), 0, s, c,
-                           part);
+        if (part < 2)
+            hipLaunchKernelGGL(k_list_sum, dim3(part ? sums : kListHeads / kListSumPos), dim3(kListSumThreads), 0, s, c,
+                               part);
         if (part == 0) hipLaunchKernelGGL(k_list_build, dim3(c.nb), dim3(kBlock), 0, s, c);
+        if (part == 1) hipLaunchKernelGGL(k_list_window, dim3(1), dim3(kSelThreads), 0, s, c);
     }
-    hipLaunchKernelGGL(k_list_window, dim3(1), dim3(kSelThreads), 0, s, c);
     return hipGetLastError();
 }
 
@@ -1388,16 +1463,17 @@ hipError_t launch_tick(const std::vector<GainsBucket>& buckets, const InstDesc* 
         hipLaunchKernelGGL(kb_wselect, one, dim3(kSelThreads), 0, s, descs, t);
     }
     if (lists) {
-        for (int32_t part = 0; part < 2; ++part) {
+        for (int32_t part = 0; part < 3; ++part) {
             for (const GainsBucket& b : buckets)
                 if (b.lists && (e = launch_gains_list_batched(b.key, descs, slot_inst + b.slot_begin, b.slots, t, part,
                                                               s)) != hipSuccess)
                     return e;
-            hipLaunchKernelGGL(kb_list_sum, dim3(part ? 32 : kListHeads / kListSumPos, unsigned(count)),
-                               dim3(kListSumThreads), 0, s, descs, t, part);
+            if (part < 2)
+                hipLaunchKernelGGL(kb_list_sum, dim3(part ? 32 : kListHeads / kListSumPos, unsigned(count)),
+                                   dim3(kListSumThreads), 0, s, descs, t, part);
             if (part == 0) hipLaunchKernelGGL(kb_list_build, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
+            if (part == 1) hipLaunchKernelGGL(kb_list_window, one, dim3(kSelThreads), 0, s, descs, t);
         }
-        hipLaunchKernelGGL(kb_list_window, one, dim3(kSelThreads), 0, s, descs, t);
     }
     hipLaunchKernelGGL(kb_rescore, rows, dim3(kBlock), 0, s, descs, row_pre, count, t);
     if (long_rows) {

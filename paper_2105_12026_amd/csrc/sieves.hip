@@ -659,7 +659,7 @@ ebc_status start_stream(ebc_dataset* ds, double* m_max, int32_t* sel_tmp, double
                         DevState* st) {
     if (launch_reset_state(ds, s) != hipSuccess) return EBC_E_DEVICE;
     if (!(*m_max > 0.0)) {
-        if (launch_greedy_step(ds, 0, sel_tmp, f_tmp, nullptr, true, s, nullptr) != hipSuccess ||
+        if (launch_greedy_step(ds, 0, 1, sel_tmp, f_tmp, nullptr, s, nullptr) != hipSuccess ||
             read_state(ds, st, s) != hipSuccess)
             return EBC_E_DEVICE;
         *m_max = st->gstar / double(ds->n);
@@ -765,6 +765,7 @@ ebc_status run_stream(ebc_dataset* ds, int32_t k, double eps, int64_t T, double 
     if (v_out) *v_out = T > 0 ? 0.0 : grid[size_t(res.best)];
     if (examined_out) *examined_out = res.examined;
     ds->stats.steps = res.count;
+    ds->stats.list_steps = 0;
     return EBC_OK;
 }
 

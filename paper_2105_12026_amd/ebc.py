@@ -50,7 +50,7 @@ class EBCError(RuntimeError):
 
 class _Stats(ctypes.Structure):
     _fields_ = [("window_max", ctypes.c_int32), ("window_overflow", ctypes.c_int32),
-                ("steps", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+                ("steps", ctypes.c_int32), ("list_steps", ctypes.c_int32)]
 
 
 class _Info(ctypes.Structure):

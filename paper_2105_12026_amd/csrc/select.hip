@@ -353,6 +353,10 @@ __device__ __forceinline__ int rescore_rows(const InstDesc& c, int W);
 // position in the window (-1: chosen outside of it).
 constexpr int kPickColumnRows = 64;
 constexpr int kPickThreads = 1024;
+// Solo runs of at most this many row blocks make the pick in every block of the
+// update, for itself, instead of in a launch before it (a launch is 4 to 5 us;
+// with more blocks the sums of a large window are read too often).
+constexpr int kPickBlocks = 128;
 
 template <int NT>
 __device__ int pick_choose(const InstDesc& c, double* gain, int* rank) {
@@ -459,7 +463,7 @@ __device__ void pick_body(const InstDesc& c, int32_t t) {
 // it had when it was last scored, times what is left of its own minimum since
 // (old: m_v before this step, which is what step 0 scored every candidate
 // with). The best of each block goes to bmax / barg.
-__device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, double old, double mv,
+__device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, int cs, double old, double mv,
                                     double* red, int* ri) {
     const Buffers& b = c.b;
     const int64_t v = blk * kBlock + threadIdx.x;
@@ -470,7 +474,7 @@ __device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, d
     else
         m_scored = lm[v];
     double est = -INFINITY;
-    if (!b.selected[v]) est = b.gsum[v] * (m_scored > 0.0f ? mv / double(m_scored) : 1.0);
+    if (!b.selected[v] && v != cs) est = b.gsum[v] * (m_scored > 0.0f ? mv / double(m_scored) : 1.0);
     int row = int(v), none = 0;
     wave_best(est, row, none);
     __syncthreads();  // red has been read
@@ -527,7 +531,7 @@ __device__ void update_body(const InstDesc& c, int64_t blk, int32_t t, int cs, i
         const double sum = tree_sum256(red, threadIdx.x);
         if (threadIdx.x == 0) b.fpart[blk] = sum;
     }
-    if (c.lazy) block_best_estimate(c, blk, t, old, mv, red, ri);
+    if (c.lazy) block_best_estimate(c, blk, t, cs, old, mv, red, ri);
 }
 
 // ---- L1 update (any row length): m_v <- min(m_v, sum_k |x_vk - x_c*k|) in
@@ -569,7 +573,7 @@ __device__ void update_l1_body(const InstDesc& c, int64_t blk, int32_t t, int cs
         const double sum = tree_sum256(red, threadIdx.x);
         if (threadIdx.x == 0) b.fpart[blk] = sum;
     }
-    if (c.lazy) block_best_estimate(c, blk, t, old, mv, red, ri);
+    if (c.lazy) block_best_estimate(c, blk, t, cs, old, mv, red, ri);
 }
 
 // ---- long rows (padded length above 128): re-score and update ----
@@ -1407,7 +1411,10 @@ hipError_t launch_greedy_step(const ebc_dataset* ds, int32_t t, int32_t k, int32
         hipLaunchKernelGGL(k_wcount, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_wselect, dim3(1), dim3(kSelThreads), 0, s, c);
     }
-    if (c.metric == 1) {
+    if (nb <= kPickBlocks && (c.metric == 1 || !wide_rows(c.k_pad))) {
+        hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_update_small, dim3(nb), dim3(kBlock), 0, s, c, t);
+    } else if (c.metric == 1) {
         hipLaunchKernelGGL(k_rescore, dim3(nb), dim3(kBlock), 0, s, c);
         hipLaunchKernelGGL(k_pick, dim3(1), dim3(kPickThreads), 0, s, c, t);
         hipLaunchKernelGGL(k_update_l1, dim3(nb), dim3(kBlock), 0, s, c, t);

@@ -444,16 +444,15 @@ kb_gains_f32_list(const InstDesc* __restrict__ descs, const int32_t* __restrict_
               [](const GainsArgs& ga, int64_t pair) { gains_f32_body<KP, TRIM>(ga, pair); });
 }
 
-// How many of a list's 128-candidate tiles take the wide kernel; the rest of
-// the list takes the narrow one. Chosen to end first: rounds of 256 workgroups
+// How many of the 128-candidate tiles take the wide kernel; the rest of the
+// candidates take the narrow one. Chosen to end first: rounds of 256 workgroups
 // (a wide and a narrow workgroup of a chunk measured 2.7 and 1.2 us per 64
 // points at d = 100) plus a launch each. Full rounds go to the wide kernel, a
 // partial last one to the narrow: 50000 x 100, 2303 candidates: 288 wide
 // workgroups 321 us a call, 256 wide and 128 narrow ones 256 us; 5000: 485 and
-// 445 us.
+// 445 us. A step over all of 1000 x 100 in 4 chunks: 33 -> 24 us.
 static int64_t wide_tiles(const GainsArgs& ga) {
     const int64_t tiles = (ga.n_cand + kGainsCandTile - 1) / kGainsCandTile;
-    if (!ga.cand) return tiles;
     const double len = double(ga.chunk) / kGainsVTile;
     auto cost = [&](int64_t w) {
         const int64_t rest = ga.n_cand - w * kGainsCandTile;
@@ -464,7 +463,8 @@ static int64_t wide_tiles(const GainsArgs& ga) {
     int64_t best = tiles;
     // candidates for the split: none, and whole rounds of wide workgroups
     const int64_t step = ga.v_splits < 256 ? 256 / ga.v_splits : 1;
-    for (int64_t w = 0; w < tiles; w += step)
+    // (all rows: one of the kernels takes them all)
+    for (int64_t w = 0; w < (ga.cand ? tiles : 1); w += step)
         if (cost(w) < cost(best)) best = w;
     return best;
 }
@@ -479,7 +479,7 @@ static void launch_kpt(const GainsArgs& ga, hipStream_t s) {
         hipLaunchKernelGGL((k_gains_f32<KP, TRIM>), dim3(unsigned(w * ga.v_splits)), dim3(256), 0, s, part);
     }
     if (first < ga.n_cand) {
-        part.cand = ga.cand + first;
+        part.cand = ga.cand ? ga.cand + first : nullptr;
         part.n_cand = ga.n_cand - first;
         part.part = ga.part + first;
         const unsigned wgs = unsigned((part.n_cand + 31) / 32 * ga.v_splits);

@@ -3,6 +3,8 @@
 // device once). Also the workspace layout and the greedy-state resets.
 #include <math.h>
 
+#include <algorithm>
+
 #include "ebc_internal.h"
 #include "quant.h"
 
@@ -119,7 +121,7 @@ hipError_t launch_gains_list_batched(int32_t bucket, const InstDesc* descs, cons
     return launch_gains_lp_list_batched(dt, kc, descs, slot_inst, slots, t, part, s);
 }
 
-int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {
+int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt, int32_t metric) {
     if (wide_rows(k_pad)) {
         // long rows: enough (candidate block, chunk) workgroups for about
         // eight waves per compute unit, chunks of at least 64 points
@@ -139,19 +141,22 @@ int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {
     // slower, reduced precision measured no faster with 16).
     int64_t tiles = n_pad / kGainsCandTile;
     if (tiles >= 64) return (dt == EBC_DT_F32 && tiles < 1024) ? 16 : 8;
-    // Small ground sets: about two workgroups for each of the 256 CUs, chunks
-    // of at least one LDS tile (1000 x 16: 8 workgroups 23 us, 128 4.5 us).
-    int64_t v = 512 / tiles;
+    // Small ground sets: 8 chunks of at least one LDS tile, for enough workgroups
+    // (bfloat16, 4000 x 64, a solo step: 38 us with 4 chunks, 31 with 8, 33 with
+    // 16). More cost a batch, which fills the chip with its instances, more than
+    // they save a solo run: each chunk loads its candidates and adds up its sums
+    // again (16 of 4000: 81, 88 and 105 us a tick). Float32 below 2048 points: 4,
+    // where the solo launch has 32-candidate workgroups (1000 x 16: solo 19 us a
+    // step with 4, 18 with 8; a batch of 64: 48 and 57 us a tick); L1 joins no
+    // batch and has no such workgroups.
     const int64_t most = n_pad / (dt == EBC_DT_F32 ? kGainsVTile : 256);
-    v = v < 16 ? v : 16;
-    v = v < most ? v : most;
-    const int64_t least = call_splits_for(n_pad, k_pad, dt);
-    return int32_t(v > least ? v : least);
+    const int64_t v = dt == EBC_DT_F32 && metric == 0 && tiles < 16 ? 4 : 8;
+    return int32_t(v < most ? v : most);
 }
 
 int32_t call_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt) {
     const int64_t tiles = n_pad / kGainsCandTile;
-    if (wide_rows(k_pad) || tiles >= 64) return v_splits_for(n_pad, k_pad, dt);
+    if (wide_rows(k_pad) || tiles >= 64) return v_splits_for(n_pad, k_pad, dt, 0);
     return tiles >= 16 ? 4 : 1;
 }
 
@@ -172,7 +177,9 @@ Layout layout(int64_t n, int32_t d, ebc_dtype dt) {
     L.off_ha = take(size_t(np) * sizeof(float));
     L.off_hm = take(size_t(np) * sizeof(float));
     L.off_sel = take(size_t(np));
-    L.off_part = take(size_t(v_splits_for(np, kp, dt)) * np * sizeof(double));
+    // (room for either metric: no size query knows it)
+    const int32_t chunks = std::max(v_splits_for(np, kp, dt, 0), v_splits_for(np, kp, dt, dt == EBC_DT_F32 ? 1 : 0));
+    L.off_part = take(size_t(chunks) * np * sizeof(double));
     L.off_gsum = take(size_t(np) * sizeof(double));
     L.off_bmax = take(size_t(nb) * sizeof(double));
     L.off_barg = take(size_t(nb) * sizeof(int32_t));

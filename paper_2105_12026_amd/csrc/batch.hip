@@ -28,7 +28,8 @@ struct ebc_batch {
     int64_t total_rows;
     bool long_rows;  // some instance has rows longer than kNarrowMaxK
     std::vector<GainsBucket> buckets;
-    std::vector<char> lists;  // instances that score lists after their first step
+    std::vector<char> lists;  // instances that score lists after their first step, in runs of `list_ticks`
+    int32_t list_ticks;
     std::vector<int64_t> h_row_pre, h_wg_pre;
     std::vector<int32_t> h_slot_inst;
     PinnedTables staging;
@@ -40,6 +41,21 @@ struct ebc_batch {
 };
 
 namespace {
+
+// Which instances score lists depends on the datasets and the number of ticks
+// alone (the captured graph is kept by that number).
+void choose_lists(ebc_batch* bt, int32_t ticks) {
+    if (bt->list_ticks == ticks) return;
+    bt->list_ticks = ticks;
+    bt->lists.assign(bt->count, 0);
+    for (GainsBucket& b : bt->buckets) {
+        b.lists = batched_lists_pay(b.key, b.worth, ticks);
+        for (int32_t j = 0; j < b.slots; ++j) {
+            const int32_t i = bt->h_slot_inst[b.slot_begin + j];
+            bt->lists[i] = b.lists && batched_lists_worth(bt->ds[i]) > 0.0;
+        }
+    }
+}
 
 hipError_t enqueue_ticks(ebc_batch* bt, int32_t ticks, hipStream_t s) {
     hipError_t e = launch_reset_batched(bt->d_desc, bt->d_row_pre, bt->count, bt->total_rows, s);
@@ -104,20 +120,19 @@ ebc_status ebc_batch_create(ebc_dataset* const* ds, int32_t count, void* workspa
         const int32_t key = gains_bucket(ds[i]);
         if (std::find(keys.begin(), keys.end(), key) == keys.end()) keys.push_back(key);
     }
+    bt->lists.assign(count, 0);
     bt->h_slot_inst.clear();
     bt->h_wg_pre.clear();
-    bt->lists.assign(count, 0);
     for (int32_t key : keys) {
         GainsBucket b{};
         b.key = key;
         b.slot_begin = int32_t(bt->h_slot_inst.size());
         b.pre_off = int32_t(bt->h_wg_pre.size());
         int64_t acc = 0;
-        double worth = 0.0;
         bt->h_wg_pre.push_back(0);
         for (int32_t i = 0; i < count; ++i) {
             if (gains_bucket(ds[i]) != key) continue;
-            worth += greedy_lists_worth(ds[i]);
+            b.worth += batched_lists_worth(ds[i]);
             const int64_t tile = gains_cand_tile(ds[i]);
             acc += (ds[i]->n_pad + tile - 1) / tile * ds[i]->v_splits;
             bt->h_slot_inst.push_back(i);
@@ -125,11 +140,6 @@ ebc_status ebc_batch_create(ebc_dataset* const* ds, int32_t count, void* workspa
         }
         b.slots = int32_t(bt->h_slot_inst.size()) - b.slot_begin;
         b.total_wgs = acc;
-        b.lists = worth > 1.0;
-        for (int32_t j = 0; j < b.slots; ++j) {
-            const int32_t i = bt->h_slot_inst[b.slot_begin + j];
-            bt->lists[i] = b.lists && greedy_lists_worth(ds[i]) > 0.0;
-        }
         bt->buckets.push_back(b);
     }
     if (bt->staging.init(L.total) != hipSuccess) {
@@ -165,6 +175,7 @@ ebc_status ebc_greedy_batched(ebc_batch* bt, const int32_t* k, int32_t* const* s
         ticks = std::max(ticks, k[i]);
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    choose_lists(bt, ticks);
     // descriptors and block maps, staged in pinned memory, one copy
     hipError_t e = hipSuccess;
     char* h = bt->staging.acquire(&e);

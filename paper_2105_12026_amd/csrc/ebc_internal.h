@@ -114,7 +114,7 @@ struct InstDesc {
     int32_t t0;                      // steps already done: a batched tick t runs step t0 + t
     int32_t dt, variant;
     int32_t metric;                  // dissimilarity: 0 squared Euclidean, 1 L1
-    int32_t lazy;                    // steps after the first re-evaluate only candidates that can win (lazy.h)
+    int32_t lazy;                    // 1: steps after the first score lists (lazy.h); 2: none does yet, but one may
     int64_t chunk;                   // ground-set chunk of the gains kernel
     int32_t* sel;
     double* f;
@@ -310,11 +310,13 @@ struct PinnedTables {
 // Host helpers shared by the solo and batched paths.
 int64_t gains_chunk(const ebc_dataset* ds, int32_t splits);
 int64_t gains_cand_tile(const ebc_dataset* ds);
-// How far scoring lists (lazy.h) pays in greedy steps of this dataset: above 1
-// it does when the dataset runs alone; 0 if it cannot.
-double greedy_lists_worth(const ebc_dataset* ds);
-// Steps of a greedy run of k steps, alone, that score lists.
+// Steps of a greedy run of k steps, alone, that score lists (lazy.h).
 int32_t greedy_list_steps(const ebc_dataset* ds, int32_t k);
+// What an instance adds to the worth of lists in its bucket of a batch (0: it
+// scores every candidate there), and whether a bucket of that worth scores
+// lists in runs of at most k steps.
+double batched_lists_worth(const ebc_dataset* ds);
+bool batched_lists_pay(int32_t bucket, double worth, int32_t k);
 int32_t gains_bucket(const ebc_dataset* ds);  // datasets with equal keys share a batched gains launch
 void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double* gain, InstDesc* out);
 
@@ -381,7 +383,8 @@ struct GainsBucket {
     int32_t slot_begin, slots;  // slots [slot_begin, slot_begin + slots) of slot_inst
     int32_t pre_off;            // its prefix array starts at wg_pre[pre_off] (slots + 1 entries)
     int64_t total_wgs;
-    bool lists;                 // some of its instances score lists after their first step
+    double worth;               // of lists, summed over its instances (batched_lists_worth)
+    bool lists;                 // those of them worth it score lists after their first step
 };
 // One tick of a batch. full: some instance scores all of its candidates in
 // it; lists: some instance scores a list. long_rows: some instance has rows

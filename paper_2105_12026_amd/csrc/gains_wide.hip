@@ -262,14 +262,14 @@ __global__ void __launch_bounds__(256) k_gains_matrix(InstDesc c) {
     gains_matrix_row(c, int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6));
 }
 
-// Batched: row block on blockIdx.x, 16 candidates of it on blockIdx.y.
+// Batched: row block on blockIdx.x, 4 candidates of it on blockIdx.y.
 __global__ void __launch_bounds__(256)
 kb_gains_matrix(const InstDesc* __restrict__ descs, const int64_t* __restrict__ row_pre, int32_t count, int32_t t) {
     const int i = find_slot(row_pre, count, blockIdx.x);
     const InstDesc c = descs[i];
     if (c.t0 + t >= c.k || !matrix_step(c, c.t0 + t)) return;
-    const int64_t row = (int64_t(blockIdx.x) - row_pre[i]) * kBlock + blockIdx.y * 16 + (threadIdx.x >> 6) * 4;
-    for (int j = 0; j < 4; ++j) gains_matrix_row(c, row + j);
+    const int64_t row = (int64_t(blockIdx.x) - row_pre[i]) * kBlock + blockIdx.y * 4 + (threadIdx.x >> 6);
+    gains_matrix_row(c, row);
 }
 
 template <int DT>
@@ -352,7 +352,7 @@ hipError_t launch_gains_matrix(const InstDesc& c, hipStream_t s) {
 
 hipError_t launch_gains_matrix_batched(const InstDesc* descs, const int64_t* row_pre, int32_t count,
                                        int64_t total_rows, int32_t t, hipStream_t s) {
-    hipLaunchKernelGGL(kb_gains_matrix, dim3(unsigned(total_rows), kBlock / 16), dim3(256), 0, s, descs, row_pre, count, t);
+    hipLaunchKernelGGL(kb_gains_matrix, dim3(unsigned(total_rows), kBlock / 4), dim3(256), 0, s, descs, row_pre, count, t);
     return hipGetLastError();
 }
 

@@ -160,7 +160,7 @@ __device__ inline GainsArgs list_args(const InstDesc& c, int32_t part, int32_t c
 }
 
 // Does step `step` of the instance score a list?
-__host__ __device__ inline bool list_step(const InstDesc& c, int32_t step) { return c.lazy != 0 && step > 0; }
+__host__ __device__ inline bool list_step(const InstDesc& c, int32_t step) { return c.lazy == 1 && step > 0; }
 
 // Batched list launches: the workgroups walk the (tile, chunk) pairs of every
 // instance of a bucket that is at a list step. The pairs of 64 instances at a

@@ -46,17 +46,16 @@ int64_t gains_cand_tile(const ebc_dataset* ds) {
 
 // Lists need room in the partial sums (lazy.h) and the short-row kernels.
 //
-// A list step launches five kernels more than one that scores everything; it
-// pays once the launch over all candidates takes longer than that. Measured
-// us per greedy step, all candidates / lists: float32 d = 16: 8192 points
-// 55 / 57, 12000 83 / 60; d = 100: 4096 58 / 70, 6000 97 / 75; BF16 d = 64:
-// 12000 62 / 64, 16384 75 / 69; FP16 d = 100: 8192 53 / 62, 12000 75 / 65;
-// FP8 d = 33: 16384 82 / 83, 24000 96 / 84; L1 d = 20: 4096 45 / 59, 6000
-// 76 / 60. The line is drawn on the time of the launch over all candidates:
-// n_pad^2 pairs at the products a pair costs plus a constant for its clamp
-// and sum and for the launch's unfilled rounds. Returned is that time in
-// units of the line: above 1 lists are faster for a dataset alone, and for a
-// bucket of a batch (which shares its launches) where the sum is above 1.
+// A list step launches three kernels more than one that scores everything (six
+// more below 4096 points); it pays once the launch over all candidates takes
+// longer than that. Measured us per step of a run of 20, all candidates / lists:
+// float32 d = 16: 8500 points 58 / 57, 14000 92 / 62; d = 100: 4200 62 / 65, 6000
+// 92 / 68; BF16 d = 64: 12800 60 / 64, 20000 89 / 66; FP16 d = 100: 11000 64 / 65,
+// 15000 83 / 70; FP8 d = 33: 16000 69 / 76, 20000 78 / 74; L1 d = 50: 3500 71 / 69,
+// 6000 136 / 74. The line is drawn on the time of the launch over all candidates:
+// n_pad^2 pairs at the products a pair costs plus a constant for its clamp and
+// sum and for the launch's unfilled rounds. Returned is that time in units of
+// about 30 us.
 double greedy_lists_worth(const ebc_dataset* ds) {
     if (wide_rows(ds->k_pad) || ds->v_splits < 4) return 0.0;
     const double pairs = double(ds->n_pad) * double(ds->n_pad);
@@ -66,8 +65,32 @@ double greedy_lists_worth(const ebc_dataset* ds) {
     return pairs * (products + 27) / 1.5e10;
 }
 
+// The first list is long (its heads are a weak bound yet) and its step costs a
+// full one and more, which the later ones must win back. BF16, 30000 x 64, all
+// candidates / lists: 2 steps 322 / 388 us, 3 steps 478 / 454, 5 steps 790 / 591;
+// 20000 x 64: 3 steps 284 / 307, 5 steps 456 / 424.
+static bool lists_pay(double worth, double line, int32_t k) { return k > 2 && worth > line * (1.0 + 1.6 / (k - 2)); }
+
 int32_t greedy_list_steps(const ebc_dataset* ds, int32_t k) {
-    return k > 0 && greedy_lists_worth(ds) > 1.0 ? k - 1 : 0;
+    return lists_pay(greedy_lists_worth(ds), ds->dt == EBC_DT_F32 ? 1.1 : 1.4, k) ? k - 1 : 0;
+}
+
+// In a batch the list launches of a bucket are shared, but walk its instances
+// with a fixed number of workgroups, and every small instance adds its heads.
+// Measured us a tick, all candidates / lists, by the worth of an instance:
+// 200 of 2000 x 64 BF16 (0.025) 251 / 405, 25 of 4000 x 64 BF16 (0.10) 146 / 108;
+// 200 of 2000 x 33 FP8 (0.016) 270 / 502, 25 of 4000 (0.066) 140 / 131; 200 of
+// 2000 x 128 FP16 (0.043) 377 / 500; 200 of 2000 x 16 float32 (0.06) 445 / 340. By
+// the sum: FP16, 4 of 6000 x 128 (1.6) 80 / 102; BF16, 3 of 9000 x 64 (1.5) 77 / 81,
+// 11 (5.7) 175 / 111; FP8, 16 of 6000 x 33 (2.4) 138 / 131; float32, 4 of 6000 x 16
+// (2.1) 82 / 69.
+double batched_lists_worth(const ebc_dataset* ds) {
+    const double worth = greedy_lists_worth(ds);
+    return worth >= (ds->dt == EBC_DT_F32 ? 0.05 : 0.1) ? worth : 0.0;
+}
+
+bool batched_lists_pay(int32_t bucket, double worth, int32_t k) {
+    return lists_pay(worth, bucket / 100000 == EBC_DT_F32 ? 1.2 : 2.0, k);
 }
 
 int32_t gains_bucket(const ebc_dataset* ds) {
@@ -145,12 +168,12 @@ int32_t v_splits_for(int64_t n_pad, int32_t k_pad, ebc_dtype dt, int32_t metric)
     // (bfloat16, 4000 x 64, a solo step: 38 us with 4 chunks, 31 with 8, 33 with
     // 16). More cost a batch, which fills the chip with its instances, more than
     // they save a solo run: each chunk loads its candidates and adds up its sums
-    // again (16 of 4000: 81, 88 and 105 us a tick). Float32 below 2048 points: 4,
-    // where the solo launch has 32-candidate workgroups (1000 x 16: solo 19 us a
-    // step with 4, 18 with 8; a batch of 64: 48 and 57 us a tick); L1 joins no
-    // batch and has no such workgroups.
+    // again (16 of 4000: 81, 88 and 105 us a tick). Below 2048 points 4 chunks
+    // (float32 1000 x 16: solo, with 32-candidate workgroups, 19 us a step with 4,
+    // 18 with 8; a batch of 64: 48 and 57 us a tick), but for L1, which joins no
+    // batch (1000 x 20: 24 us with 4, 20 with 8).
     const int64_t most = n_pad / (dt == EBC_DT_F32 ? kGainsVTile : 256);
-    const int64_t v = dt == EBC_DT_F32 && metric == 0 && tiles < 16 ? 4 : 8;
+    const int64_t v = tiles < 16 && metric == 0 ? 4 : 8;
     return int32_t(v < most ? v : most);
 }
 

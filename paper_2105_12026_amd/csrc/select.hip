@@ -461,7 +461,7 @@ __device__ void pick_body(const InstDesc& c, int32_t t) {
 
 // Estimate of candidate v's present gain, and the block's best one: the gain
 // it had when it was last scored, times what is left of its own minimum since
-// (old: m_v before this step, which is what step 0 scored every candidate
+// (old: m_v before this step, which is what a full step scores every candidate
 // with). The best of each block goes to bmax / barg.
 __device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, int cs, double old, double mv,
                                     double* red, int* ri) {
@@ -469,7 +469,7 @@ __device__ void block_best_estimate(const InstDesc& c, int64_t blk, int32_t t, i
     const int64_t v = blk * kBlock + threadIdx.x;
     float* __restrict__ lm = list_m(c);
     float m_scored = float(old);
-    if (t == 0)
+    if (!list_step(c, t))
         lm[v] = m_scored;
     else
         m_scored = lm[v];

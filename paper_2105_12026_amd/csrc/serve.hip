@@ -89,7 +89,8 @@ struct Request {
     std::vector<float> xh;
     int state = kQueued;
     int32_t t = 0;  // steps done
-    bool lists = false;  // steps after the first score lists (lazy.h)
+    double worth = 0.0;  // of scoring lists (lazy.h); 0: never
+    bool lists = false;  // its steps after the first score lists while the present requests are active
     size_t off = 0, bytes = 0;
     float* xd = nullptr;
     void* ws = nullptr;
@@ -182,8 +183,8 @@ ebc_status admit(ebc_server* sv, Request* r) {
     // gains tile variant from the autotuner's table (results do not depend on it)
     const int32_t v = tuned_variant(r->ds);
     if (v >= 0) r->ds->variant = v;
+    r->worth = r->k > 2 ? batched_lists_worth(r->ds) : 0.0;
     r->state = kActive;
-    r->lists = greedy_lists_worth(r->ds) > 0.25;  // a tick's launches are shared by several requests
     r->t = 0;
     r->t_admit = now_s();
     return EBC_OK;
@@ -212,7 +213,7 @@ void rebuild_tables(ebc_server* sv) {
         for (int32_t i = 0; i < count; ++i) {
             const ebc_dataset* ds = sv->active[i]->ds;
             if (gains_bucket(ds) != key) continue;
-            b.lists |= sv->active[i]->lists;
+            b.worth += sv->active[i]->worth;
             const int64_t tile = gains_cand_tile(ds);
             acc += (ds->n_pad + tile - 1) / tile * ds->v_splits;
             sv->h_slot.push_back(i);
@@ -220,6 +221,11 @@ void rebuild_tables(ebc_server* sv) {
         }
         b.slots = int32_t(sv->h_slot.size()) - b.slot_begin;
         b.total_wgs = acc;
+        b.lists = batched_lists_pay(key, b.worth, INT32_MAX);
+        for (int32_t j = b.slot_begin; j < b.slot_begin + b.slots; ++j) {
+            Request* r = sv->active[sv->h_slot[j]];
+            r->lists = b.lists && r->worth > 0.0;
+        }
         sv->buckets.push_back(b);
     }
 }
@@ -361,7 +367,8 @@ ebc_status ebc_server_step(ebc_server* sv, int32_t* completed) {
     for (int32_t i = 0; i < count; ++i) {
         Request* r = sv->active[i];
         fill_desc(r->ds, r->k, r->sel_d, r->f_d, r->gain_d, &hd[i]);
-        hd[i].lazy = r->lists;
+        // others keep what a list needs: one may start when requests join
+        hd[i].lazy = r->lists ? 1 : (r->worth > 0.0 ? 2 : 0);
         hd[i].t0 = r->t;
     }
     memcpy(h + sv->tl.row_pre, sv->h_row_pre.data(), sv->h_row_pre.size() * sizeof(int64_t));

@@ -65,11 +65,11 @@ def full_run(t, k, dtype, dist="sqeuclidean"):
 SOLO = [("near", 12003, 16, 20, "f32", "sqeuclidean", 1025), ("near", 9217, 100, 20, "f32", "sqeuclidean", 1025),
         ("near", 20011, 64, 20, "bf16", "sqeuclidean", 1025), ("near", 16500, 100, 20, "f16", "sqeuclidean", 1025),
         ("near", 30011, 33, 20, "fp8", "sqeuclidean", 1025), ("near", 10007, 50, 20, "f32", "l1", 1025),
-        ("tied", 12288, 22, 10, "f32", "sqeuclidean", 1023), ("tied", 18432, 28, 12, "bf16", "sqeuclidean", 1023),
-        ("tied", 18432, 28, 12, "f16", "sqeuclidean", 1023), ("tied", 18432, 28, 12, "fp8", "sqeuclidean", 1023),
+        ("tied", 12288, 22, 10, "f32", "sqeuclidean", 1023), ("tied", 21504, 31, 12, "bf16", "sqeuclidean", 1023),
+        ("tied", 21504, 31, 12, "f16", "sqeuclidean", 1023), ("tied", 21504, 31, 12, "fp8", "sqeuclidean", 1023),
         ("few", 11001, 20, 12, "f32", "sqeuclidean", 1025), ("few", 26003, 128, 12, "fp8", "sqeuclidean", 1025),
         ("few", 9001, 30, 12, "f32", "l1", 1025), ("curves", 24001, 33, 20, "fp8", "sqeuclidean", 0),
-        ("mixture", 13009, 64, 30, "bf16", "sqeuclidean", 0), ("mixture", 33001, 3, 25, "f32", "sqeuclidean", 0)]
+        ("mixture", 17001, 64, 30, "bf16", "sqeuclidean", 0), ("mixture", 33001, 3, 25, "f32", "sqeuclidean", 0)]
 
 
 @pytest.mark.parametrize("data,n,d,k,dtype,dist,window", SOLO)
@@ -107,7 +107,7 @@ def test_graph_replays(data, n, d, dtype):
         ds.marginal_gains()
 
 
-@pytest.mark.parametrize("n,d,dtype,dist", [(9217, 24, "f32", "sqeuclidean"), (15003, 64, "bf16", "sqeuclidean"),
+@pytest.mark.parametrize("n,d,dtype,dist", [(10241, 24, "f32", "sqeuclidean"), (17003, 64, "bf16", "sqeuclidean"),
                                             (8003, 24, "f32", "l1")])
 def test_calls_between_runs(n, d, dtype, dist):
     """Gains asked for between runs use buffers of the runs."""
@@ -125,7 +125,7 @@ def test_calls_between_runs(n, d, dtype, dist):
 MIXED = {"bf16": [("mixture", 30000, 64), ("near", 1024, 64), ("mixture", 2305, 60), ("near", 9000, 64)],
          "f32": [("mixture", 12000, 96), ("near", 700, 96), ("mixture", 4097, 90), ("near", 5003, 96)],
          "fp8": [("curves", 30000, 64), ("near", 1500, 50), ("near", 12345, 33), ("normal", 6000, 64)],
-         "f16": [("near", 16000, 32), ("near", 7000, 32), ("few", 3000, 30), ("mixture", 11000, 20)]}
+         "f16": [("near", 30000, 32), ("near", 7000, 32), ("few", 3000, 30), ("mixture", 11000, 20)]}
 
 
 @pytest.mark.parametrize("dtype", sorted(MIXED))
@@ -148,13 +148,16 @@ def test_mixed_batch(dtype, graph):
 
 @pytest.mark.parametrize("dtype", sorted(MIXED))
 def test_mixed_requests(dtype):
-    """Served alone and together."""
+    """Served alone and together: lists start, and end, while a request runs."""
     xs = [points(*c, i) for i, c in enumerate(MIXED[dtype])]
     ks = [11, 7, 14, 12]
     want = [full_run(torch.from_numpy(x).cuda(), k, dtype)[0] for x, k in zip(xs, ks)]
     for alone in (False, True):
         sv = ebc.Server(1 << 30, max_slots=1 if alone else 4)
-        ids = [sv.submit(x, k, dtype=dtype) for x, k in zip(xs, ks)]
+        ids = []
+        for x, k in zip(xs[::-1], ks[::-1]):  # the large one joins last
+            ids.insert(0, sv.submit(x, k, dtype=dtype))
+            sv.step()
         for _ in range(sum(ks) + 8):
             sv.step()
         for rid, w in zip(ids, want):

@@ -224,12 +224,12 @@ __device__ __forceinline__ void gains_wide_body(const GainsArgs& ga, int32_t k_p
 // the kernel that multiplies the rows (lane l stands for the points l of a
 // chunk's 64-point tiles), so that both give the same bits. 4 bytes a pair are
 // what bounds it, with the sums' lane exchanges: 1000 points (4 MB, in the L2s)
-// 92 -> 3.9 us a step against multiplying rows of 3524 values again (one float32
+// 92 -> 4 us a step against multiplying rows of 3524 values again (one float32
 // sum a lane over all chunks: 3.2 us, but other sums than a run without a matrix).
 __device__ __forceinline__ void gains_matrix_row(const InstDesc& c, int64_t row) {
     const int lane = threadIdx.x & 63;
-    const float* __restrict__ e = c.b.pairs + row * c.n_pad + lane;
-    const float* __restrict__ hm = c.b.hm + lane;
+    const float* __restrict__ e = c.b.pairs + row * c.n_pad;  // row: the same for the wave
+    const float* __restrict__ hm = c.b.hm;
     float acc[16];  // chunks; a data set with a matrix has at most 16
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
@@ -240,7 +240,7 @@ __device__ __forceinline__ void gains_matrix_row(const InstDesc& c, int64_t row)
             const int64_t v = i * c.chunk + o;
             const bool in = v < c.n_pad;
             const int64_t at = in ? v : 0;
-            const float pair = e[at], hv = hm[at];
+            const float pair = (e + at)[lane], hv = (hm + at)[lane];
             const float h = in ? hv : 0.0f;  // past the end: a term of 0
             acc[i] += __builtin_amdgcn_fmed3f(pair + h, 0.0f, h);
         }
@@ -259,7 +259,7 @@ __device__ __forceinline__ void gains_matrix_row(const InstDesc& c, int64_t row)
 }
 
 __global__ void __launch_bounds__(256) k_gains_matrix(InstDesc c) {
-    gains_matrix_row(c, int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6));
+    gains_matrix_row(c, int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // Batched: row block on blockIdx.x, 4 candidates of it on blockIdx.y.
@@ -268,7 +268,8 @@ kb_gains_matrix(const InstDesc* __restrict__ descs, const int64_t* __restrict__ 
     const int i = find_slot(row_pre, count, blockIdx.x);
     const InstDesc c = descs[i];
     if (c.t0 + t >= c.k || !matrix_step(c, c.t0 + t)) return;
-    const int64_t row = (int64_t(blockIdx.x) - row_pre[i]) * kBlock + blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int64_t row = (int64_t(blockIdx.x) - row_pre[i]) * kBlock + blockIdx.y * 4 +
+                        __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     gains_matrix_row(c, row);
 }
 

@@ -848,11 +848,11 @@ __device__ __forceinline__ int window_slices(const InstDesc& c, int W) {
     return s < 16 ? s : 16;
 }
 
-// Does the window's pass 1 hold the pick's distances (window position rank), in
-// the slices of the update? m_v must not depend on the size of the window.
+// Does the window's pass 1 hold the pick's distances (window position rank)?
+// Their slices, and so the rounding of m_v, follow the window's size, which is
+// the same in every run: the gains of long rows are, bit for bit (gains_wide.hip).
 __device__ __forceinline__ bool window_has_slices(const InstDesc& c, int rank) {
-    const int W = c.b.state->window_count;
-    return rank >= 0 && W <= split_window(c) && window_slices(c, W) == update_slices(c);
+    return rank >= 0 && c.b.state->window_count <= split_window(c);
 }
 
 // m_v update from the slice sums of the pick (pass 2), per-block sums of m_v.
@@ -861,8 +861,11 @@ __device__ void update_split_body(const InstDesc& c, int64_t blk, int cs, int ra
     __shared__ double red[kBlock];
     const Buffers& b = c.b;
     InstDesc w = c;
-    const int S = update_slices(c);
-    if (window_has_slices(c, rank)) w.b.part = b.part + int64_t(S) * rank * c.n_pad;
+    int S = update_slices(c);
+    if (window_has_slices(c, rank)) {
+        S = window_slices(c, b.state->window_count);
+        w.b.part = b.part + int64_t(S) * rank * c.n_pad;
+    }
     const int64_t v = blk * kBlock + threadIdx.x;
     double mv = 0.0;
     if (v < c.n) {
@@ -1044,12 +1047,13 @@ __device__ void list_build_body(const InstDesc& c, int64_t blk) {
 // index or rank order, so nothing depends on the order of `rows`. perm
 // non-null: `rows` holds slots of the grouped order. count: this block counts
 // the window in the statistics (several blocks may make the same window).
-// lower non-null (sums of other chunks than those of a step that scores all):
-// where more than kWindowMax candidates reach the window or come as near as its
-// rounding, no window is made, *lower is the gain they reach and false returned.
+// rounded (sums of other chunks than those of a step that scores all): where
+// more than kWindowMax candidates reach the window or come as near as its
+// rounding, no window is made, and the gain that they reach is returned;
+// otherwise infinity.
 template <int NT>
-__device__ bool window_body(const InstDesc& c, const int32_t* __restrict__ rows, const int32_t* __restrict__ perm,
-                            int len, double* lower, bool count) {
+__device__ double window_body(const InstDesc& c, const int32_t* __restrict__ rows, const int32_t* __restrict__ perm,
+                              int len, bool rounded, bool count) {
     __shared__ WindowEntry list[kWindowCap];
     __shared__ int hist[256];
     __shared__ int close;
@@ -1087,11 +1091,12 @@ __device__ bool window_body(const InstDesc& c, const int32_t* __restrict__ rows,
     const int first = ib;
     const double thr = window_threshold(gmax, b.state);
     auto inside = [&](double g) { return g >= thr && g > -INFINITY; };
-    const double low = lower ? thr - list_slack(c, gmax) : thr;
+    const double low = rounded ? thr - list_slack(c, gmax) : thr;
+    int reach = 0;  // lane 0, which makes the most passes, has those of its wave
     for (int i = tid; i < len; i += NT) {
         const int r = i == tid ? r0 : row_at(i);
         const double g = i == tid ? g0 : b.gsum[r];
-        if (lower && g >= low && g > -INFINITY) atomicAdd(&close, 1);
+        if (rounded) reach += __popcll(__builtin_amdgcn_ballot_w64(g >= low && g > -INFINITY));
         if (!inside(g)) continue;
         const int at = atomicAdd(&found, 1);
         if (at >= kWindowCap) continue;
@@ -1099,13 +1104,11 @@ __device__ bool window_body(const InstDesc& c, const int32_t* __restrict__ rows,
         list[at].idx = r;
         list[at].pad = 0;
     }
+    if (rounded && lane == 0) atomicAdd(&close, reach);
     __syncthreads();
     const int total = found, near = close;
     __syncthreads();  // every wave has read it: found is reused below
-    if (lower && near > kWindowMax) {
-        *lower = low;
-        return false;
-    }
+    if (rounded && near > kWindowMax) return low;
     if (total <= kWindowCap) {
         for (int i = tid; i < total; i += NT) {
             int rank = 0;
@@ -1183,7 +1186,7 @@ __device__ bool window_body(const InstDesc& c, const int32_t* __restrict__ rows,
         if (count && total > b.state->window_max) b.state->window_max = total;
         if (count && total > kWindowCap) b.state->window_overflow += 1;
     }
-    return true;
+    return INFINITY;
 }
 
 // The window out of the list, or the candidates of the recount (lazy.h).
@@ -1192,9 +1195,9 @@ __device__ void list_window_body(const InstDesc& c) {
     const Buffers& b = c.b;
     const int len = b.state->list_len, tid = threadIdx.x;
     int32_t* rows = list_rows(c);
-    double lower;
     if (tid == 0) kept = 0;
-    if (!window_body<kSelThreads>(c, rows, nullptr, len, list_full_cut(c, len) ? nullptr : &lower, true))
+    const double lower = window_body<kSelThreads>(c, rows, nullptr, len, !list_full_cut(c, len), true);
+    if (lower < INFINITY)
         for (int i0 = 0; i0 < len; i0 += kSelThreads) {
             const int row = i0 + tid < len ? rows[i0 + tid] : -1;
             const double g = row >= 0 ? b.gsum[row] : -INFINITY;
@@ -1222,7 +1225,7 @@ __device__ void list_exact_body(const InstDesc& c, bool count) {
         b.gsum[row] = b.selected[row] ? -INFINITY : s;
     }
     __syncthreads();
-    window_body<kBlock>(c, rows, b.perm, len, nullptr, count);
+    window_body<kBlock>(c, rows, b.perm, len, false, count);
     __syncthreads();
 }
 
@@ -1254,7 +1257,7 @@ __device__ void select_small_body(const InstDesc& c, int32_t t, int32_t splits) 
         for (int s = 0; s < splits; ++s) g += b.part[int64_t(s) * c.n_pad + i];
         b.gsum[i] = b.selected[i] || i == prev ? -INFINITY : g;
     }
-    window_body<kSelThreads>(c, nullptr, nullptr, int(c.n_pad), nullptr, true);  // each thread reads the sums it wrote
+    window_body<kSelThreads>(c, nullptr, nullptr, int(c.n_pad), false, true);  // each thread reads the sums it wrote
 }
 
 __device__ int pick_small(const InstDesc& c, int32_t t, int64_t blk, int* rank) {

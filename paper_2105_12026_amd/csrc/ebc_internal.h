@@ -351,16 +351,18 @@ __host__ __device__ inline int32_t gain_splits(const InstDesc& c, int32_t step) 
     return matrix_step(c, step) ? 1 : c.v_splits;
 }
 
-// Batched launches over a device table of descriptors (see ebc_batch).
+// Batched launches over a device table of descriptors (see ebc_batch): workgroups
+// first .. first + wgs - 1 of the block map wg_pre.
 hipError_t launch_gains_f32_batched(int32_t k_pad, bool trim, const InstDesc* descs, const int32_t* slot_inst,
-                                    const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t,
+                                    const int64_t* wg_pre, int32_t slots, int64_t first, int64_t wgs, int32_t t,
                                     hipStream_t s);
 hipError_t launch_gains_lp_batched(int32_t dt, int32_t kc, int32_t variant, const InstDesc* descs,
-                                   const int32_t* slot_inst, const int64_t* wg_pre, int32_t slots, int64_t total_wgs,
+                                   const int32_t* slot_inst, const int64_t* wg_pre, int32_t slots, int64_t first, int64_t wgs,
                                    int32_t t, hipStream_t s);
 hipError_t launch_gains_wide_batched(int32_t dt, int32_t ksplit, const InstDesc* descs, const int32_t* slot_inst,
-                                     const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t,
+                                     const int64_t* wg_pre, int32_t slots, int64_t first, int64_t wgs, int32_t t,
                                      hipStream_t s);
+// ... all of a bucket's
 hipError_t launch_gains_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst,
                                 const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t, hipStream_t s);
 // ... of the heads (part 0), lists (1) or recounts (2) of the instances at a list step (lazy.h)

@@ -421,11 +421,12 @@ __global__ void __launch_bounds__(256) k_gains_f32(GainsArgs ga) {
 template <int KP, bool TRIM>
 __global__ void __launch_bounds__(256)
 kb_gains_f32(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst,
-             const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
-    const int j = find_slot(wg_pre, slots, blockIdx.x);
+             const int64_t* __restrict__ wg_pre, int32_t slots, int64_t first, int32_t t) {
+    const int64_t bid = first + blockIdx.x;
+    const int j = find_slot(wg_pre, slots, bid);
     const InstDesc c = descs[slot_inst[j]];
     if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
-    gains_f32_body<KP, TRIM>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
+    gains_f32_body<KP, TRIM>(gains_args(c, nullptr, c.n_pad), bid - wg_pre[j]);
 }
 
 // Heads or list (lazy.h): the workgroups walk its (tile, chunk) pairs.
@@ -528,17 +529,17 @@ hipError_t launch_gains_f32_list(const InstDesc& c, int32_t part, hipStream_t s)
 
 // trim: every instance of the bucket has d <= k_pad - 4 (the bucket key says so)
 hipError_t launch_gains_f32_batched(int32_t k_pad, bool trim, const InstDesc* descs, const int32_t* slot_inst,
-                                    const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t,
+                                    const int64_t* wg_pre, int32_t slots, int64_t first, int64_t wgs, int32_t t,
                                     hipStream_t s) {
     switch (k_pad) {
 #define EBC_KP(K)                                                                                             \
     case K:                                                                                                   \
         if (trim)                                                                                             \
-            hipLaunchKernelGGL((kb_gains_f32<K, true>), dim3(unsigned(total_wgs)), dim3(256), 0, s, descs,    \
-                               slot_inst, wg_pre, slots, t);                                                  \
+            hipLaunchKernelGGL((kb_gains_f32<K, true>), dim3(unsigned(wgs)), dim3(256), 0, s, descs,    \
+                               slot_inst, wg_pre, slots, first, t);                                                  \
         else                                                                                                  \
-            hipLaunchKernelGGL((kb_gains_f32<K, false>), dim3(unsigned(total_wgs)), dim3(256), 0, s, descs,   \
-                               slot_inst, wg_pre, slots, t);                                                  \
+            hipLaunchKernelGGL((kb_gains_f32<K, false>), dim3(unsigned(wgs)), dim3(256), 0, s, descs,   \
+                               slot_inst, wg_pre, slots, first, t);                                                  \
         break;
         EBC_F32_KPS(EBC_KP)
 #undef EBC_KP

@@ -733,11 +733,12 @@ __global__ void __launch_bounds__(256) k_gains_lp_sp(GainsArgs ga) {
 template <int DT, int KC, int CB, int VTS>
 __global__ void __launch_bounds__(256)
 kb_gains_lp_sp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst,
-               const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
-    const int j = find_slot(wg_pre, slots, blockIdx.x);
+               const int64_t* __restrict__ wg_pre, int32_t slots, int64_t first, int32_t t) {
+    const int64_t bid = first + blockIdx.x;
+    const int j = find_slot(wg_pre, slots, bid);
     const InstDesc c = descs[slot_inst[j]];
     if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
-    gains_lp_sp_body<DT, KC, CB, VTS>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
+    gains_lp_sp_body<DT, KC, CB, VTS>(gains_args(c, nullptr, c.n_pad), bid - wg_pre[j]);
 }
 
 // Ring-stage width of the interleaved variant by row length (16-byte units
@@ -780,11 +781,12 @@ __global__ void __launch_bounds__(512) k_gains_lp_pp(GainsArgs ga) {
 template <int DT, int KC, int CB>
 __global__ void __launch_bounds__(512)
 kb_gains_lp_pp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst,
-               const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
-    const int j = find_slot(wg_pre, slots, blockIdx.x);
+               const int64_t* __restrict__ wg_pre, int32_t slots, int64_t first, int32_t t) {
+    const int64_t bid = first + blockIdx.x;
+    const int j = find_slot(wg_pre, slots, bid);
     const InstDesc c = descs[slot_inst[j]];
     if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
-    gains_lp_pp_body<DT, KC, CB>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
+    gains_lp_pp_body<DT, KC, CB>(gains_args(c, nullptr, c.n_pad), bid - wg_pre[j]);
 }
 
 template <int DT, int KC, int CB, bool PIPE>
@@ -797,11 +799,12 @@ __global__ void __launch_bounds__(256) k_gains_lp(GainsArgs ga) {
 template <int DT, int KC, int CB, bool PIPE>
 __global__ void __launch_bounds__(256)
 kb_gains_lp(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst,
-            const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
-    const int j = find_slot(wg_pre, slots, blockIdx.x);
+            const int64_t* __restrict__ wg_pre, int32_t slots, int64_t first, int32_t t) {
+    const int64_t bid = first + blockIdx.x;
+    const int j = find_slot(wg_pre, slots, bid);
     const InstDesc c = descs[slot_inst[j]];
     if (c.t0 + t >= c.k || list_step(c, c.t0 + t)) return;
-    gains_lp_body<DT, KC, CB, PIPE>(gains_args(c, nullptr, c.n_pad), int64_t(blockIdx.x) - wg_pre[j]);
+    gains_lp_body<DT, KC, CB, PIPE>(gains_args(c, nullptr, c.n_pad), bid - wg_pre[j]);
 }
 
 template <int DT, int KC, int CB, bool PIPE>
@@ -918,28 +921,34 @@ hipError_t launch_gains_lp_list(const InstDesc& c, int32_t part, hipStream_t s) 
 
 template <int DT, int KC>
 static void launch_lp_b(int32_t variant, const InstDesc* descs, const int32_t* slot_inst, const int64_t* wg_pre,
-                        int32_t slots, int64_t total_wgs, int32_t t, hipStream_t s) {
-    const dim3 g = dim3(unsigned(total_wgs)), b = dim3(256);
+                        int32_t slots, int64_t first, int64_t wgs, int32_t t, hipStream_t s) {
+    const dim3 g = dim3(unsigned(wgs)), b = dim3(256);
     switch (variant) {
-        case 1: hipLaunchKernelGGL((kb_gains_lp<DT, KC, 4, false>), g, b, 0, s, descs, slot_inst, wg_pre, slots, t); break;
-        case 2: hipLaunchKernelGGL((kb_gains_lp<DT, KC, 2, true>), g, b, 0, s, descs, slot_inst, wg_pre, slots, t); break;
+        case 1:
+            hipLaunchKernelGGL((kb_gains_lp<DT, KC, 4, false>), g, b, 0, s, descs, slot_inst, wg_pre, slots, first, t);
+            break;
+        case 2:
+            hipLaunchKernelGGL((kb_gains_lp<DT, KC, 2, true>), g, b, 0, s, descs, slot_inst, wg_pre, slots, first, t);
+            break;
         case 3:
             hipLaunchKernelGGL((kb_gains_lp_pp<DT, KC, pp_blocks(DT, KC)>), g, dim3(512), 0, s, descs, slot_inst, wg_pre,
-                               slots, t);
+                               slots, first, t);
             break;
         case 4:
             hipLaunchKernelGGL((kb_gains_lp_sp<DT, KC, 2, wide_stage(DT, KC)>), g, b, 0, s, descs, slot_inst, wg_pre,
-                               slots, t);
+                               slots, first, t);
             break;
-        default: hipLaunchKernelGGL((kb_gains_lp<DT, KC, 2, false>), g, b, 0, s, descs, slot_inst, wg_pre, slots, t); break;
+        default:
+            hipLaunchKernelGGL((kb_gains_lp<DT, KC, 2, false>), g, b, 0, s, descs, slot_inst, wg_pre, slots, first, t);
+            break;
     }
 }
 
 hipError_t launch_gains_lp_batched(int32_t dt, int32_t kc, int32_t variant, const InstDesc* descs,
-                                   const int32_t* slot_inst, const int64_t* wg_pre, int32_t slots, int64_t total_wgs,
-                                   int32_t t, hipStream_t s) {
+                                   const int32_t* slot_inst, const int64_t* wg_pre, int32_t slots, int64_t first,
+                                   int64_t wgs, int32_t t, hipStream_t s) {
 #define EBC_LPB(DTV, K) \
-    case K: launch_lp_b<DTV, K>(variant, descs, slot_inst, wg_pre, slots, total_wgs, t, s); break;
+    case K: launch_lp_b<DTV, K>(variant, descs, slot_inst, wg_pre, slots, first, wgs, t, s); break;
     switch (dt) {
         case EBC_DT_BF16:
             switch (kc) {

@@ -288,18 +288,19 @@ __global__ void __launch_bounds__(256) k_gains_wide(GainsArgs ga, int32_t k_pad)
 template <int DT, int KS>
 __global__ void __launch_bounds__(256)
 kb_gains_wide(const InstDesc* __restrict__ descs, const int32_t* __restrict__ slot_inst,
-              const int64_t* __restrict__ wg_pre, int32_t slots, int32_t t) {
-    const int j = find_slot(wg_pre, slots, blockIdx.x);
+              const int64_t* __restrict__ wg_pre, int32_t slots, int64_t first, int32_t t) {
+    const int64_t bid = first + blockIdx.x;
+    const int j = find_slot(wg_pre, slots, bid);
     const InstDesc c = descs[slot_inst[j]];
     if (c.t0 + t >= c.k || matrix_step(c, c.t0 + t)) return;
     if constexpr (KS == 4) {
         if (pair_matrix(c.n_pad, c.k_pad)) {  // c.b.pairs is null without a matrix
-            gains_wide_body<DT, KS, true>(gains_args(c, nullptr, c.n_pad), c.k_pad, int64_t(blockIdx.x) - wg_pre[j],
+            gains_wide_body<DT, KS, true>(gains_args(c, nullptr, c.n_pad), c.k_pad, bid - wg_pre[j],
                                           c.b.pairs);
             return;
         }
     }
-    gains_wide_body<DT, KS>(gains_args(c, nullptr, c.n_pad), c.k_pad, int64_t(blockIdx.x) - wg_pre[j]);
+    gains_wide_body<DT, KS>(gains_args(c, nullptr, c.n_pad), c.k_pad, bid - wg_pre[j]);
 }
 
 template <int DT, int KS>
@@ -319,12 +320,12 @@ void launch_w_ks(int32_t ks, const ebc_dataset* ds, const GainsArgs& ga, hipStre
 
 template <int DT>
 void launch_wb(int32_t ks, const InstDesc* descs, const int32_t* slot_inst, const int64_t* wg_pre, int32_t slots,
-               int64_t total_wgs, int32_t t, hipStream_t s) {
-    const dim3 g = dim3(unsigned(total_wgs)), b = dim3(256);
+               int64_t first, int64_t wgs, int32_t t, hipStream_t s) {
+    const dim3 g = dim3(unsigned(wgs)), b = dim3(256);
     if (ks == 4)
-        hipLaunchKernelGGL((kb_gains_wide<DT, 4>), g, b, 0, s, descs, slot_inst, wg_pre, slots, t);
+        hipLaunchKernelGGL((kb_gains_wide<DT, 4>), g, b, 0, s, descs, slot_inst, wg_pre, slots, first, t);
     else
-        hipLaunchKernelGGL((kb_gains_wide<DT, 1>), g, b, 0, s, descs, slot_inst, wg_pre, slots, t);
+        hipLaunchKernelGGL((kb_gains_wide<DT, 1>), g, b, 0, s, descs, slot_inst, wg_pre, slots, first, t);
 }
 
 }  // namespace
@@ -370,14 +371,14 @@ hipError_t launch_gains_wide(const ebc_dataset* ds, const GainsArgs& ga, hipStre
 }
 
 hipError_t launch_gains_wide_batched(int32_t dt, int32_t ksplit, const InstDesc* descs, const int32_t* slot_inst,
-                                     const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t,
+                                     const int64_t* wg_pre, int32_t slots, int64_t first, int64_t wgs, int32_t t,
                                      hipStream_t s) {
     switch (dt) {
-        case EBC_DT_F32: launch_wb<EBC_DT_F32>(ksplit, descs, slot_inst, wg_pre, slots, total_wgs, t, s); break;
-        case EBC_DT_F16: launch_wb<EBC_DT_F16>(ksplit, descs, slot_inst, wg_pre, slots, total_wgs, t, s); break;
-        case EBC_DT_BF16: launch_wb<EBC_DT_BF16>(ksplit, descs, slot_inst, wg_pre, slots, total_wgs, t, s); break;
+        case EBC_DT_F32: launch_wb<EBC_DT_F32>(ksplit, descs, slot_inst, wg_pre, slots, first, wgs, t, s); break;
+        case EBC_DT_F16: launch_wb<EBC_DT_F16>(ksplit, descs, slot_inst, wg_pre, slots, first, wgs, t, s); break;
+        case EBC_DT_BF16: launch_wb<EBC_DT_BF16>(ksplit, descs, slot_inst, wg_pre, slots, first, wgs, t, s); break;
         case EBC_DT_FP8_E4M3:
-            launch_wb<EBC_DT_FP8_E4M3>(ksplit, descs, slot_inst, wg_pre, slots, total_wgs, t, s);
+            launch_wb<EBC_DT_FP8_E4M3>(ksplit, descs, slot_inst, wg_pre, slots, first, wgs, t, s);
             break;
         default: return hipErrorInvalidValue;
     }

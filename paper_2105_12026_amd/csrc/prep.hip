@@ -127,12 +127,20 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
 hipError_t launch_gains_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst,
                                 const int64_t* wg_pre, int32_t slots, int64_t total_wgs, int32_t t, hipStream_t s) {
     const int32_t dt = bucket / 100000, k_pad = (bucket % 100000) / 10, variant = bucket % 10;
-    if (wide_rows(k_pad))
-        return launch_gains_wide_batched(dt, variant, descs, slot_inst, wg_pre, slots, total_wgs, t, s);
-    if (dt == EBC_DT_F32)
-        return launch_gains_f32_batched(k_pad, variant == 1, descs, slot_inst, wg_pre, slots, total_wgs, t, s);
     const int32_t kc = k_pad / (dt == EBC_DT_FP8_E4M3 ? 64 : 16);
-    return launch_gains_lp_batched(dt, kc, variant, descs, slot_inst, wg_pre, slots, total_wgs, t, s);
+    // a launch of 2^32 threads or more is cut off without an error
+    constexpr int64_t kMost = int64_t(1) << 22;
+    hipError_t e = hipSuccess;
+    for (int64_t first = 0; first < total_wgs && e == hipSuccess; first += kMost) {
+        const int64_t wgs = std::min(kMost, total_wgs - first);
+        if (wide_rows(k_pad))
+            e = launch_gains_wide_batched(dt, variant, descs, slot_inst, wg_pre, slots, first, wgs, t, s);
+        else if (dt == EBC_DT_F32)
+            e = launch_gains_f32_batched(k_pad, variant == 1, descs, slot_inst, wg_pre, slots, first, wgs, t, s);
+        else
+            e = launch_gains_lp_batched(dt, kc, variant, descs, slot_inst, wg_pre, slots, first, wgs, t, s);
+    }
+    return e;
 }
 
 hipError_t launch_gains_list_batched(int32_t bucket, const InstDesc* descs, const int32_t* slot_inst, int32_t slots,

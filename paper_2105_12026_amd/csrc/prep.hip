@@ -118,6 +118,7 @@ void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double
     c.variant = ds->variant;
     c.metric = ds->metric;
     c.lazy = greedy_list_steps(ds, k) > 0 ? 1 : 0;
+    if (k == 1) c.b.pairs = nullptr;  // no later step reads it
     c.chunk = gains_chunk(ds, ds->v_splits);
     c.sel = sel;
     c.f = f;

@@ -174,12 +174,20 @@ def _scratch(nbytes: int, device, stream=None) -> torch.Tensor:
     return t
 
 
+def _pair_matrix_bytes(n: int, d: int) -> int:
+    """The part of ebc_dataset_bytes that ebc_dataset_create can do without (see there)."""
+    n_pad = -(-n // 256) * 256
+    return 4 * n_pad * n_pad if d > 128 and n_pad <= 4096 else 0
+
+
 class Dataset:
     """A ground set V resident on the GPU (ebc_dataset_create).
 
     ``x`` is a float32 CUDA tensor [n, d]; it is kept alive by this object
     because the library borrows it. The workspace is a uint8 CUDA tensor of
-    exactly ``ebc_dataset_bytes(n, d, dtype)`` bytes."""
+    ``ebc_dataset_bytes(n, d, dtype)`` bytes, or, for the L1 distance and where
+    the device has no memory for it, of what is left without the pair matrix
+    (same results)."""
 
     def __init__(self, x: torch.Tensor, dtype: str = "f32", stream=None, dist: str = "sqeuclidean"):
         if not (isinstance(x, torch.Tensor) and x.is_cuda and x.dtype == torch.float32 and x.dim() == 2):
@@ -196,8 +204,15 @@ class Dataset:
         nbytes = L.ebc_dataset_bytes(self.n, self.d, DTYPES[dtype])
         if nbytes == 0:
             raise EBCError(1 if self.d <= MAX_DIM else 7, f"ebc_dataset_bytes(n={self.n}, d={self.d})")
-        self.workspace_bytes = int(nbytes)
-        self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.x.device)
+        least = int(nbytes) - _pair_matrix_bytes(self.n, self.d)
+        try:
+            self.workspace_bytes = least if dist == "l1" else int(nbytes)
+            self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.x.device)
+        except torch.cuda.OutOfMemoryError:
+            if least == self.workspace_bytes:
+                raise
+            self.workspace_bytes = least
+            self.workspace = torch.empty(least, dtype=torch.uint8, device=self.x.device)
         h = ctypes.c_void_p()
         _check(L.ebc_dataset_create(_ptr(self.x), self.n, self.d, DTYPES[dtype], DISTS[dist], _ptr(self.workspace),
                                     self.workspace_bytes, _stream(stream), ctypes.byref(h)),

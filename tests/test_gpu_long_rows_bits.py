@@ -46,3 +46,26 @@ def test_with_and_without_the_pair_matrix(n, d, dtype, window):
     sv.close()
     assert r["state"] == "done"
     assert all(np.array_equal(r[q], w) for q, w in zip(("sel", "f", "gain"), want))
+
+
+def test_workspace_without_the_pair_matrix():
+    """L1 data sets never use the matrix and take no room for it; others do without where there is none."""
+    n, d = 4096, 129
+    x = torch.from_numpy(near_duplicates(n, d, 1)).cuda()
+    whole = ebc.lib().ebc_dataset_bytes(n, d, 0)
+    matrix = 4 * n * n
+    assert ebc.Dataset(x, dist="l1").workspace_bytes == whole - matrix
+    ds = ebc.Dataset(x)
+    assert ds.workspace_bytes == whole
+    want = [q.cpu().numpy() for q in ds.greedy(9)]
+    del ds
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + matrix // 2) / total)
+        ds = ebc.Dataset(x)
+        got = [q.cpu().numpy() for q in ds.greedy(9)]
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert ds.workspace_bytes == whole - matrix
+    assert all(np.array_equal(a, b) for a, b in zip(got, want))

@@ -938,11 +938,6 @@ __device__ void rescore_split_sum(const InstDesc& c, int64_t blk, double (*red)[
     if (threadIdx.x < W) c.b.rpart[blk * kWindowMax + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__device__ void rescore_split_body(const InstDesc& c, int64_t blk) {
-    __shared__ double red[4][kBlock];
-    rescore_split_sum(c, blk, red);
-}
-
 // ---- fsum (one block per instance): f(S_t) = L({e0}) - |V|^-1 sum m_v ----
 __device__ void fsum_body(const InstDesc& c, int32_t t) {
     __shared__ double red[kBlock];
@@ -1312,7 +1307,6 @@ __global__ void __launch_bounds__(kBlock) k_update_split_small(InstDesc c, int32
     update_split_body(c, blockIdx.x, cs, rank);
 }
 __global__ void __launch_bounds__(kBlock) k_dist_window(InstDesc c) { dist_window_body(c, blockIdx.x, blockIdx.y); }
-__global__ void __launch_bounds__(kBlock) k_rescore_split(InstDesc c) { rescore_split_body(c, blockIdx.x); }
 __global__ void __launch_bounds__(kBlock) k_fsum(InstDesc c, int32_t t) { fsum_body(c, t); }
 __global__ void __launch_bounds__(kListSumThreads) k_list_sum(InstDesc c, int32_t part) {
     list_sum_body(c, part, blockIdx.x, gridDim.x);

@@ -50,9 +50,12 @@ void choose_lists(ebc_batch* bt, int32_t ticks) {
     bt->lists.assign(bt->count, 0);
     for (GainsBucket& b : bt->buckets) {
         b.lists = batched_lists_pay(b.key, b.worth, ticks);
+        const int32_t* inst = bt->h_slot_inst.data() + b.slot_begin;
+        int32_t rest = 0;
+        for (int32_t j = 0; j < b.slots; ++j) rest += batched_lists_worth(bt->ds[inst[j]]) > 0.0 ? 0 : 1;
         for (int32_t j = 0; j < b.slots; ++j) {
-            const int32_t i = bt->h_slot_inst[b.slot_begin + j];
-            bt->lists[i] = b.lists && batched_lists_worth(bt->ds[i]) > 0.0;
+            const ebc_dataset* ds = bt->ds[inst[j]];
+            bt->lists[inst[j]] = b.lists && (rest_lists(rest) ? can_list(ds) : batched_lists_worth(ds) > 0.0);
         }
     }
 }

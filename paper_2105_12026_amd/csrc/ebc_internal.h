@@ -312,11 +312,13 @@ int64_t gains_chunk(const ebc_dataset* ds, int32_t splits);
 int64_t gains_cand_tile(const ebc_dataset* ds);
 // Steps of a greedy run of k steps, alone, that score lists (lazy.h).
 int32_t greedy_list_steps(const ebc_dataset* ds, int32_t k);
-// What an instance adds to the worth of lists in its bucket of a batch (0: it
-// scores every candidate there), and whether a bucket of that worth scores
-// lists in runs of at most k steps.
+// Lists in a bucket of a batch: what an instance adds to their worth there (0:
+// nothing), whether a bucket of that worth scores lists in runs of at most k
+// steps, and whether, if it does, `rest` instances that add nothing do so too.
+bool can_list(const ebc_dataset* ds);
 double batched_lists_worth(const ebc_dataset* ds);
 bool batched_lists_pay(int32_t bucket, double worth, int32_t k);
+inline bool rest_lists(int32_t rest) { return rest <= 8; }
 int32_t gains_bucket(const ebc_dataset* ds);  // datasets with equal keys share a batched gains launch
 void fill_desc(const ebc_dataset* ds, int32_t k, int32_t* sel, double* f, double* gain, InstDesc* out);
 

@@ -83,11 +83,14 @@ int32_t greedy_list_steps(const ebc_dataset* ds, int32_t k) {
 // 2000 x 128 FP16 (0.043) 377 / 500; 200 of 2000 x 16 float32 (0.06) 445 / 340. By
 // the sum: FP16, 4 of 6000 x 128 (1.6) 80 / 102; BF16, 3 of 9000 x 64 (1.5) 77 / 81,
 // 11 (5.7) 175 / 111; FP8, 16 of 6000 x 33 (2.4) 138 / 131; float32, 4 of 6000 x 16
-// (2.1) 82 / 69.
+// (2.1) 82 / 69. A few small instances beside large ones score lists with them:
+// each costs 0.8 us a tick by that, their own full launches 3 to 25 us.
 double batched_lists_worth(const ebc_dataset* ds) {
     const double worth = greedy_lists_worth(ds);
     return worth >= (ds->dt == EBC_DT_F32 ? 0.05 : 0.1) ? worth : 0.0;
 }
+
+bool can_list(const ebc_dataset* ds) { return greedy_lists_worth(ds) > 0.0; }
 
 bool batched_lists_pay(int32_t bucket, double worth, int32_t k) {
     return lists_pay(worth, bucket / 100000 == EBC_DT_F32 ? 1.2 : 2.0, k);

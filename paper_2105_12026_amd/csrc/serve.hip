@@ -89,7 +89,8 @@ struct Request {
     std::vector<float> xh;
     int state = kQueued;
     int32_t t = 0;  // steps done
-    double worth = 0.0;  // of scoring lists (lazy.h); 0: never
+    bool can_list = false;
+    double worth = 0.0;  // of scoring lists (lazy.h)
     bool lists = false;  // its steps after the first score lists while the present requests are active
     size_t off = 0, bytes = 0;
     float* xd = nullptr;
@@ -183,7 +184,8 @@ ebc_status admit(ebc_server* sv, Request* r) {
     // gains tile variant from the autotuner's table (results do not depend on it)
     const int32_t v = tuned_variant(r->ds);
     if (v >= 0) r->ds->variant = v;
-    r->worth = r->k > 2 ? batched_lists_worth(r->ds) : 0.0;
+    r->can_list = r->k > 2 && can_list(r->ds);
+    r->worth = r->can_list ? batched_lists_worth(r->ds) : 0.0;
     r->state = kActive;
     r->t = 0;
     r->t_admit = now_s();
@@ -222,9 +224,12 @@ void rebuild_tables(ebc_server* sv) {
         b.slots = int32_t(sv->h_slot.size()) - b.slot_begin;
         b.total_wgs = acc;
         b.lists = batched_lists_pay(key, b.worth, INT32_MAX);
+        int32_t rest = 0;
+        for (int32_t j = b.slot_begin; j < b.slot_begin + b.slots; ++j)
+            rest += sv->active[sv->h_slot[j]]->worth > 0.0 ? 0 : 1;
         for (int32_t j = b.slot_begin; j < b.slot_begin + b.slots; ++j) {
             Request* r = sv->active[sv->h_slot[j]];
-            r->lists = b.lists && r->worth > 0.0;
+            r->lists = b.lists && (rest_lists(rest) ? r->can_list : r->worth > 0.0);
         }
         sv->buckets.push_back(b);
     }
@@ -368,7 +373,7 @@ ebc_status ebc_server_step(ebc_server* sv, int32_t* completed) {
         Request* r = sv->active[i];
         fill_desc(r->ds, r->k, r->sel_d, r->f_d, r->gain_d, &hd[i]);
         // others keep what a list needs: one may start when requests join
-        hd[i].lazy = r->lists ? 1 : (r->worth > 0.0 ? 2 : 0);
+        hd[i].lazy = r->lists ? 1 : (r->can_list ? 2 : 0);
         hd[i].t0 = r->t;
     }
     memcpy(h + sv->tl.row_pre, sv->h_row_pre.data(), sv->h_row_pre.size() * sizeof(int64_t));

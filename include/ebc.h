@@ -103,7 +103,8 @@ typedef enum {
  * most 4096 points it includes, at its end, room for one float per pair of
  * points (n rounded up to 256, squared), with which greedy steps after the
  * first need no dot products; ebc_dataset_create accepts a workspace without
- * it, and the served requests (ebc_request_bytes) do not count it. */
+ * it (L1 datasets never use it), with the same results, and the served
+ * requests (ebc_request_bytes) do not count it. */
 EBC_API size_t ebc_dataset_bytes(int64_t n, int32_t d, ebc_dtype dt);
 
 /* Make the ground set V resident and precompute what every evaluation reuses
@@ -221,12 +222,14 @@ EBC_API ebc_status ebc_marginal_gains(ebc_dataset* ds, const double* m, const in
  * within a window of the best is re-scored in float64 with direct
  * differences -> the best float64 gain wins, ties to the lowest index ->
  * m_v <- min(m_v, d(v, c*)) in float64 -> f(S_t) = L({e0}) - |V|^-1 sum m_v.
+ * At most 256 candidates are re-scored, those of largest computed gain where
+ * the window holds more.
  * The first step computes the gains of all n points. Where that takes longer
- * than a few launches (rows up to 128 values; the library decides by n and
- * d), a later step computes only those of the points whose earlier gain, an
- * upper bound of the present one because gains never grow, still reaches the
- * window: the same window, hence the same picks. While profiling is on every
- * step computes all n gains.
+ * than a few launches (rows up to 128 values; the library decides by n, d, the
+ * dtype and k), a later step computes only those of the points whose earlier
+ * gain, an upper bound of the present one because gains never grow, still
+ * reaches the window: the same window, hence the same picks, f and gains, bit
+ * for bit. While profiling is on every step computes all n gains.
  *   k         0 <= k <= n (k = 0 is a no-op).
  *   sel_out   [device] int32 [k]: selected indices in pick order.
  *   f_out     [device] float64 [k]: f(S_1) .. f(S_k).
@@ -307,13 +310,13 @@ EBC_API ebc_status ebc_sieve_streaming(ebc_dataset* ds, int32_t k, double eps, d
  * recorded once into a HIP graph (on a private stream; recording runs
  * nothing) and the graph is replayed on `stream` by every later call with
  * the same k, output pointers and gains variant; other calls re-record.
- * One graph launch replaces 8 to 11 kernel launches a step, which is what bounds small
- * problems. Results are identical to eager mode. Ignored while profiling. */
+ * One graph launch replaces 4 to 11 kernel launches a step (fewest for few
+ * points, most where lists are scored), which is what bounds small problems. Results are identical to eager mode. Ignored while profiling. */
 EBC_API ebc_status ebc_set_greedy_graph(ebc_dataset* ds, int32_t on);
 
 /* Batched greedy over many independent datasets (different n, d, k and
  * distance dtype). Per step tick the library issues one marginal-gains
- * launch per kernel bucket (same dtype, row padding and tile variant; two
+ * launch per kernel bucket (same dtype, row padding and tile variant; three
  * short ones where instances score lists, see ebc_greedy) and the step
  * launches, each covering every instance; instances whose k is
  * reached skip the remaining ticks. Every instance computes exactly what its
@@ -360,7 +363,7 @@ EBC_API ebc_status ebc_batch_info(ebc_batch* batch, int32_t* buckets, int64_t* g
  * ebc_server_step: one scheduler tick: admits queued requests in arrival
  * order while a slot is free and the head request fits the arena (the head
  * waits otherwise); advances every active request by one greedy step in one
- * batched launch set (one or two gains launches per kernel bucket, the step
+ * batched launch set (one or three gains launches per kernel bucket, the step
  * launches); copies out and releases the requests that reached k, waiting
  * for `stream` only when one did. Each request computes exactly what a solo
  * ebc_greedy computes, alone or in any mix.

@@ -450,7 +450,7 @@ kb_gains_f32_list(const InstDesc* __restrict__ descs, const int32_t* __restrict_
 // (a wide and a narrow workgroup of a chunk measured 2.7 and 1.2 us per 64
 // points at d = 100) plus a launch each. Full rounds go to the wide kernel, a
 // partial last one to the narrow: 50000 x 100, 2303 candidates: 288 wide
-// workgroups 321 us a call, 256 wide and 128 narrow ones 256 us; 5000: 485 and
+// workgroups 321 us a call, 256 wide and 128 narrow ones 243 us; 5000: 485 and
 // 445 us. A step over all of 1000 x 100 in 4 chunks: 33 -> 24 us.
 static int64_t wide_tiles(const GainsArgs& ga) {
     const int64_t tiles = (ga.n_cand + kGainsCandTile - 1) / kGainsCandTile;
